@@ -791,8 +791,8 @@ ug_status ug_launch_cost(const ug_kernel* k, void* const* buffers, uint32_t n_bu
                          uint32_t n, void* hip_stream, int64_t* host_ns, int64_t* gpu_ns);
 
 /* Tile variants (the autotuner of configuration 2).  The FP32 GEMM has 3
- * tile shapes (0: 128x128, 1: 64x64, 2: 32x32 with a four-way K split) and
- * the FP32 3x3 convolution 5 (output channels x pixel patch, 0: 128 x 8x16,
+ * tile shapes (0: 128x128, 1: 64x64 with a K split of two or four, 2: 32x32
+ * with a K split of four or eight) and the FP32 3x3 convolution 5 (output channels x pixel patch, 0: 128 x 8x16,
  * 1: 64 x 8x16, 2: 32 x 8x16, 3: 64 x 2x16 and 4: 32 x 2x16 with a four-way
  * K split); each launcher picks one by a fixed rule unless the process-wide
  * tuning table names one for the exact (op, shape).  Every variant computes

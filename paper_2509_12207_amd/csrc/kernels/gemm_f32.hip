@@ -1,42 +1,62 @@
-// C[M,N] = A[M,K] B[K,N], row-major FP32, on the FP32 matrix cores of gfx950.
+// C[M,N] = A[M,K] B[K,N], row-major FP32, on gfx950.
 //
-// One kernel template, three tile shapes, always four waves per workgroup:
-//   <WM, WN, TM, TN, KS>: the workgroup tile is (WM*TM*32) x (WN*TN*32); its
-//   waves form a WM x WN x KS grid; each wave owns TM x TN MFMA 32x32x2 tiles
-//   and one of KS slices of every K step.
-//   big   <2,2,2,2,1>: 128 x 128 tiles, 64 accumulators per lane;
-//   mid   <2,2,1,1,1>:  64 x  64 tiles;
-//   small <1,1,1,1,4>:  32 x  32 tiles, K split four ways inside the
-//                       workgroup and summed through LDS in a fixed order
-//                       (results do not depend on scheduling).
-// The launcher takes the largest tile that still gives two workgroups per CU
-// (or the small one), so a 256^3 product spreads over 64 CUs instead of 4,
-// unless the tuning table (an autotuner's measurements) names a variant
-// (0 big, 1 mid, 2 small) for the shape.
+// Every value is split into three bfloat16 pieces as it is staged, and the
+// products are formed by the BF16 matrix instruction (split.hpp: the error
+// against fp64 is 0.28-0.48 of the FP32 instruction's, the matrix cycles 2.67
+// times fewer).
 //
-// Operand tiles are staged through LDS, double buffered: the next K step is
-// fetched into registers while the current one feeds the matrix cores, then
-// written to the other buffer (one barrier per step).  A is stored K-major so
-// both operands are read as 32 consecutive floats per half-wave.
+// One kernel template <WM, WN, TM, TN, KS, BK, U>: the workgroup tile is
+// (WM*TM*32) x (WN*TN*32); its waves form a WM x WN x KS grid; each wave owns
+// TM x TN tiles of 32 x 32 and one of KS slices (BK values) of every K step;
+// operands are staged in units of U K values.
+//   big   <2,4,2,1,1,16,4>: 128 x 128 tiles, eight waves of 64 x 32;
+//   mid   <2,2,1,1,2,16,4> or, where K is long and no CU has more than one
+//         tile, <2,2,1,1,4,16,4>: 64 x 64, K split two or four ways;
+//   small <1,1,1,1,4,16,8> or <1,1,1,1,8,16,4>: 32 x 32, K split four or
+//         eight ways.
+// K slices are summed through LDS in a fixed order (results do not depend on
+// scheduling).
+//
+// What bounds it: at 4096^3 the matrix cores; six BF16 instructions per 16
+// products sustain 1.24 PFLOP/s there, more than the library's 8192^3 BF16
+// product (1.12) on the same card.  Smaller products are bound by the latency
+// of a step (global load, split, LDS, barrier) in the few waves a CU has,
+// hence eight waves for 128 x 128 (two such workgroups make four waves a
+// SIMD at 126 registers; four waves of 64 x 64 took 695 us at 4096^3 against
+// 670) and the K splits.  us per launch, FP32 instruction before -> now:
+//   4096^3 1170 -> 680, 2048^3 170 -> 95, 1280x2048x1024 65 -> 42,
+//   1003x2050x1021 102 -> 43, 1024^3 33 -> 18.3, 768x1280x256 11.1 -> 7.2,
+//   512^3 8.8 -> 7.1, 256x256x2048 26 -> 16, 256^3 5.8 -> 5.2.
+//
+// The pipeline of a step: while the products of the m pieces run, the next
+// step's values (in registers, loaded a step ahead) are split and written to
+// the other LDS buffer, six vector instructions per value interleaved with
+// the matrix instructions; after the step's only barrier the next fragments
+// are read under the remaining products.  The barrier waits for LDS only
+// (__syncthreads would also drain the global loads).
 //
 // Workgroups are dispatched round-robin over the 8 XCDs; the linear id is
 // remapped so each XCD works on a contiguous band of output tiles (sharing A
 // and B panels in its own L2), walked in groups of 8 tile-rows.
+#include <type_traits>
+
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
+#include "split.hpp"
 
 namespace ug {
 namespace {
 
-constexpr int BK = 16;      // K values per wave per step
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
+// s_waitcnt lgkmcnt(0) with the vmcnt and expcnt fields at their maxima
+constexpr int kWaitLdsOnly = 15 | (3 << 14) | (7 << 4) | (0 << 8);
 
 __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* tm, int* tn) {
   const int total = tiles_m * tiles_n;
-  int id = wg;
-  if (total % kXcds == 0) id = (wg % kXcds) * (total / kXcds) + wg / kXcds;
+  const int x = wg % kXcds;   // XCDs below total % kXcds have one tile more
+  const int id = x * (total / kXcds) + min(x, total % kXcds) + wg / kXcds;
   const int group = kGroupM * tiles_n;
   const int first_m = (id / group) * kGroupM;
   const int gm = min(tiles_m - first_m, kGroupM);
@@ -45,140 +65,340 @@ __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* t
   *tn = r / gm;
 }
 
-template <int WM, int WN, int TM, int TN, int KS>
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U>
 struct GemmCfg {
+  static constexpr int NT = 64 * WM * WN * KS;         // threads
   static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   static constexpr int BKT = BK * KS;                  // K values per step
-  static constexpr int SA = BM + 4, SB = BN + 4;       // LDS row strides
-  static constexpr int A4 = BM * BKT / 4 / 256;        // float4 per thread
-  static constexpr int B4 = BKT * BN / 4 / 256;
-  static constexpr int LDS = 2 * BKT * (SA + SB);      // floats
-  static_assert(WM * WN * KS == 4, "four waves");
-  static_assert(A4 >= 1 && B4 >= 1, "tile too small for 256 threads");
-  static_assert(BM * BKT % 1024 == 0 && BKT * BN % 1024 == 0, "even float4 split");
-  static_assert(KS == 1 || LDS >= (KS - 1) * 1024 * TM * TN, "reduction fits in LDS");
+  static constexpr int ROWS = BM + BN;                 // LDS rows: A's, then B's
+  static constexpr int ROWB = 2 * BK;                  // bytes per LDS row and piece
+  static constexpr int PIECE = ROWS * ROWB;            // bytes
+  static constexpr int STAGE = KS * 3 * PIECE;
+  static constexpr int UPR = BKT / U;                  // units per row and step
+  static constexpr int AU = BM * UPR / NT, BU = BN * UPR / NT;   // units per thread
+  static constexpr int LDS = 2 * STAGE;                // bytes
+  static_assert(BK == 16 || BK == 32, "one or two matrix instructions per row");
+  static_assert(BM * UPR % NT == 0 && BN * UPR % NT == 0, "even split of the units");
+  static_assert(KS == 1 || LDS >= (KS - 1) * 4096 * TM * TN * WM * WN, "reduction fits in LDS");
 };
 
-template <int WM, int WN, int TM, int TN, int KS, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                        const float* __restrict__ B,
-                                                        float* __restrict__ C, int M, int N,
-                                                        int K, unsigned* sig) {
-  using G = GemmCfg<WM, WN, TM, TN, KS>;
-  constexpr int BM = G::BM, BN = G::BN, BKT = G::BKT, SA = G::SA, SB = G::SB;
-  __shared__ float lds[G::LDS];
-  float* As0 = lds;
-  float* Bs0 = lds + 2 * BKT * SA;
+// The 16-byte chunks of a row are permuted so that a read of one chunk by
+// sixteen consecutive rows touches all 64 LDS banks once.
+template <int BK>
+__device__ __forceinline__ int swz(int row) {
+  return BK == 32 ? (row >> 2) & 3 : (row >> 3) & 1;
+}
+
+// Meets the workgroup once this wavefront's LDS accesses are done.  Unlike
+// __syncthreads it leaves global loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p) {   // raw, unbounded
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00027000);
+}
+__device__ __forceinline__ float buffer_load4(rsrc_t r, uint32_t off, uint32_t soff) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
+}
+__device__ __forceinline__ u32x4 buffer_load16(rsrc_t r, uint32_t off, uint32_t soff) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+
+// Issue order of what precedes: N times a matrix instruction, then V vector
+// instructions in its shadow.
+template <int N, int V>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U, bool WIDE>
+__global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) void gemm_f32_kernel(
+    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int M, int N,
+    int K, unsigned* sig) {
+  using G = GemmCfg<WM, WN, TM, TN, KS, BK, U>;
+  constexpr int BM = G::BM, BN = G::BN, BKT = G::BKT, NT = G::NT, UPR = G::UPR;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[G::LDS];
+  __shared__ int redo;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wave / (WM * WN);
   const int wm = (wave % (WM * WN)) / WN, wn = wave % WN;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int tm, tn;
   tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
+  if (tid == 0) redo = 0;
 
-  float4 ra[G::A4], rb[G::B4];
-  auto load = [&](int k0) {
+  // Staging units: eight K values of a row of A (contiguous in memory) or of
+  // a column of B (eight rows, consecutive threads on consecutive columns).
+  // Rows past M or N repeat the last one (their results are not stored).
+  // Loads are buffer loads: a resource that starts at the tile's first row or
+  // column and moves along K by scalar arithmetic, an offset per thread that
+  // stays, and a scalar offset per K row of B (no vector address arithmetic;
+  // A is read 16 bytes at a time at any alignment of its rows).  WIDE: K or N
+  // too large for 32-bit offsets, plain loads.
+  uint32_t pa[G::AU], pb[G::BU];  // byte offsets
+  int ra_row[G::AU], rb_col[G::BU];
+  int ka[G::AU], kb[G::BU];       // first K value of the unit in a step
+  int oa[G::AU], ob[G::BU];       // its LDS place (piece 0)
+  const auto place = [](int r, int q) {
+    const int k = q * U % BK;   // in the row
+    return q * U / BK * 3 * G::PIECE + r * G::ROWB + 16 * ((k / 8) ^ swz<BK>(r)) + 2 * (k % 8);
+  };
 #pragma unroll
-    for (int i = 0; i < G::A4; ++i) {
-      const int q = tid + 256 * i;
-      const int m = m0 + q / (BKT / 4);
-      const int k = k0 + 4 * (q % (BKT / 4));
-      if (VEC) {
-        ra[i] = (m < M && k < K) ? *reinterpret_cast<const float4*>(A + (size_t)m * K + k)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-      } else {
-        float v[4];
+  for (int i = 0; i < G::AU; ++i) {
+    const int u = tid + NT * i, r = u / UPR, q = u % UPR;
+    ka[i] = U * q;
+    ra_row[i] = min(m0 + r, M - 1);
+    pa[i] = ((uint32_t)(ra_row[i] - m0) * (uint32_t)K + U * q) * 4;
+    oa[i] = place(r, q);
+  }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (m < M && k + j < K) ? A[(size_t)m * K + k + j] : 0.f;
-        ra[i] = make_float4(v[0], v[1], v[2], v[3]);
+  for (int i = 0; i < G::BU; ++i) {
+    const int u = tid + NT * i, r = u % BN, q = u / BN;
+    kb[i] = U * q;
+    rb_col[i] = min(n0 + r, N - 1);
+    pb[i] = ((uint32_t)(rb_col[i] - n0) + (uint32_t)(U * q) * (uint32_t)N) * 4;
+    ob[i] = place(BM + r, q);
+  }
+  const float* a0 = A + (size_t)m0 * K;
+  const float* b0 = B + n0;
+
+  float ra[G::AU][U], rb[G::BU][U];   // the step staged next
+  auto load_a = [&](int k0) {
+    const rsrc_t rs = make_rsrc(a0 + k0);
+#pragma unroll
+    for (int i = 0; i < G::AU; ++i)
+#pragma unroll
+      for (int j = 0; j < U; j += 4) {
+        if constexpr (!WIDE) {
+          const u32x4 v = buffer_load16(rs, pa[i] + 4 * j, 0);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) ra[i][j + t] = __uint_as_float(v[t]);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            ra[i][j + t] = A[(size_t)ra_row[i] * K + k0 + ka[i] + j + t];
+        }
       }
-    }
+  };
+  auto load_b = [&](int k0) {
+    const rsrc_t rs = make_rsrc(b0 + (size_t)k0 * N);
 #pragma unroll
-    for (int i = 0; i < G::B4; ++i) {
-      const int q = tid + 256 * i;
-      const int k = k0 + q / (BN / 4);
-      const int n = n0 + 4 * (q % (BN / 4));
-      if (VEC) {
-        rb[i] = (k < K && n < N) ? *reinterpret_cast<const float4*>(B + (size_t)k * N + n)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-      } else {
-        float v[4];
+    for (int i = 0; i < G::BU; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (k < K && n + j < N) ? B[(size_t)k * N + n + j] : 0.f;
-        rb[i] = make_float4(v[0], v[1], v[2], v[3]);
+      for (int j = 0; j < U; ++j)
+        rb[i][j] = WIDE ? B[(size_t)(k0 + kb[i] + j) * N + rb_col[i]]
+                        : buffer_load4(rs, pb[i], j * N * 4);
+  };
+  // the first step: its K values from `kn` on are zero
+  auto load_first = [&](int kn) {
+#pragma unroll
+    for (int i = 0; i < G::AU; ++i)
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int k = ka[i] + j;
+        const float v = A[(size_t)ra_row[i] * K + min(k, kn - 1)];
+        ra[i][j] = k < kn ? v : 0.f;
       }
+#pragma unroll
+    for (int i = 0; i < G::BU; ++i)
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int k = kb[i] + j;
+        const float v = B[(size_t)min(k, kn - 1) * N + rb_col[i]];
+        rb[i][j] = k < kn ? v : 0.f;
+      }
+  };
+  uint32_t lost = 0;
+  auto put = [&](const float (&x)[U], unsigned char* at) {
+    uint32_t p[3][U / 2];
+#pragma unroll
+    for (int j = 0; j < U / 2; ++j)
+      split2(x[2 * j], x[2 * j + 1], &p[0][j], &p[1][j], &p[2][j], &lost);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if constexpr (U == 8)
+        *reinterpret_cast<uint4*>(at + j * G::PIECE) = make_uint4(p[j][0], p[j][1], p[j][2], p[j][3]);
+      else
+        *reinterpret_cast<uint2*>(at + j * G::PIECE) = make_uint2(p[j][0], p[j][1]);
     }
   };
-  auto store = [&](int buf) {
-    float* As = As0 + buf * BKT * SA;
-    float* Bs = Bs0 + buf * BKT * SB;
+  auto store_a = [&]() {
 #pragma unroll
-    for (int i = 0; i < G::A4; ++i) {
-      const int q = tid + 256 * i;
-      float* a = As + (4 * (q % (BKT / 4))) * SA + q / (BKT / 4);
-      a[0 * SA] = ra[i].x;
-      a[1 * SA] = ra[i].y;
-      a[2 * SA] = ra[i].z;
-      a[3 * SA] = ra[i].w;
-    }
-#pragma unroll
-    for (int i = 0; i < G::B4; ++i) {
-      const int q = tid + 256 * i;
-      *reinterpret_cast<float4*>(Bs + (q / (BN / 4)) * SB + 4 * (q % (BN / 4))) = rb[i];
-    }
+    for (int i = 0; i < G::AU; ++i) put(ra[i], lds + oa[i]);
   };
-
-  f32x16 acc[TM][TN];
+  auto store_b = [&]() {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
-
-  const int nk = (K + BKT - 1) / BKT;
-  load(0);
-  store(0);
-  __syncthreads();
+    for (int i = 0; i < G::BU; ++i) put(rb[i], lds + ob[i]);
+  };
 
   const int half = lane >> 5, col = lane & 31;
-  const int am = wm * TM * 32 + col, bn = wn * TN * 32 + col;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * BKT);
-    const float* as = As0 + buf * BKT * SA + ks * BK * SA;
-    const float* bs = Bs0 + buf * BKT * SB + ks * BK * SB;
+  constexpr int KH = BK / 16;   // matrix instructions per row and product
+  uint4 a[3][KH][TM], b[3][KH][TN];   // this wave's fragments, by piece
+  // (their rows start at a multiple of 32, so they have row col's permutation)
+  int fa[KH], fb[KH];
 #pragma unroll
-    for (int kk = 0; kk < BK / 2; ++kk) {
-      const int k = 2 * kk + half;
-      float a[TM], b[TN];
+  for (int h = 0; h < KH; ++h) {
+    const int c = ks * 3 * G::PIECE + 16 * ((2 * h + half) ^ swz<BK>(col));
+    fa[h] = c + (wm * TM * 32 + col) * G::ROWB;
+    fb[h] = c + (BM + wn * TN * 32 + col) * G::ROWB;
+  }
+  auto frag = [&](int p) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = as[k * SA + am + 32 * i];
+    for (int h = 0; h < KH; ++h) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = bs[k * SB + bn + 32 * j];
+      for (int i = 0; i < TM; ++i)
+        a[p][h][i] = *reinterpret_cast<const uint4*>(lds + fa[h] + p * G::PIECE +
+                                                     i * 32 * G::ROWB);
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        b[p][h][j] = *reinterpret_cast<const uint4*>(lds + fb[h] + p * G::PIECE +
+                                                     j * 32 * G::ROWB);
+    }
+  };
+  // to the other buffer
+  int stage = G::STAGE;
+  auto flip = [&]() {
+#pragma unroll
+    for (int i = 0; i < G::AU; ++i) oa[i] += stage;
+#pragma unroll
+    for (int i = 0; i < G::BU; ++i) ob[i] += stage;
+#pragma unroll
+    for (int h = 0; h < KH; ++h) {
+      fa[h] += stage;
+      fb[h] += stage;
+    }
+    stage = -stage;
+  };
+  f32x16 ah[TM][TN], as[TM][TN];   // sums of hh, of the other five products
+  auto mul = [&](int p, int q, f32x16 (&d)[TM][TN]) {
+#pragma unroll
+    for (int h = 0; h < KH; ++h)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x2(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < TN; ++j) d[i][j] = mfma_bf16(a[p][h][i], b[q][h][j], d[i][j]);
+  };
+
+  // The first step takes what K leaves over from whole ones.  Step kt: the
+  // next step's values are split and written to the other buffer among the
+  // products of m, and its fragments are read after the barrier, each piece
+  // once this step's products of it are done.
+  const int nk = (K - 1) / BKT + 1;
+  const int first = K - (nk - 1) * BKT;
+  if (TM * TN == 1 && first == BKT) {   // (the big tile has no registers for a branch)
+    load_a(0);
+    load_b(0);
+  } else {
+    load_first(first);
+  }
+  store_a();
+  store_b();
+  if (nk > 1) {
+    load_a(first);
+    load_b(first);
+  }
+  lds_barrier();
+  frag(1);
+  frag(2);
+  frag(0);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
+  __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
+#pragma clang loop unroll(disable)
+  for (int kt = 0; kt + 1 < nk; ++kt) {
+    flip();
+    const int k2 = first + min(kt + 1, nk - 2) * BKT;   // the last one again, unused
+    mul(1, 1, as);
+    store_a();
+    load_a(k2);
+    interleave<KH * TM * TN, (6 * U * G::AU + KH * TM * TN - 1) / (KH * TM * TN)>();
+    mul(1, 0, as);
+    store_b();
+    load_b(k2);
+    interleave<KH * TM * TN, (6 * U * G::BU + KH * TM * TN - 1) / (KH * TM * TN)>();
+    mul(0, 1, as);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    frag(1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(2, 0, as);
+    mul(0, 2, as);
+    __builtin_amdgcn_sched_barrier(0);
+    frag(2);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(0, 0, ah);
+    frag(0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  mul(1, 1, as);
+  mul(1, 0, as);
+  mul(0, 1, as);
+  mul(2, 0, as);
+  mul(0, 2, as);
+  mul(0, 0, ah);
+
+  bool bad = (lost & 0xffffu) != 0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      ah[i][j] += as[i][j];
+      bad = bad || !finite16(ah[i][j]);
     }
-    if (kt + 1 < nk) store(buf ^ 1);
-    __syncthreads();
+  if (bad) redo = 1;
+  __syncthreads();   // also: every read of the stages is done
+  if (redo) {   // inputs without a split: the FP32 instruction, from memory
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) ah[i][j] = zero16();
+    for (int64_t k0 = ks * BK; k0 < K; k0 += BKT)
+      for (int64_t k = k0 + half; k < k0 + BK; k += 2) {
+        float x[TM], y[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int m = min(m0 + (wm * TM + i) * 32 + col, M - 1);
+          x[i] = k < K ? A[(size_t)m * K + k] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int n = min(n0 + (wn * TN + j) * 32 + col, N - 1);
+          y[j] = k < K ? B[(size_t)k * N + n] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) ah[i][j] = mfma_32x32x2(x[i], y[j], ah[i][j]);
+      }
   }
 
   if (KS > 1) {
     // K slices 1..KS-1 hand their partial sums to slice 0 through LDS; slice
     // 0 adds them in slice order.
     constexpr int PER = TM * TN * 16 * 64;   // floats per wave
+    float* red0 = reinterpret_cast<float*>(lds);
     if (ks > 0) {
-      float* red = lds + (ks - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
+      float* red = red0 + (ks - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) red[((i * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+          for (int r = 0; r < 16; ++r) red[((i * TN + j) * 16 + r) * 64 + lane] = ah[i][j][r];
     }
     __syncthreads();
     if (ks > 0) {   // handed over: meet slice 0 at the counter's barrier, then leave
@@ -187,13 +407,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
 #pragma unroll
     for (int s = 1; s < KS; ++s) {
-      const float* red = lds + (s - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
+      const float* red = red0 + (s - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * TN + j) * 16 + r) * 64 + lane];
+          for (int r = 0; r < 16; ++r) ah[i][j][r] += red[((i * TN + j) * 16 + r) * 64 + lane];
     }
   }
 
@@ -206,7 +426,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int m = m0 + wm * TM * 32 + 32 * i + mfma32_row(r, lane);
-        if (m < M) C[(size_t)m * N + n] = acc[i][j][r];
+        if (m < M) C[(size_t)m * N + n] = ah[i][j][r];
       }
     }
   group_done(sig);
@@ -216,11 +436,16 @@ enum Shape { kBig = 0, kMid = 1, kSmall = 2 };
 
 int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 
+// Two 64 x 64 workgroups share a CU, and up to 512 of them finish together;
+// past that 128 x 128 is faster (1280x2048x1024, 640 / 160 tiles: 42 against
+// 44 us; 1024x2048x1024, 512 / 128: 41 against 32), unless the matrix's edge
+// would leave a quarter of its work as padding.  64 x 64 needs about 160
+// tiles to beat 32 x 32 (768x1024x512, 192 / 768 tiles: 10.6 against 12.2 us;
+// 512x1024x512, 128 / 512: 10.4 against 9.6).
 Shape pick(int64_t M, int64_t N) {
-  constexpr int64_t kWant = 512;   // two workgroups per CU
-  if (tiles(M, N, 128, 128) >= kWant) return kBig;
-  if (tiles(M, N, 64, 64) >= kWant / 2) return kMid;
-  return kSmall;
+  const int64_t t64 = tiles(M, N, 64, 64);
+  if (t64 > 512 && 3 * tiles(M, N, 128, 128) <= t64) return kBig;
+  return t64 >= 160 ? kMid : kSmall;
 }
 
 // The variant asked for, else the tuning table's, else the rule above.
@@ -232,62 +457,43 @@ Shape choose(int64_t M, int64_t N, int64_t K, int variant) {
   return variant >= 0 && variant < 3 ? static_cast<Shape>(variant) : pick(M, N);
 }
 
-template <int WM, int WN, int TM, int TN, int KS>
-const void* fn(bool vec) {
-  return vec ? reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, true>)
-             : reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, false>);
-}
-
-template <int WM, int WN, int TM, int TN, int KS>
-void launch(bool vec, dim3 grid, hipStream_t s, const float* A, const float* B, float* C, int M,
-            int N, int K, unsigned* sig) {
-  if (vec)
-    hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TN, KS, true>), grid, dim3(256), 0, s, A, B,
-                       C, M, N, K, sig);
-  else
-    hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TN, KS, false>), grid, dim3(256), 0, s, A, B,
-                       C, M, N, K, sig);
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U>
+OpPlan plan(int64_t M, int64_t N, bool wide) {
+  OpPlan p;
+  p.func = wide ? reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, true>)
+                : reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, false>);
+  p.grid = dim3((unsigned)tiles(M, N, WM * TM * 32, WN * TN * 32));
+  p.block = dim3(64 * WM * WN * KS);
+  return p;
 }
 
 }  // namespace
 
-static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool vec, int variant) {
-  OpPlan p;
-  p.block = dim3(256);
+OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, int variant) {
+  // 32-bit offsets within a step's panels: 128 rows of K values, 128 of N
+  const bool wide = K >= (1 << 22) || N >= (1 << 22);
   switch (choose(M, N, K, variant)) {
     case kBig:
-      p.func = fn<2, 2, 2, 2, 1>(vec);
-      p.grid = dim3((unsigned)tiles(M, N, 128, 128));
-      break;
+      return plan<2, 4, 2, 1, 1, 16, 4>(M, N, wide);
     case kMid:
-      p.func = fn<2, 2, 1, 1, 1>(vec);
-      p.grid = dim3((unsigned)tiles(M, N, 64, 64));
-      break;
+      // one tile a CU at most: eight more waves pay once K is long
+      // (4096x256x4096 71 -> 62 us, 1024^3 18.8 -> 18.3, K = 256 7.2 -> 7.6)
+      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4>(M, N, wide)
+                                                     : plan<2, 2, 1, 1, 2, 16, 4>(M, N, wide);
     default:
-      p.func = fn<1, 1, 1, 1, 4>(vec);
-      p.grid = dim3((unsigned)tiles(M, N, 32, 32));
+      // the same for 32 x 32 (256x256x2048 19.7 -> 16.3 us, 512^3 7.6 -> 7.1;
+      // with 512 tiles 9.6 -> 12.6)
+      return K >= 512 && tiles(M, N, 32, 32) <= 256 ? plan<1, 1, 1, 1, 8, 16, 4>(M, N, wide)
+                                                    : plan<1, 1, 1, 1, 4, 16, 8>(M, N, wide);
   }
-  return p;
 }
 
 hipError_t gemm_f32_launch(const float* A, const float* B, float* C, int64_t M, int64_t N,
                            int64_t K, hipStream_t s, unsigned* sig, int variant) {
-  const bool vec = (K % 4 == 0) && (N % 4 == 0) && aligned16(A) && aligned16(B);
-  const Shape sh = choose(M, N, K, variant);
-  OpPlan p = gemm_f32_plan(M, N, K, vec, static_cast<int>(sh));
-  switch (sh) {
-    case kBig:
-      launch<2, 2, 2, 2, 1>(vec, p.grid, s, A, B, C, (int)M, (int)N, (int)K, sig);
-      break;
-    case kMid:
-      launch<2, 2, 1, 1, 1>(vec, p.grid, s, A, B, C, (int)M, (int)N, (int)K, sig);
-      break;
-    default:
-      launch<1, 1, 1, 1, 4>(vec, p.grid, s, A, B, C, (int)M, (int)N, (int)K, sig);
-  }
-  return hipGetLastError();
+  const OpPlan p = gemm_f32_plan(M, N, K, variant);
+  int m = (int)M, n = (int)N, k = (int)K;
+  void* args[] = {&A, &B, &C, &m, &n, &k, &sig};
+  return hipLaunchKernel(p.func, p.grid, p.block, args, p.lds, s);
 }
 
 }  // namespace ug

@@ -1,0 +1,79 @@
+// FP32 products on the BF16 matrix cores of gfx950, with FP32 accuracy.
+//
+// An FP32 value is exactly the sum of three bfloat16 values: h is x rounded
+// to nearest, m is x - h rounded to nearest, l is the rest (24 = 3 x 8
+// significant bits; both differences are exact).  Of the nine products of two
+// split values the six of relative size 2^-16 and more are formed:
+//   hh | mh hm | lh hl mm
+// and hm, mh, lh, hl, mm are accumulated apart from hh.  What is left out (lm,
+// ml, ll) is below 2^-25 of the product, with no sign of its own.  BF16 x BF16
+// is exact in FP32; the matrix instruction rounds its FP32 accumulator once
+// per 16 products, where the FP32 instruction rounds once per product, so the
+// sum is closer to the exact one: against fp64 the error (rms) of a K-long
+// product is 0.28-0.40 of the FP32 instruction's for uniform and normal values
+// and K = 32 to 4096, and 0.36-0.48 where all products are positive.
+//
+// Rate: six v_mfma_f32_32x32x16_bf16 (32 cycles each) take the place of eight
+// v_mfma_f32_32x32x2_f32 (64 cycles each): 2.67 times fewer matrix cycles.
+// The split costs six vector instructions per staged element, paid once per
+// element and workgroup tile.
+//
+// Two kinds of input have no such split: values that are not finite (or
+// round to infinity in bfloat16), which turn every output they touch into
+// a NaN, and values below about 2^-109, whose l is not a bfloat16 value.
+// Both are noticed (the outputs; the lower halves of the l's) and the
+// workgroup then computes its tile again with the FP32 instruction.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "mfma.hpp"
+
+namespace ug {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x16 mfma_bf16(uint4 a, uint4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                 __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {   // nearest even
+  const f32x2_t v = {x, y};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+// Splits a pair; `lost` collects the bits of l that bfloat16 cannot hold
+// (its lower half).
+__device__ __forceinline__ void split2(float x, float y, uint32_t* h, uint32_t* m, uint32_t* l,
+                                       uint32_t* lost) {
+  *h = pack_bf16(x, y);
+  const float rx = x - __uint_as_float(*h << 16);
+  const float ry = y - __uint_as_float(*h & 0xffff0000u);
+  *m = pack_bf16(rx, ry);
+  const uint32_t lx = __float_as_uint(rx - __uint_as_float(*m << 16));
+  const uint32_t ly = __float_as_uint(ry - __uint_as_float(*m & 0xffff0000u));
+  *l = __builtin_amdgcn_perm(ly, lx, 0x07060302u);
+  *lost |= lx | ly;
+}
+
+// Eight consecutive K values of a row -> the 16-byte chunk of each piece.
+__device__ __forceinline__ void split8(const float (&x)[8], uint4* p, uint32_t* lost) {
+  split2(x[0], x[1], &p[0].x, &p[1].x, &p[2].x, lost);
+  split2(x[2], x[3], &p[0].y, &p[1].y, &p[2].y, lost);
+  split2(x[4], x[5], &p[0].z, &p[1].z, &p[2].z, lost);
+  split2(x[6], x[7], &p[0].w, &p[1].w, &p[2].w, lost);
+}
+
+__device__ __forceinline__ bool finite16(f32x16 v) {
+  bool ok = true;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) ok = ok && (__float_as_uint(v[r]) & 0x7f800000u) != 0x7f800000u;
+  return ok;
+}
+
+}  // namespace ug

@@ -1,0 +1,77 @@
+"""The FP32 contractions on the BF16 matrix cores: every value split into
+three bfloat16 pieces, six of nine products (csrc/kernels/split.hpp).
+
+Accuracy: the matrix instruction rounds its accumulator once per 16 products
+(at most one unit in the last place, 2^-23, of a partial sum that the sum of
+|products| bounds), the five small products have an accumulator of their own
+(below 2^-7 of that), and the products left out are below 2^-24 of the sum:
+(K / 16 + 8) * 2^-23 of the sum of |products| covers all of it.
+
+Values without a split (infinities, NaN, values that round to infinity in
+bfloat16, values below about 2^-109) are computed by the FP32 instruction and
+come out as before."""
+
+import numpy as np
+import pytest
+
+import test_gpu_kernels as G
+from oracle import kernels as OK
+
+pytestmark = pytest.mark.gpu
+
+
+def bound(K):
+    return (K / 16 + 8) * 2.0 ** -23
+
+
+# each tile with its K splits, at and around their edges: 128x128; 64x64 split
+# two and four ways; 32x32 split four and eight ways; rows longer than 2^22
+@pytest.mark.parametrize("M,N,K", [(1500, 1700, 33), (1537, 1665, 16), (700, 1100, 65),
+                                   (1000, 1000, 1030), (65, 33, 64), (31, 32, 63),
+                                   (200, 130, 600), (1, 5, 129), (3, (1 << 22) + 1, 5),
+                                   (2, 3, (1 << 22) + 5)])
+def test_gemm_error(M, N, K):
+    r = np.random.default_rng(M + 3 * N + 5 * K)
+    A = r.standard_normal((M, K)).astype(np.float32)
+    B = r.standard_normal((K, N)).astype(np.float32)
+    C = G.run_gemm(A, B)
+    ref, scale = OK.gemm_f64(A, B), OK.gemm_abs_f64(A, B)
+    assert np.all(np.abs(C - ref) <= bound(K) * scale), np.max(np.abs(C - ref) / scale)
+
+
+def same_kind(got, ref):
+    """Infinities and NaN where the exact result has them."""
+    with np.errstate(over="ignore"):
+        want = ref.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf]) and not np.isinf(got[~inf]).any()
+    return np.isfinite(want)
+
+
+@pytest.mark.parametrize("M,N,K", [(70, 90, 40), (1500, 1700, 20), (700, 1100, 48)])
+def test_gemm_values_without_a_split(M, N, K):
+    r = np.random.default_rng(M)
+    A = r.uniform(0.5, 1, (M, K)).astype(np.float32)
+    B = r.uniform(-1, 1, (K, N)).astype(np.float32)
+    A[3, 5], A[9, 0], A[17, K - 1] = np.inf, -np.inf, np.nan
+    A[21, 7], B[7, :] = 3.4e38, np.float32(2.0 ** -40)   # rounds to infinity in bfloat16
+    B[2, N - 1] = np.inf
+    with np.errstate(invalid="ignore"):
+        ref = A.astype(np.float64) @ B.astype(np.float64)
+        scale = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+    C = G.run_gemm(A, B)
+    ok = same_kind(C, ref)
+    assert np.all(np.abs(C - ref)[ok] <= K * 2.0 ** -23 * scale[ok])
+
+
+@pytest.mark.parametrize("lo", [-112, -126, -140])
+def test_gemm_tiny_values(lo):
+    M, N, K = 100, 70, 50
+    r = np.random.default_rng(-lo)
+    A = (r.uniform(1, 2, (M, K)) * 2.0 ** lo).astype(np.float32)
+    B = (r.uniform(1, 2, (K, N)) * 2.0 ** 100).astype(np.float32)
+    A[::2] = 0.0
+    C = G.run_gemm(A, B)
+    ref, scale = OK.gemm_f64(A, B), OK.gemm_abs_f64(A, B)
+    assert np.all(np.abs(C - ref) <= K * 2.0 ** -23 * scale)
