@@ -469,7 +469,7 @@ OpPlan plan(int64_t M, int64_t N, bool wide) {
 
 }  // namespace
 
-OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, int variant) {
+OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
   // 32-bit offsets within a step's panels: 128 rows of K values, 128 of N
   const bool wide = K >= (1 << 22) || N >= (1 << 22);
   switch (choose(M, N, K, variant)) {
@@ -490,7 +490,7 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, int variant) {
 
 hipError_t gemm_f32_launch(const float* A, const float* B, float* C, int64_t M, int64_t N,
                            int64_t K, hipStream_t s, unsigned* sig, int variant) {
-  const OpPlan p = gemm_f32_plan(M, N, K, variant);
+  const OpPlan p = gemm_f32_plan(M, N, K, true, variant);
   int m = (int)M, n = (int)N, k = (int)K;
   void* args[] = {&A, &B, &C, &m, &n, &k, &sig};
   return hipLaunchKernel(p.func, p.grid, p.block, args, p.lds, s);

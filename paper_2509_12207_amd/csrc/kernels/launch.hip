@@ -259,7 +259,7 @@ int chosen_variant(const ug_kernel& k) {
       if (v >= 0) return v;
       // the plan's function tells the rule's choice apart
       for (int i = 0; i < tile_variants(UG_OP_GEMM_F32); ++i)
-        if (gemm_f32_plan(s[0], s[1], s[2], i).func == gemm_f32_plan(s[0], s[1], s[2]).func)
+        if (gemm_f32_plan(s[0], s[1], s[2], true, i).func == gemm_f32_plan(s[0], s[1], s[2], true).func)
           return i;
       return -1;
     }
@@ -279,7 +279,7 @@ OpPlan plan_kernel(const ug_kernel& k, int variant) {
   const int64_t* s = k.shape;
   switch (k.op) {
     case UG_OP_GEMM_F32:
-      return gemm_f32_plan(s[0], s[1], s[2], variant);
+      return gemm_f32_plan(s[0], s[1], s[2], true, variant);
     case UG_OP_BIAS_RELU_F32:
       return bias_relu_f32_plan(s[0], s[1], (int)s[2], s[1] % 4 == 0);
     case UG_OP_CONV3X3_F32:

@@ -19,7 +19,8 @@ struct OpPlan {
   size_t lds = 0;
 };
 
-OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, int variant = -1);
+// `vec` (operands readable 16 bytes at a time) does not change the plan.
+OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool vec, int variant = -1);
 hipError_t gemm_f32_launch(const float* A, const float* B, float* C, int64_t M, int64_t N,
                            int64_t K, hipStream_t s, unsigned* sig = nullptr, int variant = -1);
 
