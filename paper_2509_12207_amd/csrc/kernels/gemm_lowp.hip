@@ -19,24 +19,31 @@
 //   +7.  A 64-byte K slice (32 values) takes two of them: lane l reads 16-
 //   byte chunk l / 32 for the first and chunk 2 + l / 32 for the second.
 //
-// Kernels, all with a 256 x 256 workgroup tile:
+// One kernel, gemm_ring<type, CONV, RAGGED, WM, WN, TM, TN, KS, NST>: a
+// workgroup of WM x WN x KS waves computes a (WM*TM*32) x (WN*TN*32) tile,
+// each wave TM x TN products of 32 x 32 over every KS-th 64-byte K slice
+// (a step).  Global memory goes straight to LDS (global_load_lds_dwordx4)
+// into a ring of NST stages per K slice, NST - 1 stages ahead of the matrix
+// cores; the fragments of step s+1 are read from LDS while step s runs.  One
+// barrier a step.  LDS rows are 64 bytes with the four 16-byte chunks of row
+// r XOR-permuted by (r / 4) % 4: a 16-byte read by sixteen consecutive rows
+// then touches all 64 LDS banks once.  The direct-to-LDS loads are issued
+// from inline assembly so that the compiler, which cannot tell them apart
+// from the ring slots being read, does not wait for every load in flight
+// before each LDS read; their completion is waited for explicitly (vmcnt)
+// before each barrier.  K slices are summed through LDS in a fixed order.
+// RAGGED (FP8 rows that are not a multiple of 64 bytes): the chunks past the
+// row's end are read from a zero slice.
 //
-// * gemm_ring<FP8 | BF16> (rows a multiple of 64 bytes: K % 64 == 0 for
-//   FP8, K % 32 == 0 for BF16): eight waves of 128 x 64 (two per SIMD).
-//   Global memory goes straight to LDS (global_load_lds_dwordx4) into a
-//   ring of four 32 KiB stages, three stages ahead of the matrix cores; the
-//   fragments of step s+1 are read from LDS while step s runs.  One barrier
-//   a step.  LDS rows are 64 bytes with the four 16-byte chunks of row r
-//   XOR-permuted by (r / 4) % 4: a 16-byte read by sixteen consecutive rows
-//   then touches all 64 LDS banks once.  The direct-to-LDS loads are issued
-//   from inline assembly so that the compiler, which cannot tell them apart
-//   from the ring slots being read, does not wait for every load in flight
-//   before each LDS read; their completion is waited for explicitly
-//   (vmcnt) before each barrier.
-//
-// * gemm_fp8_kernel (FP8, any K multiple of 16): four waves of 128 x 128;
-//   the next 128-byte K step is fetched into registers while the current
-//   one, in two padded LDS stages, feeds the matrix cores.
+// What bounds it, and the tiles: 256 x 256 is bound by the rate at which
+// panels stream into LDS (about 7.9 TB/s over the chip) and needs about 144
+// tiles to fill it; anything smaller left most CUs idle, and a short product
+// is a chain of steps whose latency (barrier, LDS, loads) K slices divide.
+// us per launch, 256 x 256 only -> now: BF16 4096^3 134, 2048^3 47 -> 24,
+// 1280x1792x768 22 -> 9.2, 1024^3 25 -> 6.5, 512^3 16 -> 4.1, 256x256x2048
+// 42 -> 5.9; BF16 convolution C = 256, 256^2 100, C = 128, 128^2 45 -> 17,
+// C = 64, 128^2 26 -> 8.6, C = 256, 32^2 80 -> 8.9; FP8 2048x8192x8192 125,
+// 2048^3 27 -> 14, 1024^3 15 -> 4.9.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -46,25 +53,15 @@ namespace {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int BM = 256, BN = 256;   // workgroup tile
-constexpr int BK = 128;             // bytes of K per step
-constexpr int LDR = BK + 16;        // LDS row stride (bytes)
-constexpr int ROWS = BM + BN;       // LDS rows per stage (A then B)
-constexpr int STAGE = ROWS * LDR;   // bytes per stage
-constexpr int CHUNKS = ROWS * BK / 16 / 256;   // 16-byte loads per thread per step
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 // s_waitcnt lgkmcnt(0) with the vmcnt and expcnt fields at their maxima
 constexpr int kWaitLdsOnly = 15 | (3 << 14) | (7 << 4) | (0 << 8);
 
-// K offset (within a 64-byte slice) of the 8-byte piece p (0..3) of lane
-// group g (= lane / 32) of a matrix-core operand.
-__device__ __forceinline__ int kpos(int g, int p) { return 32 * g + 8 * p; }
-
 __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* tm, int* tn) {
   const int total = tiles_m * tiles_n;
-  int id = wg;
-  if (total % kXcds == 0) id = (wg % kXcds) * (total / kXcds) + wg / kXcds;
+  const int x = wg % kXcds;   // XCDs below total % kXcds have one tile more
+  const int id = x * (total / kXcds) + min(x, total % kXcds) + wg / kXcds;
   const int group = kGroupM * tiles_n;
   const int first_m = (id / group) * kGroupM;
   const int gm = min(tiles_m - first_m, kGroupM);
@@ -73,124 +70,8 @@ __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* t
   *tn = r / gm;
 }
 
-__device__ __forceinline__ i32x8 load_frag(const unsigned char* row, int g) {
-  i32x8 v;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int2 w = *reinterpret_cast<const int2*>(row + kpos(g, p));
-    v[2 * p] = w.x;
-    v[2 * p + 1] = w.y;
-  }
-  return v;
-}
-
-__global__ __launch_bounds__(256, 1) void gemm_fp8_kernel(const unsigned char* __restrict__ A,
-                                                          const unsigned char* __restrict__ Bt,
-                                                          float* __restrict__ C, int M, int N,
-                                                          int K) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  int tm, tn;
-  tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  // global -> register mapping: chunk c = tid + 256 u covers LDS row c / 8
-  // (rows 0..255 of A, 256..511 of Bt), bytes 16 (c % 8) of the step, i.e.
-  // row rA + 32 u of A (u < 8) or rB + 32 (u - 8) of Bt.  Chunks of rows
-  // past M or N, or past K, are zeroed: the loads themselves are
-  // unconditional (no branches in the stream).
-  const int part = tid & 7;
-  const int rA = m0 + (tid >> 3), rB = n0 + (tid >> 3);
-  auto fetch = [&](uint4 (&reg)[CHUNKS], int k0) {
-    const bool kin = k0 + 16 * part < K;
-#pragma unroll
-    for (int u = 0; u < CHUNKS; ++u) {
-      const bool isa = u < CHUNKS / 2;
-      const int row = (isa ? rA : rB) + 32 * (u % (CHUNKS / 2));
-      const bool ok = row < (isa ? M : N) && kin;
-      // a zeroed chunk reads the first 16 bytes of its matrix (always there:
-      // K >= 16), never past the end
-      const unsigned char* X = isa ? A : Bt;
-      const unsigned char* p = ok ? X + (int64_t)row * K + 16 * part + k0 : X;
-      const uint4 v = *reinterpret_cast<const uint4*>(p);
-      reg[u] = ok ? v : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto stash = [&](const uint4 (&reg)[CHUNKS], int stage) {
-    unsigned char* base = lds + stage * STAGE;
-#pragma unroll
-    for (int u = 0; u < CHUNKS; ++u) {
-      const int c = tid + 256 * u;
-      *reinterpret_cast<uint4*>(base + (c >> 3) * LDR + 16 * (c & 7)) = reg[u];
-    }
-  };
-
-  f32x16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = zero16();
-
-  const int g = lane >> 5, r32 = lane & 31;
-  auto compute = [&](int stage) {
-    const unsigned char* base = lds + stage * STAGE;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 64) {
-      i32x8 a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = load_frag(base + (wm * 128 + i * 32 + r32) * LDR + kk, g);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        b[j] = load_frag(base + (BM + wn * 128 + j * 32 + r32) * LDR + kk, g);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i], b[j], acc[i][j], 0, 0,
-                                                                      0, 127, 0, 127);
-      // keep each 64-byte slice's operands live on their own (64 VGPRs)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  // the next step is fetched into registers while the current one, in LDS,
-  // feeds the matrix cores
-  const int steps = (K + BK - 1) / BK;
-  uint4 reg[CHUNKS];
-  fetch(reg, 0);
-  stash(reg, 0);
-  __syncthreads();
-  for (int s = 0; s < steps; ++s) {
-    if (s + 1 < steps) fetch(reg, (s + 1) * BK);
-    compute(s & 1);
-    if (s + 1 < steps) stash(reg, (s + 1) & 1);
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + wn * 128 + j * 32 + r32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 128 + i * 32 + mfma32_row(r, lane);
-        if (row < M && col < N) C[(int64_t)row * N + col] = acc[i][j][r];
-      }
-    }
-}
-
-
 // ------------------------------------------------------------ ring kernel
 constexpr int RK = 64;                       // bytes of K per step
-constexpr int RNST = 4;                      // ring stages
-constexpr int RSTAGE = (BM + BN) * RK;       // 32 KiB per stage
-constexpr int RWAVES = 8;
-constexpr int RCPT = (BM + BN) * RK / 16 / (64 * RWAVES);   // 16-byte loads per lane per stage
-constexpr int RNF = 2;                       // B fragments per wave (wave tile 128 x 64)
 enum RingType { kRingFp8 = 0, kRingBf16 = 1 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -223,40 +104,65 @@ __device__ __forceinline__ int ring_chunk(int g, int h) {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(int4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// 64 zero bytes: the K slice of a pixel outside the image (3x3 convolution)
+// 64 zero bytes: the K slice of a pixel outside the image (3x3 convolution),
+// the chunks past the end of a ragged row
 __device__ __attribute__((aligned(64))) unsigned char kZeroSlice[64];
 
-// Operands: A and Bt as bytes, `kb` bytes per row (a multiple of 64).
+// Geometry of a ring workgroup: WM x WN x KS waves, each with TM x TN tiles
+// of 32 x 32 and every KS-th K step; each K slice has a ring of NST stages.
+template <int WM, int WN, int TM, int TN, int KS, int NST>
+struct Ring {
+  static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+  static constexpr int WAVES = WM * WN;                  // of one K slice
+  static constexpr int NT = 64 * WAVES * KS;
+  static constexpr int STAGE = (BM + BN) * RK;           // bytes per stage
+  static constexpr int BLOCKS = STAGE / 1024;            // one load of a wave each
+  static constexpr int CPT = BLOCKS / WAVES;             // loads per wave and stage
+  static constexpr int LDS = KS * NST * STAGE;
+  static_assert(BLOCKS % WAVES == 0, "even split of the loads");
+  static_assert((NST - 1) * CPT < 64, "the wait counts fit vmcnt");
+  static_assert(KS == 1 || LDS >= (KS - 1) * WAVES * TM * TN * 4096, "reduction fits in LDS");
+};
+
+// Operands: A and Bt as bytes, `kb` bytes per row (a multiple of 64; of 16 if
+// RAGGED).
 // CONV (BF16 only): the 3x3 convolution as an implicit GEMM on NHWC
 // activations `Bt` ([H, W, Cc]) and OHWI weights `A` ([M, 3, 3, Cc], i.e.
 // rows of kb = 18 Cc bytes): M output channels, N = H W pixels, and K slice
 // s = (tap, 32-channel group) of a pixel row read at the pixel shifted by the
 // tap (zero slice outside the image).
-template <int T, bool CONV = false>
-__global__ __launch_bounds__(64 * RWAVES, 1) void gemm_ring(const unsigned char* __restrict__ A,
-                                                            const unsigned char* __restrict__ Bt,
-                                                            float* __restrict__ C, int M, int N,
-                                                            int kb, int H = 0, int W = 0,
-                                                            int Cc = 0, unsigned* sig = nullptr) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[RNST * RSTAGE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;   // 2 x 4 waves
+template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST>
+__global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
+    const unsigned char* __restrict__ A, const unsigned char* __restrict__ Bt,
+    float* __restrict__ C, int M, int N, int kb, int H, int W, int Cc, unsigned* sig) {
+  using R = Ring<WM, WN, TM, TN, KS, NST>;
+  constexpr int BM = R::BM, BN = R::BN, CPT = R::CPT;
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[R::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wid / R::WAVES, wave = wid % R::WAVES;
+  const int wm = wave / WN, wn = wave % WN;
+  unsigned char* lds = ring + ks * NST * R::STAGE;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   int tm, tn;
   tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int steps = kb / RK;
+  const int steps = RAGGED ? (kb + RK - 1) / RK : kb / RK;
+  const int mine = (steps + KS - 1) / KS;   // steps of a K slice (the last may be missing)
 
-  // A stage is 512 rows (256 of A, then 256 of Bt) of 64 bytes = 2048
-  // chunks; load i of wave w fills the 1 KiB block w * RCPT + i, lane l the
-  // chunk q = 64 (w RCPT + i) + l: row q / 4, stored chunk q % 4, which
-  // holds K chunk (q % 4) ^ ring_swz(row).  Rows past M or N read the
-  // matrix's first row (never stored).
-  const unsigned char* src[RCPT];
-  int py[RCPT], px[RCPT], kcs[RCPT];   // convolution: this lane's pixels
+  // A stage is BM + BN rows (of A, then of Bt) of 64 bytes; load i of wave w
+  // fills the 1 KiB block w * CPT + i, lane l the chunk q = 64 (w CPT + i) + l:
+  // row q / 4, stored chunk q % 4, which holds K chunk (q % 4) ^
+  // ring_swz(row).  Rows past M or N read the matrix's first row (never
+  // stored).
+  const unsigned char* src[CPT];
+  int py[CPT], px[CPT];   // convolution: this lane's pixels
+  int kcs[CPT];
+  unsigned at[CPT];
 #pragma unroll
-  for (int i = 0; i < RCPT; ++i) {
-    const int q = (wave * RCPT + i) * 64 + lane;
+  for (int i = 0; i < CPT; ++i) {
+    at[i] = (wave * CPT + i) * 1024;
+    const int q = (wave * CPT + i) * 64 + lane;
     const int row = q >> 2, kc = (q & 3) ^ ring_swz(row);
     const bool isa = row < BM;
     const int grow = isa ? m0 + row : n0 + (row - BM);
@@ -267,40 +173,43 @@ __global__ __launch_bounds__(64 * RWAVES, 1) void gemm_ring(const unsigned char*
       // pixel rows past the image get y = -2: outside for every tap
       py[i] = ok ? grow / W : -2;
       px[i] = ok ? grow % W : 0;
-      kcs[i] = kc;
     }
+    kcs[i] = kc;
   }
   const int groups = CONV ? Cc / 32 : 1;   // 32-channel groups per tap
+  const unsigned inv = groups > 1 ? 0xffffffffu / groups + 1 : 0;   // x / groups = umulhi(x, inv)
   // Stages past the end re-load the last K slice into their own slot, which
   // is never read again: every step issues the same number of loads, so the
   // wait counts are constants.
   auto issue = [&](int step) {
-    const int slot = step % RNST;
-    const int sc = min(step, steps - 1);
+    const int slot = step % NST;
+    const int sc = min(step * KS + ks, steps - 1);
     const int k0 = sc * RK;
-    const int tap = sc / groups, grp = sc - tap * groups;
+    const int tap = CONV ? (groups > 1 ? (int)__umulhi(sc, inv) : sc) : 0;
+    const int grp = sc - tap * groups;
     const int dy = tap / 3 - 1, dx = tap % 3 - 1;
 #pragma unroll
-    for (int i = 0; i < RCPT; ++i) {
-      const unsigned at = (unsigned)(uintptr_t)(lds + slot * RSTAGE + (wave * RCPT + i) * 1024);
+    for (int i = 0; i < CPT; ++i) {
+      const unsigned to = (unsigned)(uintptr_t)(lds + slot * R::STAGE) + at[i];
       const unsigned char* g = src[i] + k0;
+      if (RAGGED && k0 + 16 * kcs[i] >= kb) g = kZeroSlice + 16 * kcs[i];
       if constexpr (CONV) {
-        if (wave * RCPT + i >= BM / 16) {   // activation rows (wave-uniform)
+        if (at[i] >= BM * RK) {   // activation rows (wave-uniform)
           const int yy = py[i] + dy, xx = px[i] + dx;
           g = (yy >= 0 && yy < H && xx >= 0 && xx < W)
                   ? Bt + (((int64_t)yy * W + xx) * Cc + grp * 32) * 2 + 16 * kcs[i]
                   : kZeroSlice + 16 * kcs[i];
         }
       }
-      ring_load16(g, __builtin_amdgcn_readfirstlane(at));
+      ring_load16(g, __builtin_amdgcn_readfirstlane(to));
     }
   };
 
-  f32x16 acc[4][RNF];
+  f32x16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < RNF; ++j) acc[i][j] = zero16();
+    for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
 
   // fragment of the 32 rows from `row0`: this lane's row, its two K chunks
   // (row0 is a multiple of 32, so row0 + r32 has the swizzle of r32)
@@ -316,18 +225,18 @@ __global__ __launch_bounds__(64 * RWAVES, 1) void gemm_ring(const unsigned char*
     v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
     return v;
   };
-  auto read = [&](int step, i32x8 (&a)[4], i32x8 (&b)[RNF]) {
-    const unsigned char* base = lds + (step % RNST) * RSTAGE;
+  auto read = [&](int step, i32x8 (&a)[TM], i32x8 (&b)[TN]) {
+    const unsigned char* base = lds + (step % NST) * R::STAGE;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = frag(base, wm * 128 + i * 32);
+    for (int i = 0; i < TM; ++i) a[i] = frag(base, (wm * TM + i) * 32);
 #pragma unroll
-    for (int j = 0; j < RNF; ++j) b[j] = frag(base, BM + wn * 64 + j * 32);
+    for (int j = 0; j < TN; ++j) b[j] = frag(base, BM + (wn * TN + j) * 32);
   };
-  auto multiply = [&](const i32x8 (&a)[4], const i32x8 (&b)[RNF]) {
+  auto multiply = [&](const i32x8 (&a)[TM], const i32x8 (&b)[TN]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < RNF; ++j) {
+      for (int j = 0; j < TN; ++j) {
         if constexpr (T == kRingFp8) {
           acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i], b[j], acc[i][j], 0, 0,
                                                                       0, 127, 0, 127);
@@ -343,104 +252,170 @@ __global__ __launch_bounds__(64 * RWAVES, 1) void gemm_ring(const unsigned char*
       }
   };
   // Step s: wait until stage s+1 is in LDS for every wave (this wave's loads
-  // but the two latest stages, then the barrier) and this wave's reads of
+  // but the NST - 2 latest stages, then the barrier) and this wave's reads of
   // stage s are done; refill the slot of stage s (its fragments are in
-  // registers) with stage s+4; read stage s+1 (past the end: stale bytes,
+  // registers) with stage s+NST; read stage s+1 (past the end: stale bytes,
   // never used); multiply stage s.
-  auto step = [&](int s, const i32x8 (&ca)[4], const i32x8 (&cb)[RNF], i32x8 (&na)[4],
-                  i32x8 (&nb)[RNF]) {
-    ring_wait_loads<2 * RCPT>();
+  auto step = [&](int s, const i32x8 (&ca)[TM], const i32x8 (&cb)[TN], i32x8 (&na)[TM],
+                  i32x8 (&nb)[TN]) {
+    ring_wait_loads<(NST - 2) * CPT>();
     __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
     asm volatile("s_barrier" ::: "memory");
-    issue(s + RNST);
+    issue(s + NST);
     read(s + 1, na, nb);
-    multiply(ca, cb);
+    if (KS == 1 || s * KS + ks < steps) multiply(ca, cb);
   };
 
-  for (int s = 0; s < RNST; ++s) issue(s);
-  ring_wait_loads<3 * RCPT>();
+  for (int s = 0; s < NST; ++s) issue(s);
+  ring_wait_loads<(NST - 1) * CPT>();
   asm volatile("s_barrier" ::: "memory");
-  i32x8 a0[4], b0[RNF], a1[4], b1[RNF];
+  i32x8 a0[TM], b0[TN], a1[TM], b1[TN];
   read(0, a0, b0);
-  for (int s = 0; s < steps; s += 2) {
+  for (int s = 0; s < mine; s += 2) {
     step(s, a0, b0, a1, b1);
-    if (s + 1 < steps) step(s + 1, a1, b1, a0, b0);
+    if (s + 1 < mine) step(s + 1, a1, b1, a0, b0);
   }
   // no load may still be writing LDS when the workgroup ends
   ring_wait_loads<0>();
 
+  if (KS > 1) {
+    // K slices 1..KS-1 hand their sums to slice 0 through LDS, added in order
+    constexpr int PER = TM * TN * 16 * 64;   // floats per wave
+    float* red = reinterpret_cast<float*>(ring);
+    __syncthreads();
+    if (ks > 0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < RNF; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + r32;
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            red[((ks - 1) * R::WAVES + wave) * PER + ((i * TN + j) * 16 + r) * 64 + lane] =
+                acc[i][j][r];
+    }
+    __syncthreads();
+    if (ks > 0) {   // handed over: meet slice 0 at the counter's barrier, then leave
+      group_done(sig);
+      return;
+    }
+#pragma unroll
+    for (int s = 1; s < KS; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            acc[i][j][r] += red[((s - 1) * R::WAVES + wave) * PER + ((i * TN + j) * 16 + r) * 64 + lane];
+  }
+
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + (wn * TN + j) * 32 + r32;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 128 + i * 32 + mfma32_row(r, lane);
+        const int row = m0 + (wm * TM + i) * 32 + mfma32_row(r, lane);
         if (row < M && col < N) C[(int64_t)row * N + col] = acc[i][j][r];
       }
     }
   group_done(sig);
 }
 
+struct Launch {
+  const void* func;
+  int bm, bn, nt;
+};
+template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST>
+Launch ring() {
+  using R = Ring<WM, WN, TM, TN, KS, NST>;
+  return {reinterpret_cast<const void*>(&gemm_ring<T, CONV, RAGGED, WM, WN, TM, TN, KS, NST>), R::BM, R::BN,
+          R::NT};
+}
+
+int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
+// The tile by the number of workgroups it gives (us at either side of a line):
+// * 256 x 256 from 144 workgroups on (BF16 2560x4096x1024, 160: 30.5 against
+//   32.2 for 128 x 128; 2304x3072x768, 108: 23.9 against 19.7), unless the
+//   edges would be mostly padding (convolution of 128 channels: 48 against 32);
+// * 128 x 128 where 64 x 64 would take more than two rounds of 256 CUs
+//   (1280x1792x768, 560 / 140 workgroups: 9.2 against 11.4; 1024x2048x1024,
+//   512 / 128: 10.9 against 10.0), with the same exception;
+// * 32 x 32 with eight K slices for few workgroups and a long K (512x512x2048
+//   6.4 against 7.1 for 32 x 64, 512^3 4.6 against 4.1) and, a step costing
+//   more there (pixel addresses), for every convolution that small (C = 256,
+//   32^2: 8.9 against 16.7; C = 32, 32^2: 5.6 against 6.5);
+// * 32 x 64 with two K slices up to 128 workgroups of 64 x 64 (512x1024x512
+//   4.2 against 4.7; 768x1024x512, 192: 5.2 against 4.9);
+// * 64 x 64, with two K slices where one round of CUs holds them all and K is
+//   long (1024^3 6.5 against 7.0; K = 512: equal) or, for a convolution, two
+//   rounds do (C = 160, 100^2: 20.3 against 26.0; C = 64, 256^2, 1024
+//   workgroups: 21.1 against 17.4), four for a longer one (C = 256, 64^2: 17.2
+//   against 19.7; C = 64, 128^2, 18 steps: 9.4 against 8.6).
+template <int T, bool CONV, bool RAGGED>
+Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
+  const int64_t steps = (kb + RK - 1) / RK;
+  const int64_t t256 = tiles(M, N, 256, 256), t128 = tiles(M, N, 128, 128);
+  const int64_t t64 = tiles(M, N, 64, 64), t32 = tiles(M, N, 32, 32);
+  if (t256 >= 144 && 3 * t256 <= t128) return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
+  if (t64 > 512 && 3 * t128 <= t64) return ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4>();
+  if (t32 <= 256 && (CONV || steps >= 64)) return ring<T, CONV, RAGGED, 1, 1, 1, 1, 8, 4>();
+  if constexpr (CONV) {
+    if (t64 <= 256 && steps >= 36) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 4, 4>();
+    if (t64 <= 512) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 2, 4>();
+  } else {
+    if (t64 <= 128) return ring<T, CONV, RAGGED, 1, 2, 1, 1, 2, 4>();
+    if (t64 <= 256 && steps >= 32) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 2, 4>();
+  }
+  return ring<T, CONV, RAGGED, 2, 2, 1, 1, 1, 4>();
+}
+
+OpPlan ring_plan(const Launch& l, int64_t M, int64_t N) {
+  OpPlan p;
+  p.func = l.func;
+  p.grid = dim3((unsigned)(((M + l.bm - 1) / l.bm) * ((N + l.bn - 1) / l.bn)));
+  p.block = dim3(l.nt);
+  return p;
+}
+
+hipError_t ring_launch(const OpPlan& p, const void* A, const void* Bt, float* C, int64_t M,
+                       int64_t N, int64_t kb, int64_t H, int64_t W, int64_t Cc, unsigned* sig,
+                       hipStream_t s) {
+  int m = (int)M, n = (int)N, k = (int)kb, h = (int)H, w = (int)W, c = (int)Cc;
+  void* args[] = {&A, &Bt, &C, &m, &n, &k, &h, &w, &c, &sig};
+  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
+}
+
 }  // namespace
 
 OpPlan gemm_fp8_plan(int64_t M, int64_t N, int64_t K) {
-  OpPlan p;
-  const bool ring = K % RK == 0;
-  p.func = ring ? reinterpret_cast<const void*>(&gemm_ring<kRingFp8>)
-                : reinterpret_cast<const void*>(&gemm_fp8_kernel);
-  p.grid = dim3((unsigned)(((M + BM - 1) / BM) * ((N + BN - 1) / BN)));
-  p.block = dim3(ring ? 64 * RWAVES : 256);
-  return p;
+  return ring_plan(K % RK == 0 ? pick_ring<kRingFp8, false, false>(M, N, K)
+                               : pick_ring<kRingFp8, false, true>(M, N, K), M, N);
 }
 
 hipError_t gemm_fp8_launch(const unsigned char* A, const unsigned char* Bt, float* C, int64_t M,
                            int64_t N, int64_t K, hipStream_t s) {
-  OpPlan p = gemm_fp8_plan(M, N, K);
-  if (K % RK == 0)
-    hipLaunchKernelGGL(gemm_ring<kRingFp8>, p.grid, p.block, 0, s, A, Bt, C, (int)M, (int)N,
-                       (int)K);
-  else
-    hipLaunchKernelGGL(gemm_fp8_kernel, p.grid, p.block, 0, s, A, Bt, C, (int)M, (int)N, (int)K);
-  return hipGetLastError();
+  return ring_launch(gemm_fp8_plan(M, N, K), A, Bt, C, M, N, K, 0, 0, 0, nullptr, s);
 }
 
 OpPlan gemm_bf16_plan(int64_t M, int64_t N, int64_t K) {
-  (void)K;
-  OpPlan p;
-  p.func = reinterpret_cast<const void*>(&gemm_ring<kRingBf16>);
-  p.grid = dim3((unsigned)(((M + BM - 1) / BM) * ((N + BN - 1) / BN)));
-  p.block = dim3(64 * RWAVES);
-  return p;
+  return ring_plan(pick_ring<kRingBf16, false, false>(M, N, 2 * K), M, N);
 }
 
 hipError_t gemm_bf16_launch(const uint16_t* A, const uint16_t* Bt, float* C, int64_t M,
                             int64_t N, int64_t K, hipStream_t s, unsigned* sig) {
-  OpPlan p = gemm_bf16_plan(M, N, K);
-  hipLaunchKernelGGL(gemm_ring<kRingBf16>, p.grid, p.block, 0, s,
-                     reinterpret_cast<const unsigned char*>(A),
-                     reinterpret_cast<const unsigned char*>(Bt), C, (int)M, (int)N, (int)(2 * K),
-                     0, 0, 0, sig);
-  return hipGetLastError();
+  return ring_launch(gemm_bf16_plan(M, N, K), A, Bt, C, M, N, 2 * K, 0, 0, 0, sig, s);
 }
 
 OpPlan conv3x3_bf16_plan(int64_t C, int64_t H, int64_t W) {
-  OpPlan p;
-  p.func = reinterpret_cast<const void*>(&gemm_ring<kRingBf16, true>);
-  p.grid = dim3((unsigned)(((C + BM - 1) / BM) * ((H * W + BN - 1) / BN)));
-  p.block = dim3(64 * RWAVES);
-  return p;
+  return ring_plan(pick_ring<kRingBf16, true, false>(C, H * W, 18 * C), C, H * W);
 }
 
 hipError_t conv3x3_bf16_launch(const uint16_t* X, const uint16_t* Wt, float* Y, int64_t C,
                                int64_t H, int64_t W, hipStream_t s, unsigned* sig) {
-  OpPlan p = conv3x3_bf16_plan(C, H, W);
-  hipLaunchKernelGGL((gemm_ring<kRingBf16, true>), p.grid, p.block, 0, s,
-                     reinterpret_cast<const unsigned char*>(Wt),
-                     reinterpret_cast<const unsigned char*>(X), Y, (int)C, (int)(H * W),
-                     (int)(18 * C), (int)H, (int)W, (int)C, sig);
-  return hipGetLastError();
+  return ring_launch(conv3x3_bf16_plan(C, H, W), Wt, X, Y, C, H * W, 18 * C, H, W, C, sig, s);
 }
 
 }  // namespace ug
