@@ -1,201 +1,322 @@
 // 3x3 convolution (cross-correlation, stride 1, zero pad 1, C_out = C_in),
-// NCHW FP32, as an implicit GEMM on the FP32 matrix cores of gfx950:
+// NCHW FP32, as an implicit GEMM on gfx950:
 //   Y[o, p] = sum_{c, dy, dx} W[o, c, dy, dx] * X[c, py + dy - 1, px + dx - 1]
-// i.e. M = output channels, N = pixels, K = 9 * input channels.
+// i.e. M = output channels, N = pixels, K = 9 * input channels, on the BF16
+// matrix cores with every value split into three bfloat16 pieces as it is
+// staged (split.hpp: error against fp64 below half the FP32 instruction's,
+// matrix cycles 2.67 times fewer).
 //
-// Template <WM, WN, TM, TN, KS, TH, TW>: a workgroup owns BM = WM*TM*32
-// output channels x a TH x TW pixel patch (TH*TW = WN*TN*32 pixels); its four
-// waves form a WM x WN x KS grid.  The reduction runs over chunks of 4 input
-// channels (36 K values): per step the workgroup stages KS chunks, each wave
-// consumes the chunk of its K slice: the chunk's weights (BM x 36, K-major in
-// LDS) and the input patch with its one-pixel halo (4 x (TH+2) x (TW+2)).
-// The im2col operand is never materialised: each MFMA lane reads its
-// (c, dy, dx)-shifted pixel straight from the patch.  The next step is
-// prefetched into registers while the current one is consumed (32-bit
-// offsets from a per-step uniform base).  With KS > 1
-// the K slices are summed through LDS in slice order at the end, so results
-// do not depend on scheduling.
+// A workgroup owns BM = WM*TM*32 output channels x a TH x TW pixel patch
+// (TH*TW = WN*TN*32 pixels) and runs over chunks of 16 input channels (one
+// matrix instruction per tap and product): the chunk's weights and its input
+// patch with a one-pixel halo are split into LDS, channels innermost, and
+// each fragment is 16 bytes (eight channels) of 32 consecutive rows or
+// pixels; the nine taps read the same patch at nine offsets, so the im2col
+// operand is never formed and a pixel is split once for nine taps.  Two
+// buffers: the next chunk is split, from registers loaded a chunk ahead,
+// while this one multiplies.
 //
-// The launcher picks the largest tile that still gives ~two workgroups per CU,
-// or one per CU for a tile without a K split (measured faster than a K split),
-// unless the tuning table (an autotuner's measurements) names a variant
-// (0..4, the order of kShapes) for the shape.
+// Two kernels:
+// * conv3x3_f32_kernel <WM, WN, TM, TN, KS, TH, TW>: all nine taps of a chunk
+//   in LDS, the taps divided over KS groups of wavefronts (three: one tap row
+//   each; nine: one tap) and summed through LDS in a fixed order.  One
+//   workgroup a CU (two of the smallest).
+// * conv3x3_f32_rows <WM, WN, TM, TN, TH, TW>: the weights of one tap row at
+//   a time in LDS, so that two workgroups share a CU and one splits while the
+//   other multiplies.
+//
+// What bounds it: at C = 256, 256^2 the matrix cores are busy about 65 % of
+// the time (MFMA alone about 270 us of 401), the rest is splitting that the
+// other workgroup does not cover.  The small tiles are bound by the latency
+// of a chunk (loads, split, LDS, barrier: 1.3 to 1.8 us) and by the launch.
+// us per launch, FP32 instruction before -> now:
+//   C=256 256^2 670 -> 401, C=236 145^2 288 -> 142, C=128 128^2 52 -> 29,
+//   C=64 256^2 48 -> 33, C=256 64^2 59 -> 35, C=64 128^2 17.4 -> 12.1,
+//   C=128 64^2 20.5 -> 15.9, C=64 84^2 12.9 -> 9.8, C=32 256^2 16.2 -> 12.9,
+//   C=256 32^2 24 -> 21, C=16 64^2 5.7 -> 4.5, C=16 336^2 15.1 -> 12.6.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
+#include "split.hpp"
 
 namespace ug {
 namespace {
 
-constexpr int CC = 4;          // input channels per chunk
-constexpr int KC = CC * 9;     // K values per chunk
+constexpr int CC = 16;         // input channels per chunk: one matrix instruction a tap
+constexpr int kXcds = 8;
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB>
 struct ConvCfg {
+  static constexpr int WAVES = WM * WN, NT = 64 * WAVES * KS;
   static constexpr int BM = WM * TM * 32;
-  static constexpr int PH = TH + 2, PW = TW + 2, PLANE = PH * PW;
-  static constexpr int SW = BM + 33;                  // LDS stride, K-major weights
-  static constexpr int WS = KC * SW;                  // weight floats per chunk
-  static constexpr int XS = CC * PLANE;               // patch floats per chunk
-  static constexpr int W_PER = (KS * BM * KC + 255) / 256;
-  static constexpr int X_PER = (KS * XS + 255) / 256;
-  static constexpr int LDS = KS * (WS + XS);
-  static_assert(WM * WN * KS == 4, "four waves");
-  static_assert(WN * TN * 32 == TH * TW, "pixel tile");
-  static_assert(KS == 1 || LDS >= (KS - 1) * 1024 * TM * TN, "reduction fits in LDS");
+  static constexpr int PH = TH + 2, PW = TW + 2, PX = PH * PW;   // patch with halo
+  static constexpr int PXP = (PX + 63) / 64 * 64;                // whole wavefronts
+  static constexpr int TAPS = 9 / KS;                            // taps of a wave
+  // LDS, bytes: weights [tap][piece][half][row] and patch [piece][half][pixel]
+  // of 16 bytes each (eight channels); 32 bytes between the halves of the
+  // weights keep the staging writes of a row, its channels and its tap rows
+  // in different banks
+  static constexpr int WH = BM * 16 + 32, WT = 6 * WH, XH = PX * 16;
+  static constexpr int STAGE = 9 * WT + 6 * XH;
+  static constexpr int RED = (KS - 1) * WAVES * TM * TN * 4096;   // sums handed over at the end
+  static constexpr int LDS = NB * STAGE > RED ? NB * STAGE : RED;
+  static constexpr int WU = (BM * 12 + NT - 1) / NT;             // weight units per thread
+  static constexpr int XU = (PXP * 4 + NT - 1) / NT;             // patch units per thread
+  static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
 };
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
-__global__ __launch_bounds__(256) void conv3x3_f32_kernel(const float* __restrict__ X,
-                                                           const float* __restrict__ Wt,
-                                                           float* __restrict__ Y, int C, int H,
-                                                           int W, unsigned* sig) {
-  using Cf = ConvCfg<WM, WN, TM, TN, KS, TH, TW>;
-  constexpr int BM = Cf::BM, SW = Cf::SW, PW = Cf::PW, PLANE = Cf::PLANE;
-  __shared__ float lds[Cf::LDS];
-  float* Ws0 = lds;                     // [KS][KC][SW]
-  float* Xs0 = lds + KS * Cf::WS;       // [KS][CC][PLANE]
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int ks = wave / (WM * WN);
-  const int wm = (wave % (WM * WN)) / WN, wn = wave % WN;
-  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
-  const int pt = blockIdx.x % (tiles_x * tiles_y);
-  const int n = blockIdx.x / (tiles_x * tiles_y);
-  const int y0 = (pt / tiles_x) * TH, x0 = (pt % tiles_x) * TW;
-  const int o0 = blockIdx.y * BM;
+// Inputs without a split: taps t0 .. t1 - 1 of a wave's tile (output channels
+// from o, pixels from p of the patch at y0, x0) with the FP32 instruction,
+// from memory.
+template <int TM, int TN, int TW>
+__device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], const float* __restrict__ X,
+                                        const float* __restrict__ Wt, int C, int H, int W, int o0,
+                                        int p0, int y0, int x0, int t0, int t1) {
+  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const size_t plane = (size_t)H * W;
-  const float* Xn = X + (size_t)n * C * plane;
-
-  float rw[Cf::W_PER];
-  float rx[Cf::X_PER];
-
-  // Byte offsets of this thread's staged elements from the step's base
-  // (weights: row o0, input channel c0; input: image n, channel c0), fixed
-  // for the whole K loop; ~0u marks padding (outside the tile, the output
-  // channels or the image).  32-bit offsets from a uniform base keep one
-  // register per element instead of a 64-bit address; the operation's
-  // validation keeps H * W below 2^26, so the byte offsets of the KS * CC
-  // (at most 16) planes of one step fit in 32 bits.
-  uint32_t wo[Cf::W_PER], xo[Cf::X_PER];
-#pragma unroll
-  for (int i = 0; i < Cf::W_PER; ++i) {
-    const int idx = tid + 256 * i;
-    const int s = idx / (BM * KC), rem = idx % (BM * KC);
-    const int o = rem / KC, k = rem % KC;
-    wo[i] = (idx < KS * BM * KC && o0 + o < C)
-                ? (uint32_t)(((int64_t)(o * C + s * CC) * 9 + k) * 4) : ~0u;
-  }
-#pragma unroll
-  for (int i = 0; i < Cf::X_PER; ++i) {
-    const int idx = tid + 256 * i;
-    const int s = idx / Cf::XS, rem = idx % Cf::XS;
-    const int c = rem / PLANE, r = rem % PLANE;
-    const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
-    xo[i] = (idx < KS * Cf::XS && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                ? (uint32_t)((((int64_t)(s * CC + c) * H + yy) * W + xx) * 4) : ~0u;
-  }
-
-  // stage KS chunks starting at input channel c0 (chunk s covers c0 + 4 s ..);
-  // only a step that runs past the last channel checks channels per element
-  auto load = [&](int c0) {
-    const char* wbase = reinterpret_cast<const char*>(Wt + ((size_t)o0 * C + c0) * 9);
-    const char* xbase = reinterpret_cast<const char*>(Xn + (size_t)c0 * plane);
-    if (c0 + KS * CC <= C) {
-#pragma unroll
-      for (int i = 0; i < Cf::W_PER; ++i)
-        rw[i] = wo[i] != ~0u ? *reinterpret_cast<const float*>(wbase + wo[i]) : 0.f;
-#pragma unroll
-      for (int i = 0; i < Cf::X_PER; ++i)
-        rx[i] = xo[i] != ~0u ? *reinterpret_cast<const float*>(xbase + xo[i]) : 0.f;
-    } else {
-#pragma unroll
-      for (int i = 0; i < Cf::W_PER; ++i) {
-        const int idx = tid + 256 * i;
-        const int s = idx / (BM * KC), k = (idx % (BM * KC)) % KC;
-        rw[i] = (wo[i] != ~0u && c0 + s * CC + k / 9 < C)
-                    ? *reinterpret_cast<const float*>(wbase + wo[i]) : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < Cf::X_PER; ++i) {
-        const int idx = tid + 256 * i;
-        const int s = idx / Cf::XS, c = (idx % Cf::XS) / PLANE;
-        rx[i] = (xo[i] != ~0u && c0 + s * CC + c < C)
-                    ? *reinterpret_cast<const float*>(xbase + xo[i]) : 0.f;
-      }
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int i = 0; i < Cf::W_PER; ++i) {
-      const int idx = tid + 256 * i;
-      if (idx < KS * BM * KC) {
-        const int s = idx / (BM * KC), rem = idx % (BM * KC);
-        Ws0[s * Cf::WS + (rem % KC) * SW + rem / KC] = rw[i];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < Cf::X_PER; ++i) {
-      const int idx = tid + 256 * i;
-      if (idx < KS * Cf::XS) Xs0[idx] = rx[i];
-    }
-  };
-
-  f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
-
-  // MFMA step kk of a chunk: lane half h supplies K index k = kk + 18 h, so
-  // the lower half walks input channels 0-1 of the chunk and the upper half
-  // channels 2-3.  Both operands' LDS offsets then differ between the halves
-  // by a per-lane constant, and every step's offset is a compile-time
-  // immediate once the loop is unrolled.
-  const int half = lane >> 5, col = lane & 31;
-  const float* wb = Ws0 + ks * Cf::WS + half * (KC / 2) * SW + wm * TM * 32 + col;
-  const float* xb[TN];
+  for (int t = t0; t < t1; ++t)
+    for (int c = half; c < C + half; c += 2) {
+      float x[TM], y[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int p = (wn * TN + j) * 32 + col;
-    xb[j] = Xs0 + ks * Cf::XS + half * (CC / 2) * PLANE + (p / TW) * PW + (p % TW);
-  }
-
-  const int nsteps = (C + KS * CC - 1) / (KS * CC);
-  load(0);
-  for (int st = 0; st < nsteps; ++st) {
-    __syncthreads();          // previous step fully consumed
-    store();
-    __syncthreads();
-    if (st + 1 < nsteps) load((st + 1) * KS * CC);
+      for (int i = 0; i < TM; ++i) {
+        const int o = min(o0 + i * 32 + col, C - 1);
+        x[i] = c < C ? Wt[((size_t)o * C + c) * 9 + t] : 0.f;
+      }
 #pragma unroll
-    for (int kk = 0; kk < KC / 2; ++kk) {
-      const int r = kk % 9;
-      const int xo = (kk / 9) * PLANE + (r / 3) * PW + (r % 3);
-      float a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = wb[kk * SW + 32 * i];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = xb[j][xo];
+      for (int j = 0; j < TN; ++j) {
+        const int p = p0 + j * 32 + col;
+        const int yy = y0 + p / TW + t / 3 - 1, xx = x0 + p % TW + t % 3 - 1;
+        y[j] = c < C && yy >= 0 && yy < H && xx >= 0 && xx < W
+                   ? X[c * plane + (size_t)yy * W + xx] : 0.f;
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x2(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x2(x[i], y[j], acc[i][j]);
     }
+}
+
+template <int TM, int TN, int TW>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[TM][TN], float* __restrict__ Y,
+                                           int C, int H, int W, int o0, int p0, int y0, int x0) {
+  const int lane = threadIdx.x & 63, col = lane & 31;
+  const size_t plane = (size_t)H * W;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int p = p0 + j * 32 + col;
+    const int yy = y0 + p / TW, xx = x0 + p % TW;
+    if (yy >= H || xx >= W) continue;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int o = o0 + 32 * i + mfma32_row(q, lane);
+        if (o < C) Y[(size_t)o * plane + (size_t)yy * W + xx] = acc[i][j][q];
+      }
+  }
+}
+
+// NB: two buffers, or one where all channels are one chunk (C <= 16).
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB>
+__global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
+    const float* __restrict__ X, const float* __restrict__ Wt, float* __restrict__ Y, int C, int H,
+    int W, unsigned* sig) {
+  using Cf = ConvCfg<WM, WN, TM, TN, KS, TH, TW, NB>;
+  constexpr int BM = Cf::BM, PW = Cf::PW, NT = Cf::NT, TAPS = Cf::TAPS;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[Cf::LDS];
+  __shared__ int redo;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wid / Cf::WAVES, wave = wid % Cf::WAVES;
+  const int wm = wave / WN, wn = wave % WN;
+  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
+  const int xcd = blockIdx.x % kXcds;
+  const int id = xcd * (gridDim.x / kXcds) + min(xcd, (int)(gridDim.x % kXcds)) + blockIdx.x / kXcds;
+  const int pt = id % (tiles_x * tiles_y), n = id / (tiles_x * tiles_y);
+  const int y0 = (pt / tiles_x) * TH, x0 = (pt % tiles_x) * TW;
+  const int o0 = blockIdx.y * BM;
+  const size_t plane = (size_t)H * W;
+  const float* Xn = X + (size_t)n * C * plane;
+  if (tid == 0) redo = 0;
+
+  // Staging units.  Weights: three taps of a row (one ky) of four channels of
+  // an output channel, 4 x 12 bytes 36 bytes apart.  Patch: four channels of
+  // a pixel, consecutive threads on consecutive pixels.  Output channels past
+  // C repeat the last one (never stored).  Buffer loads, relative to the
+  // chunk: what lies past the tensor (channels past C) or has offset 2^31
+  // (pixels outside the image) reads as zero.
+  uint32_t wo[Cf::WU], xo[Cf::XU];
+  int wl[Cf::WU], xl[Cf::XU], xq[Cf::XU];   // LDS places; channel quad of the patch unit
+#pragma unroll
+  for (int i = 0; i < Cf::WU; ++i) {
+    const int u = tid + NT * i, q = u % 4, ky = u / 4 % 3, row = u / 12;
+    wo[i] = (((uint32_t)min(row, C - 1 - o0) * C + 4 * q) * 9 + 3 * ky) * 4;
+    wl[i] = row < BM ? 3 * ky * Cf::WT + (q / 2) * Cf::WH + row * 16 + (q % 2) * 8 : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < Cf::XU; ++i) {
+    const int u = tid + NT * i, r = u % Cf::PXP;
+    const int q = __builtin_amdgcn_readfirstlane(u / Cf::PXP);
+    const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
+    xo[i] = yy >= 0 && yy < H && xx >= 0 && xx < W ? (uint32_t)((size_t)yy * W + xx) * 4 : 1u << 31;
+    xl[i] = r < Cf::PX && q < 4 ? 9 * Cf::WT + (q / 2) * Cf::XH + r * 16 + (q % 2) * 8 : -1;
+    xq[i] = min(q, 3);
   }
 
+  float rw[Cf::WU][4][3], rx[Cf::XU][4];   // the chunk staged next
+  auto load = [&](int c0) {
+    const int64_t left = ((int64_t)C * C - ((int64_t)o0 * C + c0)) * 36;   // bytes to the end
+    const auto ws = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(Wt + ((size_t)o0 * C + c0) * 9), 0,
+        (int)(uint32_t)(left < 0xffffffffll ? left : 0xffffffffll), 0x00027000);
+#pragma unroll
+    for (int i = 0; i < Cf::WU; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const u32x3 v = __builtin_bit_cast(
+            u32x3, __builtin_amdgcn_raw_buffer_load_b96(ws, wo[i] + 36 * j, 0, 0));
+#pragma unroll
+        for (int t = 0; t < 3; ++t) rw[i][j][t] = __uint_as_float(v[t]);
+      }
+#pragma unroll
+    for (int i = 0; i < Cf::XU; ++i) {
+      const int c = c0 + 4 * xq[i];
+      const auto xs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(Xn + (size_t)min(c, C - 1) * plane), 0,
+          (int)((uint32_t)max(0, min(C - c, 4)) * (uint32_t)plane * 4), 0x00027000);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        rx[i][j] = __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(xs, xo[i] + j * (uint32_t)plane * 4, 0, 0));
+    }
+  };
+  uint32_t lost = 0;
+  auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
+    uint2 p[3];
+    split2(a, b, &p[0].x, &p[1].x, &p[2].x, &lost);
+    split2(c, d, &p[0].y, &p[1].y, &p[2].y, &lost);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
+  };
+  int stage = 0;   // byte offset of the buffer staged into
+  auto store_w = [&]() {
+#pragma unroll
+    for (int i = 0; i < Cf::WU; ++i)
+      if (BM * 12 % NT == 0 || wl[i] >= 0)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          put(rw[i][0][t], rw[i][1][t], rw[i][2][t], rw[i][3][t], lds + stage + wl[i] + t * Cf::WT,
+              2 * Cf::WH);
+  };
+  auto store_x = [&]() {
+#pragma unroll
+    for (int i = 0; i < Cf::XU; ++i)
+      if (xl[i] >= 0) put(rx[i][0], rx[i][1], rx[i][2], rx[i][3], lds + stage + xl[i], 2 * Cf::XH);
+  };
+
+  // fragments of tap t of this wave: rows of output channels and of pixels
+  const int half = lane >> 5, col = lane & 31;
+  const int ky0 = KS == 3 ? ks : KS == 9 ? ks / 3 : 0, kx0 = KS == 9 ? ks % 3 : 0;
+  int fa = (3 * ky0 + kx0) * Cf::WT + half * Cf::WH + (wm * TM * 32 + col) * 16;
+  int fb[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int p = (wn * TN + j) * 32 + col;
+    fb[j] = 9 * Cf::WT + half * Cf::XH + ((p / TW + ky0) * PW + p % TW + kx0) * 16;
+  }
+  uint4 a[3][TM], b[3][TN];
+  auto frag = [&](int t, int p) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      a[p][i] = *reinterpret_cast<const uint4*>(lds + fa + t * Cf::WT + p * 2 * Cf::WH + i * 512);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      b[p][j] = *reinterpret_cast<const uint4*>(lds + fb[j] + ((t / 3) * PW + t % 3) * 16 +
+                                                p * 2 * Cf::XH);
+  };
+  f32x16 ah[TM][TN], as[TM][TN];   // sums of hh, of the other five products
+  auto mul = [&](int p, int q, f32x16 (&d)[TM][TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) d[i][j] = mfma_bf16(a[p][i], b[q][j], d[i][j]);
+  };
+
+  const int chunks = NB == 1 ? 1 : (C + CC - 1) / CC;
+  load(0);
+  store_w();
+  store_x();
+  if (chunks > 1) load(CC);
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
+  int flip = Cf::STAGE;
+#pragma clang loop unroll(disable)
+  for (int ch = 0; ch < chunks; ++ch) {
+    stage += flip;
+    const bool more = ch + 1 < chunks;
+    frag(0, 1);
+    frag(0, 0);
+    frag(0, 2);
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) {
+      mul(1, 1, as);
+      mul(1, 0, as);
+      mul(0, 1, as);
+      if (t + 1 < TAPS) frag(t + 1, 1);
+      if (t == 0 && more) store_w();
+      if (t == TAPS - 1 && more) {
+        store_x();
+        if (ch + 2 < chunks) load((ch + 2) * CC);
+      }
+      mul(2, 0, as);
+      mul(0, 2, as);
+      if (t + 1 < TAPS) frag(t + 1, 2);
+      mul(0, 0, ah);
+      if (t + 1 < TAPS) frag(t + 1, 0);
+    }
+    lds_barrier();
+    fa += flip;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[j] += flip;
+    flip = -flip;
+  }
+
+  bool bad = (lost & 0xffffu) != 0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      ah[i][j] += as[i][j];
+      bad = bad || !finite16(ah[i][j]);
+    }
+  if (bad) redo = 1;
+  __syncthreads();   // also: every read of the stages is done
+  if (redo)
+    exact_tile<TM, TN, TW>(ah, Xn, Wt, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0, x0, ks * TAPS,
+                           (ks + 1) * TAPS);
+
   if (KS > 1) {
-    constexpr int PER = TM * TN * 16 * 64;
-    __syncthreads();
+    constexpr int PER = TM * TN * 16 * 64;   // floats per wave
+    float* red0 = reinterpret_cast<float*>(lds);
     if (ks > 0) {
-      float* red = lds + (ks - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
+      float* red = red0 + ((ks - 1) * Cf::WAVES + wave) * PER;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int q = 0; q < 16; ++q) red[((i * TN + j) * 16 + q) * 64 + lane] = acc[i][j][q];
+          for (int q = 0; q < 16; ++q) red[((i * TN + j) * 16 + q) * 64 + lane] = ah[i][j][q];
     }
     __syncthreads();
     if (ks > 0) {   // handed over: meet slice 0 at the counter's barrier, then leave
@@ -204,30 +325,208 @@ __global__ __launch_bounds__(256) void conv3x3_f32_kernel(const float* __restric
     }
 #pragma unroll
     for (int s = 1; s < KS; ++s) {
-      const float* red = lds + (s - 1) * PER * (WM * WN) + (wave % (WM * WN)) * PER;
+      const float* red = red0 + ((s - 1) * Cf::WAVES + wave) * PER;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int q = 0; q < 16; ++q) acc[i][j][q] += red[((i * TN + j) * 16 + q) * 64 + lane];
+          for (int q = 0; q < 16; ++q) ah[i][j][q] += red[((i * TN + j) * 16 + q) * 64 + lane];
     }
   }
 
-  float* Yn = Y + (size_t)n * C * plane;
+  store_tile<TM, TN, TW>(ah, Y + (size_t)n * C * plane, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0,
+                         x0);
+  group_done(sig);
+}
+
+// The large tiles: the weights of one tap row (ky) at a time in LDS, so that
+// two workgroups share a CU and one splits while the other multiplies.
+template <int WM, int WN, int TM, int TN, int TH, int TW>
+struct RowsCfg {
+  static constexpr int NT = 64 * WM * WN, BM = WM * TM * 32;
+  static constexpr int PH = TH + 2, PW = TW + 2, PX = PH * PW;
+  static constexpr int PXP = (PX + 31) / 32 * 32;
+  static constexpr int WH = BM * 16 + 128, WT = 6 * WH, XH = PX * 16;
+  static constexpr int WS = 3 * WT, XS = 6 * XH;          // bytes per buffer
+  static constexpr int LDS = 2 * (WS + XS);
+  static constexpr int XU = (PXP * 4 + NT - 1) / NT;
+  static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
+  static_assert(BM * 4 <= NT, "at most one weight unit a thread");
+};
+
+template <int WM, int WN, int TM, int TN, int TH, int TW>
+__global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
+    const float* __restrict__ X, const float* __restrict__ Wt, float* __restrict__ Y, int C, int H,
+    int W, unsigned* sig) {
+  using Cf = RowsCfg<WM, WN, TM, TN, TH, TW>;
+  constexpr int BM = Cf::BM, PW = Cf::PW, NT = Cf::NT;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[Cf::LDS];
+  __shared__ int redo;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
+  const int xcd = blockIdx.x % kXcds;
+  const int id = xcd * (gridDim.x / kXcds) + min(xcd, (int)(gridDim.x % kXcds)) + blockIdx.x / kXcds;
+  const int pt = id % (tiles_x * tiles_y), n = id / (tiles_x * tiles_y);
+  const int y0 = (pt / tiles_x) * TH, x0 = (pt % tiles_x) * TW;
+  const int o0 = blockIdx.y * BM;
+  const size_t plane = (size_t)H * W;
+  const float* Xn = X + (size_t)n * C * plane;
+  if (tid == 0) redo = 0;
+
+  const bool has_w = BM * 4 == NT || wave < BM * 4 / 64;
+  const int row = tid / 4, q = tid % 4;
+  const uint32_t wo = ((uint32_t)min(row, C - 1 - o0) * C + 4 * q) * 36;
+  int wl = (q / 2) * Cf::WH + row * 16 + (q % 2) * 8;
+  uint32_t xo[Cf::XU];
+  int xl[Cf::XU], xc[Cf::XU];
+#pragma unroll
+  for (int i = 0; i < Cf::XU; ++i) {
+    const int u = tid + NT * i, sub = u % 2, e = u / 2;
+    const int r = e % Cf::PXP, h = __builtin_amdgcn_readfirstlane(e / Cf::PXP);
+    const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
+    xo[i] = yy >= 0 && yy < H && xx >= 0 && xx < W
+                ? ((uint32_t)(4 * sub) * (uint32_t)plane + (uint32_t)((size_t)yy * W + xx)) * 4
+                : 1u << 31;
+    xl[i] = r < Cf::PX && h < 2 ? 2 * Cf::WS + h * Cf::XH + r * 16 + sub * 8 : -1;
+    xc[i] = 8 * min(h, 1);
+  }
+  float rw[36], rx[Cf::XU][4];
+  auto load_w = [&](int c0) {
+    const int64_t left = ((int64_t)C * C - ((int64_t)o0 * C + c0)) * 36;   // bytes to the end
+    const auto ws = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(Wt + ((size_t)o0 * C + c0) * 9), 0,
+        (int)(uint32_t)(left < 0xffffffffll ? left : 0xffffffffll), 0x00027000);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+      const u32x4 v = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(ws, wo + 16 * j, 0, 0));
+#pragma unroll
+      for (int t = 0; t < 4; ++t) rw[4 * j + t] = __uint_as_float(v[t]);
+    }
+  };
+  auto load_x = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < Cf::XU; ++i) {
+      const int c = c0 + xc[i];
+      const auto xs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(Xn + (size_t)min(c, C - 1) * plane), 0,
+          (int)((uint32_t)max(0, min(C - c, 8)) * (uint32_t)plane * 4), 0x00027000);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        rx[i][j] = __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(xs, xo[i] + j * (uint32_t)plane * 4, 0, 0));
+    }
+  };
+  uint32_t lost = 0;
+  auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
+    uint2 p[3];
+    split2(a, b, &p[0].x, &p[1].x, &p[2].x, &lost);
+    split2(c, d, &p[0].y, &p[1].y, &p[2].y, &lost);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
+  };
+  int wst = 0, xst = 0;   // offsets of the buffers staged into
+  auto store_w = [&](int t) {
+    if (has_w) put(rw[t], rw[9 + t], rw[18 + t], rw[27 + t], lds + wst + wl + t % 3 * Cf::WT, 2 * Cf::WH);
+  };
+  auto store_x = [&]() {
+#pragma unroll
+    for (int i = 0; i < Cf::XU; ++i)
+      if (xl[i] >= 0) put(rx[i][0], rx[i][1], rx[i][2], rx[i][3], lds + xst + xl[i], 2 * Cf::XH);
+  };
+
+  const int half = lane >> 5, col = lane & 31;
+  int fa = half * Cf::WH + (wm * TM * 32 + col) * 16;
+  int fb[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int p = (wn * TN + j) * 32 + col;
-    const int yy = y0 + p / TW, xx = x0 + p % TW;
-    if (yy >= H || xx >= W) continue;
+    fb[j] = 2 * Cf::WS + half * Cf::XH + ((p / TW) * PW + p % TW) * 16;
+  }
+  uint4 a[3][TM], b[3][TN];
+  auto frag = [&](int ky, int kx, int p) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      a[p][i] = *reinterpret_cast<const uint4*>(lds + fa + kx * Cf::WT + p * 2 * Cf::WH + i * 512);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      b[p][j] = *reinterpret_cast<const uint4*>(lds + fb[j] + (ky * PW + kx) * 16 + p * 2 * Cf::XH);
+  };
+  f32x16 ah[TM][TN], as[TM][TN];   // sums of hh, of the other five products
+  auto mul = [&](int p, int q, f32x16 (&d)[TM][TN]) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int o = o0 + wm * TM * 32 + 32 * i + mfma32_row(q, lane);
-        if (o < C) Yn[(size_t)o * plane + (size_t)yy * W + xx] = acc[i][j][q];
+      for (int j = 0; j < TN; ++j) d[i][j] = mfma_bf16(a[p][i], b[q][j], d[i][j]);
+  };
+
+  const int chunks = (C + CC - 1) / CC;
+  load_w(0);
+  load_x(0);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) store_w(t);
+  store_x();
+  if (chunks > 1) load_x(CC);
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
+  int wflip = Cf::WS, xflip = Cf::XS;
+#pragma clang loop unroll(disable)
+  for (int ch = 0; ch < chunks; ++ch) {
+    const bool more = ch + 1 < chunks;
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky) {
+      wst += wflip;
+      if (ky == 2) xst += xflip;
+      frag(ky, 0, 1);
+      frag(ky, 0, 0);
+      frag(ky, 0, 2);
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) {
+        mul(1, 1, as);
+        mul(1, 0, as);
+        mul(0, 1, as);
+        if (kx < 2) frag(ky, kx + 1, 1);
+        if (ky < 2 || more) store_w((3 * ky + 3) % 9 + kx);   // the next tap row
+        if (ky == 2 && kx == 1 && more) {
+          store_x();
+          if (ch + 2 < chunks) load_x((ch + 2) * CC);
+        }
+        if (ky == 1 && kx == 2 && more) load_w((ch + 1) * CC);
+        mul(2, 0, as);
+        mul(0, 2, as);
+        if (kx < 2) frag(ky, kx + 1, 2);
+        mul(0, 0, ah);
+        if (kx < 2) frag(ky, kx + 1, 0);
       }
+      lds_barrier();
+      fa += wflip;
+      wflip = -wflip;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[j] += xflip;
+    xflip = -xflip;
   }
+
+  bool bad = (lost & 0xffffu) != 0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      ah[i][j] += as[i][j];
+      bad = bad || !finite16(ah[i][j]);
+    }
+  if (bad) redo = 1;
+  __syncthreads();
+  if (redo) exact_tile<TM, TN, TW>(ah, Xn, Wt, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0, x0, 0, 9);
+  store_tile<TM, TN, TW>(ah, Y + (size_t)n * C * plane, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0,
+                         x0);
   group_done(sig);
 }
 
@@ -236,22 +535,42 @@ struct Shape {
   int bm, th, tw;
 };
 constexpr Shape kShapes[] = {
-    {128, 8, 16},   // <2,2,2,2,1>
-    {64, 8, 16},    // <1,4,2,1,1>
-    {32, 8, 16},    // <1,4,1,1,1>
-    {64, 2, 16},    // <1,1,2,1,4>
-    {32, 2, 16},    // <1,1,1,1,4>
+    {64, 8, 16},    // rows <1,4,2,1> or <1,4,2,1,3>
+    {32, 16, 16},   // <1,4,1,2,3>
+    {32, 8, 16},    // <1,4,1,1,3>
+    {32, 4, 16},    // <1,2,1,1,3>
+    {32, 2, 16},    // <1,1,1,1,9>
 };
 
 int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
   return ((H + s.th - 1) / s.th) * ((W + s.tw - 1) / s.tw) * N * ((C + s.bm - 1) / s.bm);
 }
 
-// First (largest) tile with ~two workgroups per CU, or one per CU if it has no
-// K split; else the one with the most workgroups.
-int pick(int64_t N, int64_t C, int64_t H, int64_t W);
+// The smallest tile that one round of the 256 CUs holds: a chunk takes a
+// workgroup 1.3 us (32 x 2x16) to 2.3 us (64 x 8x16), so that a second round
+// costs more than a larger tile (C=64 128^2: 256 workgroups of 32 x 8x16 take
+// 12.1 us, 512 of 32 x 4x16 17.5, 128 of 64 x 8x16 15.4; C=128 64^2: 15.9 at
+// 32 x 4x16, 18.8 and 23.6 either side).  One chunk (C <= 16) takes one
+// buffer, four workgroups a CU and no time to speak of: the ends of the
+// kernel are what is left (128^2: 4.7 us at 32 x 4x16, 5.1 at 32 x 8x16; 336^2:
+// 14.3 and 12.6).
+int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
+  if (C <= CC) return wgs(kShapes[3], N, C, H, W) <= 256 ? 3 : 2;
+  const int largest = C <= 32 ? 1 : 0;
+  for (int i = 4; i > largest; --i)
+    if (!(i == 1 && C > 32) && wgs(kShapes[i], N, C, H, W) <= 256) return i;
+  return largest;
+}
 
-// The variant asked for, else the tuning table's, else the rule below.
+// 64 x 8x16: a round of two tap-row workgroups a CU takes 1.9 times as long as
+// one of a nine-tap workgroup a CU (C=256 256^2, 2048 workgroups: 401 against
+// 419 us; C=236 145^2, 760: 152 against 142).
+bool by_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
+  const int64_t n = wgs(kShapes[0], N, C, H, W);
+  return 19 * ((n + 511) / 512) < 10 * ((n + 255) / 256);
+}
+
+// The variant asked for, else the tuning table's, else the rule above.
 int choose(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
   if (variant < 0) {
     const int64_t key[4] = {N, C, H, W};
@@ -260,60 +579,50 @@ int choose(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
   return variant >= 0 && variant < 5 ? variant : pick(N, C, H, W);
 }
 
-int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
-  constexpr int64_t kWant = 480, kOnePerCu = 256;
-  int best = 4;
-  int64_t most = 0;
-  for (int i = 0; i < 5; ++i) {
-    if (kShapes[i].bm > 32 && C <= kShapes[i].bm / 2) continue;   // mostly padding
-    const int64_t n = wgs(kShapes[i], N, C, H, W);
-    if (n >= kWant || (i < 3 && n >= kOnePerCu)) return i;       // tiles 0-2: no K split
-    if (n > most) {
-      most = n;
-      best = i;
-    }
-  }
-  return best;
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
+OpPlan plan(int64_t N, int64_t C, int64_t H, int64_t W) {
+  constexpr int BM = WM * TM * 32;
+  OpPlan p;
+  p.func = C <= CC && BM == 32
+               ? reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, BM == 32 ? 1 : 2>)
+               : reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, 2>);
+  p.grid = dim3((unsigned)(((H + TH - 1) / TH) * ((W + TW - 1) / TW) * N),
+                (unsigned)((C + BM - 1) / BM));
+  p.block = dim3(64 * WM * WN * KS);
+  return p;
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
-void launch(dim3 grid, hipStream_t s, const float* X, const float* Wt, float* Y, int C, int H,
-            int W, unsigned* sig) {
-  hipLaunchKernelGGL((conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW>), grid, dim3(256), 0, s, X,
-                     Wt, Y, C, H, W, sig);
+template <int WM, int WN, int TM, int TN, int TH, int TW>
+OpPlan plan_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
+  constexpr int BM = WM * TM * 32;
+  OpPlan p;
+  p.func = reinterpret_cast<const void*>(&conv3x3_f32_rows<WM, WN, TM, TN, TH, TW>);
+  p.grid = dim3((unsigned)(((H + TH - 1) / TH) * ((W + TW - 1) / TW) * N),
+                (unsigned)((C + BM - 1) / BM));
+  p.block = dim3(64 * WM * WN);
+  return p;
 }
 
 }  // namespace
 
 OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
-  OpPlan p;
-  const int i = choose(N, C, H, W, variant);
-  const Shape& s = kShapes[i];
-  const void* f[] = {reinterpret_cast<const void*>(&conv3x3_f32_kernel<2, 2, 2, 2, 1, 8, 16>),
-                     reinterpret_cast<const void*>(&conv3x3_f32_kernel<1, 4, 2, 1, 1, 8, 16>),
-                     reinterpret_cast<const void*>(&conv3x3_f32_kernel<1, 4, 1, 1, 1, 8, 16>),
-                     reinterpret_cast<const void*>(&conv3x3_f32_kernel<1, 1, 2, 1, 4, 2, 16>),
-                     reinterpret_cast<const void*>(&conv3x3_f32_kernel<1, 1, 1, 1, 4, 2, 16>)};
-  p.func = f[i];
-  p.grid = dim3((unsigned)(((H + s.th - 1) / s.th) * ((W + s.tw - 1) / s.tw) * N),
-                (unsigned)((C + s.bm - 1) / s.bm));
-  p.block = dim3(256);
-  return p;
+  switch (choose(N, C, H, W, variant)) {
+    case 0:
+      return by_rows(N, C, H, W) ? plan_rows<1, 4, 2, 1, 8, 16>(N, C, H, W)
+                                 : plan<1, 4, 2, 1, 3, 8, 16>(N, C, H, W);
+    case 1: return plan<1, 4, 1, 2, 3, 16, 16>(N, C, H, W);
+    case 2: return plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
+    case 3: return plan<1, 2, 1, 1, 3, 4, 16>(N, C, H, W);
+    default: return plan<1, 1, 1, 1, 9, 2, 16>(N, C, H, W);
+  }
 }
 
 hipError_t conv3x3_f32_launch(const float* X, const float* Wt, float* Y, int64_t N, int64_t C,
                               int64_t H, int64_t W, hipStream_t s, unsigned* sig, int variant) {
-  const int v = choose(N, C, H, W, variant);
-  OpPlan p = conv3x3_f32_plan(N, C, H, W, v);
-  const int c = (int)C, h = (int)H, w = (int)W;
-  switch (v) {
-    case 0: launch<2, 2, 2, 2, 1, 8, 16>(p.grid, s, X, Wt, Y, c, h, w, sig); break;
-    case 1: launch<1, 4, 2, 1, 1, 8, 16>(p.grid, s, X, Wt, Y, c, h, w, sig); break;
-    case 2: launch<1, 4, 1, 1, 1, 8, 16>(p.grid, s, X, Wt, Y, c, h, w, sig); break;
-    case 3: launch<1, 1, 2, 1, 4, 2, 16>(p.grid, s, X, Wt, Y, c, h, w, sig); break;
-    default: launch<1, 1, 1, 1, 4, 2, 16>(p.grid, s, X, Wt, Y, c, h, w, sig); break;
-  }
-  return hipGetLastError();
+  const OpPlan p = conv3x3_f32_plan(N, C, H, W, variant);
+  int c = (int)C, h = (int)H, w = (int)W;
+  void* args[] = {&X, &Wt, &Y, &c, &h, &w, &sig};
+  return hipLaunchKernel(p.func, p.grid, p.block, args, p.lds, s);
 }
 
 }  // namespace ug

@@ -89,12 +89,6 @@ __device__ __forceinline__ int swz(int row) {
   return BK == 32 ? (row >> 2) & 3 : (row >> 3) & 1;
 }
 
-// Meets the workgroup once this wavefront's LDS accesses are done.  Unlike
-// __syncthreads it leaves global loads in flight.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* p) {   // raw, unbounded
@@ -119,7 +113,7 @@ __device__ __forceinline__ void interleave() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int BK, int U, bool WIDE>
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) void gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int M, int N,
     int K, unsigned* sig) {
@@ -174,8 +168,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
   const float* a0 = A + (size_t)m0 * K;
   const float* b0 = B + n0;
 
-  float ra[G::AU][U], rb[G::BU][U];   // the step staged next
-  auto load_a = [&](int k0) {
+  // PF sets of registers: each is filled PF steps before it is staged
+  float ra[PF][G::AU][U], rb[PF][G::BU][U];
+  auto load_a = [&](int k0, float (&ra)[G::AU][U]) {
     const rsrc_t rs = make_rsrc(a0 + k0);
 #pragma unroll
     for (int i = 0; i < G::AU; ++i)
@@ -192,7 +187,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
         }
       }
   };
-  auto load_b = [&](int k0) {
+  auto load_b = [&](int k0, float (&rb)[G::BU][U]) {
     const rsrc_t rs = make_rsrc(b0 + (size_t)k0 * N);
 #pragma unroll
     for (int i = 0; i < G::BU; ++i)
@@ -202,7 +197,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
                         : buffer_load4(rs, pb[i], j * N * 4);
   };
   // the first step: its K values from `kn` on are zero
-  auto load_first = [&](int kn) {
+  auto load_first = [&](int kn, float (&ra)[G::AU][U], float (&rb)[G::BU][U]) {
 #pragma unroll
     for (int i = 0; i < G::AU; ++i)
 #pragma unroll
@@ -234,11 +229,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
         *reinterpret_cast<uint2*>(at + j * G::PIECE) = make_uint2(p[j][0], p[j][1]);
     }
   };
-  auto store_a = [&]() {
+  auto store_a = [&](const float (&ra)[G::AU][U]) {
 #pragma unroll
     for (int i = 0; i < G::AU; ++i) put(ra[i], lds + oa[i]);
   };
-  auto store_b = [&]() {
+  auto store_b = [&](const float (&rb)[G::BU][U]) {
 #pragma unroll
     for (int i = 0; i < G::BU; ++i) put(rb[i], lds + ob[i]);
   };
@@ -298,16 +293,21 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
   const int nk = (K - 1) / BKT + 1;
   const int first = K - (nk - 1) * BKT;
   if (TM * TN == 1 && first == BKT) {   // (the big tile has no registers for a branch)
-    load_a(0);
-    load_b(0);
+    load_a(0, ra[0]);
+    load_b(0, rb[0]);
   } else {
-    load_first(first);
+    load_first(first, ra[0], rb[0]);
   }
-  store_a();
-  store_b();
+  store_a(ra[0]);
+  store_b(rb[0]);
+  // K value where step i starts; past the end the last one again, never used
+  auto at = [&](int i) { return first + (min(i, nk - 1) - 1) * BKT; };
   if (nk > 1) {
-    load_a(first);
-    load_b(first);
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      load_a(at(i + 1), ra[i]);
+      load_b(at(i + 1), rb[i]);
+    }
   }
   lds_barrier();
   frag(1);
@@ -318,17 +318,16 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
 #pragma unroll
     for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
   __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
-#pragma clang loop unroll(disable)
-  for (int kt = 0; kt + 1 < nk; ++kt) {
+  auto step = [&](int kt, float (&ra)[G::AU][U], float (&rb)[G::BU][U]) {
     flip();
-    const int k2 = first + min(kt + 1, nk - 2) * BKT;   // the last one again, unused
+    const int k2 = at(kt + 1 + PF);
     mul(1, 1, as);
-    store_a();
-    load_a(k2);
+    store_a(ra);
+    load_a(k2, ra);
     interleave<KH * TM * TN, (6 * U * G::AU + KH * TM * TN - 1) / (KH * TM * TN)>();
     mul(1, 0, as);
-    store_b();
-    load_b(k2);
+    store_b(rb);
+    load_b(k2, rb);
     interleave<KH * TM * TN, (6 * U * G::BU + KH * TM * TN - 1) / (KH * TM * TN)>();
     mul(0, 1, as);
     __builtin_amdgcn_sched_barrier(0);
@@ -343,6 +342,14 @@ __global__ __launch_bounds__(64 * WM * WN * KS, (WM * WN * KS >= 8 ? 4 : 2)) voi
     mul(0, 0, ah);
     frag(0);
     __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma clang loop unroll(disable)
+  for (int kt = 0; kt + 1 < nk;) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      step(kt, ra[i], rb[i]);
+      if (++kt + 1 >= nk) break;
+    }
   }
   mul(1, 1, as);
   mul(1, 0, as);
@@ -439,13 +446,13 @@ int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm)
 // Two 64 x 64 workgroups share a CU, and up to 512 of them finish together;
 // past that 128 x 128 is faster (1280x2048x1024, 640 / 160 tiles: 42 against
 // 44 us; 1024x2048x1024, 512 / 128: 41 against 32), unless the matrix's edge
-// would leave a quarter of its work as padding.  64 x 64 needs about 160
-// tiles to beat 32 x 32 (768x1024x512, 192 / 768 tiles: 10.6 against 12.2 us;
-// 512x1024x512, 128 / 512: 10.4 against 9.6).
+// would leave a quarter of its work as padding.  64 x 64 needs about 128
+// tiles to beat 32 x 32 (768x768x512, 144 / 576 tiles: 11.2 against 13.9 us;
+// 512x768x512, 96 / 384: 10.3 against 9.5).
 Shape pick(int64_t M, int64_t N) {
   const int64_t t64 = tiles(M, N, 64, 64);
   if (t64 > 512 && 3 * tiles(M, N, 128, 128) <= t64) return kBig;
-  return t64 >= 160 ? kMid : kSmall;
+  return t64 >= 128 ? kMid : kSmall;
 }
 
 // The variant asked for, else the tuning table's, else the rule above.
@@ -457,11 +464,11 @@ Shape choose(int64_t M, int64_t N, int64_t K, int variant) {
   return variant >= 0 && variant < 3 ? static_cast<Shape>(variant) : pick(M, N);
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int BK, int U>
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF>
 OpPlan plan(int64_t M, int64_t N, bool wide) {
   OpPlan p;
-  p.func = wide ? reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, true>)
-                : reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, false>);
+  p.func = wide ? reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, true>)
+                : reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, false>);
   p.grid = dim3((unsigned)tiles(M, N, WM * TM * 32, WN * TN * 32));
   p.block = dim3(64 * WM * WN * KS);
   return p;
@@ -474,17 +481,17 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
   const bool wide = K >= (1 << 22) || N >= (1 << 22);
   switch (choose(M, N, K, variant)) {
     case kBig:
-      return plan<2, 4, 2, 1, 1, 16, 4>(M, N, wide);
+      return plan<2, 4, 2, 1, 1, 16, 4, 1>(M, N, wide);
     case kMid:
       // one tile a CU at most: eight more waves pay once K is long
       // (4096x256x4096 71 -> 62 us, 1024^3 18.8 -> 18.3, K = 256 7.2 -> 7.6)
-      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4>(M, N, wide)
-                                                     : plan<2, 2, 1, 1, 2, 16, 4>(M, N, wide);
+      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4, 4>(M, N, wide)
+                                                     : plan<2, 2, 1, 1, 2, 16, 4, 4>(M, N, wide);
     default:
       // the same for 32 x 32 (256x256x2048 19.7 -> 16.3 us, 512^3 7.6 -> 7.1;
       // with 512 tiles 9.6 -> 12.6)
-      return K >= 512 && tiles(M, N, 32, 32) <= 256 ? plan<1, 1, 1, 1, 8, 16, 4>(M, N, wide)
-                                                    : plan<1, 1, 1, 1, 4, 16, 8>(M, N, wide);
+      return K >= 512 && tiles(M, N, 32, 32) <= 256 ? plan<1, 1, 1, 1, 8, 16, 4, 3>(M, N, wide)
+                                                    : plan<1, 1, 1, 1, 4, 16, 8, 3>(M, N, wide);
   }
 }
 

@@ -76,4 +76,10 @@ __device__ __forceinline__ bool finite16(f32x16 v) {
   return ok;
 }
 
+// Meets the workgroup once this wavefront's LDS accesses are done.  Unlike
+// __syncthreads it leaves global loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 }  // namespace ug

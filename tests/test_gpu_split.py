@@ -75,3 +75,51 @@ def test_gemm_tiny_values(lo):
     C = G.run_gemm(A, B)
     ref, scale = OK.gemm_f64(A, B), OK.gemm_abs_f64(A, B)
     assert np.all(np.abs(C - ref) <= K * 2.0 ** -23 * scale)
+
+
+# ------------------------------------------------------------- convolution
+# 64 x 8x16 by tap rows and at once, 32 x 16x16, 32 x 8x16, 32 x 4x16 and
+# 32 x 2x16 with two buffers; one chunk of channels at 32 x 4x16 and 32 x 8x16
+CONV = [(1, 64, 250, 250), (1, 130, 70, 90), (1, 30, 250, 260), (1, 40, 100, 140), (1, 40, 60, 80),
+        (1, 100, 33, 47), (3, 17, 5, 16), (2, 16, 40, 50), (1, 3, 13, 21), (1, 7, 200, 199)]
+
+
+@pytest.mark.parametrize("n,c,h,w", CONV)
+def test_conv_error(n, c, h, w):
+    r = np.random.default_rng(n + 3 * c + 5 * h + 7 * w)
+    X = r.standard_normal((n, c, h, w)).astype(np.float32)
+    W = r.standard_normal((c, c, 3, 3)).astype(np.float32)
+    Y = G.run_conv(X, W)
+    ref, scale = OK.conv3x3_f64(X, W), OK.conv3x3_abs_f64(X, W)
+    # every chunk of 16 channels is one matrix instruction a tap
+    K = 9 * ((c + 15) // 16) * 16
+    assert np.all(np.abs(Y - ref) <= bound(K) * scale), np.max(np.abs(Y - ref) / scale)
+
+
+def conv_abs(X, W):
+    """Sum of |products| of a zero-padded convolution, zero where one is not finite."""
+    return OK.conv3x3_abs_f64(np.nan_to_num(X, posinf=0, neginf=0),
+                              np.nan_to_num(W, posinf=0, neginf=0))
+
+
+@pytest.mark.parametrize("n,c,h,w", [CONV[0], CONV[1], CONV[4], CONV[7]])
+def test_conv_values_without_a_split(n, c, h, w):
+    r = np.random.default_rng(c)
+    X = r.uniform(0.5, 1, (n, c, h, w)).astype(np.float32)
+    W = r.uniform(-1, 1, (c, c, 3, 3)).astype(np.float32)
+    X[0, 2, 3, 4], X[0, 5, h - 3, w - 2], X[0, c - 1, 20, 9] = np.inf, -np.inf, np.nan
+    with np.errstate(invalid="ignore"):
+        ref = OK.conv3x3_f64(X, W)
+    Y = G.run_conv(X, W)
+    ok = same_kind(Y, ref)
+    assert np.all(np.abs(Y - ref)[ok] <= 9 * c * 2.0 ** -23 * conv_abs(X, W)[ok])
+
+
+@pytest.mark.parametrize("n,c,h,w", [CONV[4], CONV[7]])
+def test_conv_tiny_values(n, c, h, w):
+    r = np.random.default_rng(c + 1)
+    X = (r.uniform(1, 2, (n, c, h, w)) * 2.0 ** -125).astype(np.float32)
+    W = (r.uniform(1, 2, (c, c, 3, 3)) * 2.0 ** 90).astype(np.float32)
+    Y = G.run_conv(X, W)
+    ref, scale = OK.conv3x3_f64(X, W), OK.conv3x3_abs_f64(X, W)
+    assert np.all(np.abs(Y - ref) <= 9 * c * 2.0 ** -23 * scale)
