@@ -101,70 +101,95 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// One wave per row (4 rows per workgroup): rows of up to a few thousand.
-__global__ __launch_bounds__(256) void rowsum_wave(const float* __restrict__ Z,
-                                                   float* __restrict__ r, int64_t R, int64_t C) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= R) return;
-  const float* z = Z + row * C;
-  float s = 0.f;
-  if ((C & 3) == 0 && ((reinterpret_cast<uintptr_t>(z) & 15) == 0)) {
-    const float4* z4 = reinterpret_cast<const float4*>(z);
-    for (int64_t j = lane; j < C / 4; j += 64) {
-      const float4 v = load_stream(z4 + j);
-      s += (v.x + v.y) + (v.z + v.w);
-    }
-  } else {
-    for (int64_t j = lane; j < C; j += 64) s += z[j];
-  }
-  s = wave_sum(s);
-  if (lane == 0) r[row] = s;
+// A row of L floats at any 4-byte alignment: `head` floats up to the first
+// 16-byte boundary (at most 3), `n4` float4, `tail` floats.
+struct RowParts {
+  int head, tail;
+  int64_t n4;
+};
+__device__ __forceinline__ RowParts row_parts(const float* z, int64_t L) {
+  int64_t h = (int64_t)(((16 - (reinterpret_cast<uintptr_t>(z) & 15)) & 15) >> 2);
+  h = h < L ? h : L;
+  const int64_t n4 = (L - h) >> 2;
+  return {(int)h, (int)(L - h - 4 * n4), n4};
 }
 
-// One workgroup (4 waves) per row: long rows.
-__global__ __launch_bounds__(256) void rowsum_block(const float* __restrict__ Z,
-                                                    float* __restrict__ r, int64_t R, int64_t C) {
-  __shared__ float part[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = blockIdx.x;
-  const float* z = Z + row * C;
+// WAVES waves per row, U float4 per lane in flight (a chain of dependent
+// rounds of loads is what a row costs: 1280 rows of 2048 took 5.6 us with one
+// load in flight a lane, 3.4 with eight; 32 rows of 65536 9.9 us with one
+// workgroup of four waves, 5.0 with sixteen waves).  Rows of any alignment are
+// read 16 bytes at a time (235 rows of 21025: 10.3 us element by element, 4.6
+// so).  Partial sums are combined in a fixed order.
+template <int WAVES, int U>
+__global__ __launch_bounds__(WAVES <= 4 ? 256 : 64 * WAVES) void rowsum_rows(
+    const float* __restrict__ Z, float* __restrict__ r, int64_t R, int64_t C) {
+  constexpr int T = WAVES * 64;                    // lanes per row
+  constexpr int ROWS = WAVES <= 4 ? 256 / T : 1;   // rows per workgroup
+  __shared__ float part[ROWS * WAVES];
+  const int t = threadIdx.x % T, lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * ROWS + threadIdx.x / T;
   float s = 0.f;
-  if ((C & 3) == 0 && ((reinterpret_cast<uintptr_t>(z) & 15) == 0)) {
-    // four independent loads in flight per lane, summed in a fixed order
-    const float4* z4 = reinterpret_cast<const float4*>(z);
-    const int64_t c4 = C / 4;
-    float a[4] = {0.f, 0.f, 0.f, 0.f};
-    int64_t j = threadIdx.x;
-    for (; j + 768 < c4; j += 1024) {
-      float4 v[4];
+  if (row < R) {
+    const float* z = Z + row * C;
+    const RowParts p = row_parts(z, C);
+    const float4* z4 = reinterpret_cast<const float4*>(z + p.head);
+    float a[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = load_stream(z4 + j + 256 * u);
+    for (int u = 0; u < U; ++u) a[u] = 0.f;
+    int64_t j = t;
+    for (; j + (U - 1) * T < p.n4; j += U * T) {
+      float4 v[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+      for (int u = 0; u < U; ++u) v[u] = load_stream(z4 + j + u * T);
+#pragma unroll
+      for (int u = 0; u < U; ++u) a[u] += (v[u].x + v[u].y) + (v[u].z + v[u].w);
     }
-    for (; j < c4; j += 256) {
-      const float4 v = load_stream(z4 + j);
-      a[0] += (v.x + v.y) + (v.z + v.w);
-    }
-    s = (a[0] + a[1]) + (a[2] + a[3]);
-  } else {
-    for (int64_t j = threadIdx.x; j < C; j += 256) s += z[j];
+    // the last round, all loads at once
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = j + u * T < p.n4 ? load_stream(z4 + j + u * T) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float e = 0.f;
+    if (t < p.head) e = z[t];
+    if (t >= 4 && t < 4 + p.tail) e = z[C - p.tail + (t - 4)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+#pragma unroll
+    for (int u = 1; u < U; u *= 2)
+#pragma unroll
+      for (int w = 0; w + u < U; w += 2 * u) a[w] += a[w + u];
+    s = a[0] + e;
   }
   s = wave_sum(s);
-  if (lane == 0) part[wave] = s;
+  if (WAVES == 1) {
+    if (lane == 0 && row < R) r[row] = s;
+    return;
+  }
+  if (lane == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) r[row] = (part[0] + part[1]) + (part[2] + part[3]);
+  if (t == 0 && row < R) {
+    const float* q = part + threadIdx.x / T * WAVES;
+    float v[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) v[w] = q[w];
+#pragma unroll
+    for (int u = 1; u < WAVES; u *= 2)
+#pragma unroll
+      for (int w = 0; w + u < WAVES; w += 2 * u) v[w] += v[w + u];
+    r[row] = v[0];
+  }
 }
 
 // ---------------------------------------------------------------- softmax
-// Row held in registers: NV float4 per lane, WAVES waves per row.
+// Row held in registers: NV float4 per lane, WAVES waves per row, and in
+// lanes 0-2 and 4-6 the floats before the row's first and after its last
+// 16-byte boundary.  X and Y rows share their alignment.
 template <int WAVES, int NV, bool NT>
-__global__ __launch_bounds__(256) void softmax_reg(const float* __restrict__ X,
-                                                   float* __restrict__ Y, int64_t R, int64_t L) {
-  constexpr int T = WAVES * 64;               // lanes per row
-  constexpr int ROWS = 256 / T;               // rows per workgroup
-  __shared__ float red[4];
+__global__ __launch_bounds__(WAVES <= 4 ? 256 : 64 * WAVES) void softmax_reg(
+    const float* __restrict__ X, float* __restrict__ Y, int64_t R, int64_t L) {
+  constexpr int T = WAVES * 64;                    // lanes per row
+  constexpr int ROWS = WAVES <= 4 ? 256 / T : 1;   // rows per workgroup
+  __shared__ float red[ROWS * WAVES];
   const int t = threadIdx.x % T;
   const int sub = threadIdx.x / T;
   const int lane = threadIdx.x & 63;
@@ -173,19 +198,22 @@ __global__ __launch_bounds__(256) void softmax_reg(const float* __restrict__ X,
   const bool live = row < R;
   const float* x = X + row * L;
   float* y = Y + row * L;
+  const RowParts p = row_parts(x, live ? L : 0);
+  const float4* x4 = reinterpret_cast<const float4*>(x + p.head);
+  float4* y4 = reinterpret_cast<float4*>(y + p.head);
+  const int64_t end = t < p.head ? t : t >= 4 && t < 4 + p.tail ? L - p.tail + (t - 4) : -1;
   float4 v[NV];
-  const int64_t L4 = L / 4;
-  float m = -INFINITY;
+  float e = end >= 0 ? x[end] : -INFINITY;
+  float m = e;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int64_t j = t + (int64_t)i * T;
-    if (live && j < L4) {
-      v[i] = ld4<NT>(reinterpret_cast<const float4*>(x) + j);
-      m = fmaxf(m, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
-    } else {
-      v[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    }
+    v[i] = j < p.n4 ? ld4<NT>(x4 + j)
+                    : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
   }
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    m = fmaxf(m, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
   m = wave_max(m);
   if (WAVES > 1) {
     if (lane == 0) red[threadIdx.x >> 6] = m;
@@ -195,7 +223,7 @@ __global__ __launch_bounds__(256) void softmax_reg(const float* __restrict__ X,
     for (int w = 1; w < WAVES; ++w) m = fmaxf(m, red[wbase + w]);
     __syncthreads();
   }
-  float s = 0.f;
+  float s = e = expf(e - m);
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     v[i].x = expf(v[i].x - m);
@@ -213,12 +241,12 @@ __global__ __launch_bounds__(256) void softmax_reg(const float* __restrict__ X,
     for (int w = 1; w < WAVES; ++w) s += red[wbase + w];
   }
   const float inv = 1.0f / s;
+  if (end >= 0) y[end] = e * inv;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int64_t j = t + (int64_t)i * T;
-    if (live && j < L4)
-      st4<NT>(reinterpret_cast<float4*>(y) + j,
-              make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv));
+    if (j < p.n4)
+      st4<NT>(y4 + j, make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv));
   }
 }
 
@@ -313,77 +341,79 @@ hipError_t bias_relu_f32_launch(const float* X, const float* b, float* Y, int64_
   return hipGetLastError();
 }
 
+// One wave a row up to 512 floats (two float4 a lane), four waves a row from
+// there, sixteen where the rows are long and four waves of each would leave
+// CUs with little in flight.
 OpPlan rowsum_f32_plan(int64_t R, int64_t C) {
   OpPlan p;
-  p.block = dim3(256);
-  if (C <= 2048) {
-    p.func = reinterpret_cast<const void*>(&rowsum_wave);
+  if (C <= 512) {
+    p.func = reinterpret_cast<const void*>(&rowsum_rows<1, 2>);
     p.grid = dim3((unsigned)((R + 3) / 4));
-  } else {
-    p.func = reinterpret_cast<const void*>(&rowsum_block);
+    p.block = dim3(256);
+  } else if (C <= 2048) {
+    p.func = reinterpret_cast<const void*>(&rowsum_rows<1, 8>);
+    p.grid = dim3((unsigned)((R + 3) / 4));
+    p.block = dim3(256);
+  } else if (C <= 8192 || R >= 1024) {
+    p.func = reinterpret_cast<const void*>(&rowsum_rows<4, 4>);
     p.grid = dim3((unsigned)R);
+    p.block = dim3(256);
+  } else {
+    p.func = reinterpret_cast<const void*>(&rowsum_rows<16, 4>);
+    p.grid = dim3((unsigned)R);
+    p.block = dim3(1024);
   }
   return p;
 }
 
 hipError_t rowsum_f32_launch(const float* Z, float* r, int64_t R, int64_t C, hipStream_t s) {
   OpPlan p = rowsum_f32_plan(R, C);
-  if (C <= 2048)
-    hipLaunchKernelGGL(rowsum_wave, p.grid, p.block, 0, s, Z, r, R, C);
-  else
-    hipLaunchKernelGGL(rowsum_block, p.grid, p.block, 0, s, Z, r, R, C);
-  return hipGetLastError();
+  void* args[] = {&Z, &r, &R, &C};
+  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
 }
 
-// Register-resident variants by row length (L % 4 == 0):
-//   L <= 256: one wave per row, 1 float4 per lane; <= 1024: one wave, 4;
-//   <= 2048: two waves, 4; <= 4096: four waves, 4.
-OpPlan softmax_f32_plan(int64_t R, int64_t L, bool vec) {
+namespace {
+// Register-resident variants by row length: one wave per row of up to 256
+// floats (one float4 a lane) or 1024 (four), then two, four, eight and
+// sixteen waves.  512 rows of 8192 took 18.2 us in three passes over memory,
+// 3000 rows of 2999 25.3 (element by element).
+template <int W, int V>
+OpPlan softmax_plan(int64_t R, bool nt) {
   OpPlan p;
-  p.block = dim3(256);
-  if (!vec || L > 4096) {
-    p.func = reinterpret_cast<const void*>(&softmax_any);
-    p.grid = dim3((unsigned)R);
-  } else if (L <= 256) {
-    p.func = reinterpret_cast<const void*>(&softmax_reg<1, 1, false>);
-    p.grid = dim3((unsigned)((R + 3) / 4));
-  } else if (L <= 1024) {
-    p.func = reinterpret_cast<const void*>(&softmax_reg<1, 4, false>);
-    p.grid = dim3((unsigned)((R + 3) / 4));
-  } else if (L <= 2048) {
-    p.func = reinterpret_cast<const void*>(&softmax_reg<2, 4, false>);
-    p.grid = dim3((unsigned)((R + 1) / 2));
-  } else {
-    p.func = reinterpret_cast<const void*>(&softmax_reg<4, 4, false>);
-    p.grid = dim3((unsigned)R);
-  }
+  p.func = nt ? reinterpret_cast<const void*>(&softmax_reg<W, V, true>)
+              : reinterpret_cast<const void*>(&softmax_reg<W, V, false>);
+  const int rows = W <= 4 ? 4 / W : 1;
+  p.grid = dim3((unsigned)((R + rows - 1) / rows));
+  p.block = dim3(W <= 4 ? 256 : 64 * W);
   return p;
 }
 
-template <int W, int V>
-static void launch_softmax_reg(bool nt, const OpPlan& p, hipStream_t s, const float* X, float* Y,
-                               int64_t R, int64_t L) {
-  if (nt)
-    hipLaunchKernelGGL((softmax_reg<W, V, true>), p.grid, p.block, 0, s, X, Y, R, L);
-  else
-    hipLaunchKernelGGL((softmax_reg<W, V, false>), p.grid, p.block, 0, s, X, Y, R, L);
+OpPlan softmax_plan_for(int64_t R, int64_t L, bool vec) {
+  const bool nt = R * L * 4 >= kStreamBytes;
+  if (!vec || L > 16384) {
+    OpPlan p;
+    p.func = reinterpret_cast<const void*>(&softmax_any);
+    p.grid = dim3((unsigned)R);
+    p.block = dim3(256);
+    return p;
+  }
+  if (L <= 256) return softmax_plan<1, 1>(R, nt);
+  if (L <= 1024) return softmax_plan<1, 4>(R, nt);
+  if (L <= 2048) return softmax_plan<2, 4>(R, nt);
+  if (L <= 4096) return softmax_plan<4, 4>(R, nt);
+  if (L <= 8192) return softmax_plan<8, 4>(R, nt);
+  return softmax_plan<16, 4>(R, nt);
 }
+}  // namespace
+
+// (`vec` of the caller's plan, whole float4 rows, no longer matters)
+OpPlan softmax_f32_plan(int64_t R, int64_t L, bool) { return softmax_plan_for(R, L, true); }
 
 hipError_t softmax_f32_launch(const float* X, float* Y, int64_t R, int64_t L, hipStream_t s) {
-  const bool vec = (L % 4 == 0) && aligned16(X) && aligned16(Y);
-  OpPlan p = softmax_f32_plan(R, L, vec);
-  const bool nt = R * L * 4 >= kStreamBytes;
-  if (!vec || L > 4096)
-    hipLaunchKernelGGL(softmax_any, p.grid, p.block, 0, s, X, Y, R, L);
-  else if (L <= 256)
-    launch_softmax_reg<1, 1>(nt, p, s, X, Y, R, L);
-  else if (L <= 1024)
-    launch_softmax_reg<1, 4>(nt, p, s, X, Y, R, L);
-  else if (L <= 2048)
-    launch_softmax_reg<2, 4>(nt, p, s, X, Y, R, L);
-  else
-    launch_softmax_reg<4, 4>(nt, p, s, X, Y, R, L);
-  return hipGetLastError();
+  const uintptr_t x = reinterpret_cast<uintptr_t>(X), y = reinterpret_cast<uintptr_t>(Y);
+  OpPlan p = softmax_plan_for(R, L, (x & 3) == 0 && ((x ^ y) & 15) == 0);
+  void* args[] = {&X, &Y, &R, &L};
+  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
 }
 
 // ------------------------------------------------------------ vector add
