@@ -34,16 +34,21 @@
 // before each barrier.  K slices are summed through LDS in a fixed order.
 // RAGGED (FP8 rows that are not a multiple of 64 bytes): the chunks past the
 // row's end are read from a zero slice.
+// PAIR: two stages are loaded together, the two halves of a row's 128-byte
+// line by neighbouring loads.  A stage alone fetches half a line, and by the
+// next one the rest has left the first-level cache: twice the traffic from
+// the second level, which is what bounds large products.  The lead is two
+// stages instead of three.
 //
 // What bounds it, and the tiles: 256 x 256 is bound by the rate at which
-// panels stream into LDS (about 7.9 TB/s over the chip) and needs about 144
+// panels stream into LDS (about 9 TB/s over the chip) and needs about 144
 // tiles to fill it; anything smaller left most CUs idle, and a short product
 // is a chain of steps whose latency (barrier, LDS, loads) K slices divide.
-// us per launch, 256 x 256 only -> now: BF16 4096^3 134, 2048^3 47 -> 24,
+// us per launch, 256 x 256 only -> now: BF16 4096^3 122 -> 117, 2048^3 47 -> 24,
 // 1280x1792x768 22 -> 9.2, 1024^3 25 -> 6.5, 512^3 16 -> 4.1, 256x256x2048
-// 42 -> 5.9; BF16 convolution C = 256, 256^2 100, C = 128, 128^2 45 -> 17,
-// C = 64, 128^2 26 -> 8.6, C = 256, 32^2 80 -> 8.9; FP8 2048x8192x8192 125,
-// 2048^3 27 -> 14, 1024^3 15 -> 4.9.
+// 42 -> 5.9; BF16 convolution C = 256, 256^2 88 -> 84, C = 128, 128^2 45 -> 17,
+// C = 64, 128^2 26 -> 8.6, C = 256, 32^2 80 -> 8.9; FP8 2048x8192x8192
+// 122 -> 115, 2048^3 27 -> 14, 1024^3 15 -> 4.9.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -131,7 +136,8 @@ struct Ring {
 // rows of kb = 18 Cc bytes): M output channels, N = H W pixels, and K slice
 // s = (tap, 32-channel group) of a pixel row read at the pixel shifted by the
 // tap (zero slice outside the image).
-template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST>
+template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
+          bool PAIR>
 __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     const unsigned char* __restrict__ A, const unsigned char* __restrict__ Bt,
     float* __restrict__ C, int M, int N, int kb, int H, int W, int Cc, unsigned* sig) {
@@ -181,15 +187,14 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
   // Stages past the end re-load the last K slice into their own slot, which
   // is never read again: every step issues the same number of loads, so the
   // wait counts are constants.
-  auto issue = [&](int step) {
+  auto loader = [&](int step) {
     const int slot = step % NST;
     const int sc = min(step * KS + ks, steps - 1);
     const int k0 = sc * RK;
     const int tap = CONV ? (groups > 1 ? (int)__umulhi(sc, inv) : sc) : 0;
     const int grp = sc - tap * groups;
     const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
+    auto one = [=, &src, &at, &py, &px, &kcs](int i) {
       const unsigned to = (unsigned)(uintptr_t)(lds + slot * R::STAGE) + at[i];
       const unsigned char* g = src[i] + k0;
       if (RAGGED && k0 + 16 * kcs[i] >= kb) g = kZeroSlice + 16 * kcs[i];
@@ -202,6 +207,21 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
         }
       }
       ring_load16(g, __builtin_amdgcn_readfirstlane(to));
+    };
+    return one;
+  };
+  auto issue = [&](int step) {
+    auto one = loader(step);
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) one(i);
+  };
+  // two stages, block by block: the two halves of a row's 128 bytes together
+  auto issue2 = [&](int step) {
+    auto one = loader(step), two = loader(step + 1);
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      one(i);
+      two(i);
     }
   };
 
@@ -266,14 +286,34 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     if (KS == 1 || s * KS + ks < steps) multiply(ca, cb);
   };
 
-  for (int s = 0; s < NST; ++s) issue(s);
-  ring_wait_loads<(NST - 1) * CPT>();
-  asm volatile("s_barrier" ::: "memory");
   i32x8 a0[TM], b0[TN], a1[TM], b1[TN];
-  read(0, a0, b0);
-  for (int s = 0; s < mine; s += 2) {
-    step(s, a0, b0, a1, b1);
-    if (s + 1 < mine) step(s + 1, a1, b1, a0, b0);
+  if constexpr (PAIR) {
+    static_assert(NST == 4 && KS == 1, "two pairs of stages, one K slice");
+    issue2(0);
+    issue2(2);
+    ring_wait_loads<2 * CPT>();
+    asm volatile("s_barrier" ::: "memory");
+    read(0, a0, b0);
+    for (int s = 0; s < mine; s += 2) {
+      read(s + 1, a1, b1);
+      multiply(a0, b0);
+      // stages s, s + 1 are in registers in every wave, s + 2 and s + 3 in LDS
+      ring_wait_loads<0>();
+      __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
+      asm volatile("s_barrier" ::: "memory");
+      issue2(s + 4);
+      read(s + 2, a0, b0);
+      if (s + 1 < mine) multiply(a1, b1);
+    }
+  } else {
+    for (int s = 0; s < NST; ++s) issue(s);
+    ring_wait_loads<(NST - 1) * CPT>();
+    asm volatile("s_barrier" ::: "memory");
+    read(0, a0, b0);
+    for (int s = 0; s < mine; s += 2) {
+      step(s, a0, b0, a1, b1);
+      if (s + 1 < mine) step(s + 1, a1, b1, a0, b0);
+    }
   }
   // no load may still be writing LDS when the workgroup ends
   ring_wait_loads<0>();
@@ -327,11 +367,13 @@ struct Launch {
   const void* func;
   int bm, bn, nt;
 };
-template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST>
+template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
+          bool PAIR = false>
 Launch ring() {
   using R = Ring<WM, WN, TM, TN, KS, NST>;
-  return {reinterpret_cast<const void*>(&gemm_ring<T, CONV, RAGGED, WM, WN, TM, TN, KS, NST>), R::BM, R::BN,
-          R::NT};
+  return {reinterpret_cast<const void*>(
+              &gemm_ring<T, CONV, RAGGED, WM, WN, TM, TN, KS, NST, PAIR>),
+          R::BM, R::BN, R::NT};
 }
 
 int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
@@ -354,13 +396,23 @@ int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm)
 //   rounds do (C = 160, 100^2: 20.3 against 26.0; C = 64, 256^2, 1024
 //   workgroups: 21.1 against 17.4), four for a longer one (C = 256, 64^2: 17.2
 //   against 19.7; C = 64, 128^2, 18 steps: 9.4 against 8.6).
+// Stages in pairs where workgroups enough hide the shorter lead (us single ->
+// pairs): 256 x 256 from 192 workgroups (4096^3 121.5 -> 117, FP8
+// 2048x8192x8192 122 -> 115; 3072x3072x2048, 144: 47.8 -> 50.1), 128 x 128 from
+// two a CU (2304x3072x768 19.5 -> 18.4, FP8 2048x4096x4096 44 -> 37.5; 2048^3,
+// 256: 23.3 -> 26.6), both always for convolutions (C = 256, 256^2 88 -> 84),
+// 64 x 64 always (1024x2048x1024 9.5 -> 8.7).
 template <int T, bool CONV, bool RAGGED>
 Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
   const int64_t steps = (kb + RK - 1) / RK;
   const int64_t t256 = tiles(M, N, 256, 256), t128 = tiles(M, N, 128, 128);
   const int64_t t64 = tiles(M, N, 64, 64), t32 = tiles(M, N, 32, 32);
-  if (t256 >= 144 && 3 * t256 <= t128) return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
-  if (t64 > 512 && 3 * t128 <= t64) return ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4>();
+  if (t256 >= 144 && 3 * t256 <= t128)
+    return CONV || t256 >= 192 ? ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4, true>()
+                               : ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
+  if (t64 > 512 && 3 * t128 <= t64)
+    return CONV || t128 > 256 ? ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4, true>()
+                              : ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4>();
   if (t32 <= 256 && (CONV || steps >= 64)) return ring<T, CONV, RAGGED, 1, 1, 1, 1, 8, 4>();
   if constexpr (CONV) {
     if (t64 <= 256 && steps >= 36) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 4, 4>();
@@ -369,7 +421,7 @@ Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
     if (t64 <= 128) return ring<T, CONV, RAGGED, 1, 2, 1, 1, 2, 4>();
     if (t64 <= 256 && steps >= 32) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 2, 4>();
   }
-  return ring<T, CONV, RAGGED, 2, 2, 1, 1, 1, 4>();
+  return ring<T, CONV, RAGGED, 2, 2, 1, 1, 1, 4, true>();
 }
 
 OpPlan ring_plan(const Launch& l, int64_t M, int64_t N) {

@@ -43,3 +43,24 @@ def test_conv3x3_bf16_tiles(C, H, W):
     X, Wt = BF16[r.integers(0, 5, (H, W, C))], BF16[r.integers(0, 5, (C, 3, 3, C))]
     assert np.array_equal(G.run_conv_bf16(X, Wt),
                           OK.conv3x3_bf16_f64(X, Wt).astype(np.float32))
+
+
+# stages loaded in pairs, odd and even numbers of them, fewer than the ring
+# holds and more: 256x256; 128x128; 64x64
+PAIRS = [(3600, 3500, 32), (3590, 3585, 160), (2300, 2310, 96), (2177, 2305, 64), (1000, 900, 288)]
+
+
+@pytest.mark.parametrize("M,N,K", PAIRS)
+def test_gemm_bf16_stage_pairs(M, N, K):
+    test_gemm_bf16_tiles(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(m, n, 2 * k + d) for m, n, k in PAIRS for d in (0, 16)])
+def test_gemm_fp8_stage_pairs(M, N, K):
+    test_gemm_fp8_tiles(M, N, K)
+
+
+# 256x256 with an odd number of steps
+@pytest.mark.parametrize("C,H,W", [(224, 193, 192)])
+def test_conv3x3_bf16_stage_pairs(C, H, W):
+    test_conv3x3_bf16_tiles(C, H, W)
