@@ -15,8 +15,11 @@
 //   One workgroup per 2048 cells reading every point's cell and reducing in
 //   LDS took 19.7 us (8.8 at 20 000).
 //
-// * binned (large clouds): the grid is cut into tiles of kTileCells
-//   consecutive cells, small enough that one tile's accumulators live in LDS.
+// * binned (large clouds): the grid is cut into tiles of kTileCells cells,
+//   small enough that one tile's accumulators live in LDS.  A tile takes its
+//   cells from all over the grid (tiled): with consecutive cells the tiles of
+//   a cloud's dense rows held twice the mean, and the reduction waited for
+//   them (8 M points 84 -> 71 us, 4 M 46 -> 43, 1.1 M 33.5 -> 31.4).
 //     1. bin:    per chunk of kChunk points (read once), the cell of every
 //                point (vidx) and an 8-byte record (z key, cell in tile,
 //                index in chunk) per point, counting-sorted by tile in LDS
@@ -147,6 +150,20 @@ __device__ void block_scan_tiles(int n, F val, int* out, int* wsum) {
   __syncthreads();
 }
 
+// Where a cell is kept: blocks of 64 consecutive cells are dealt to the T
+// tiles in turn, each round of T blocks one tile further, so that the rows and
+// the columns of a dense part of the cloud spread over all tiles.  Returns
+// tile << kTileBits | place in the tile.  b < 2^16 and T <= 2^10: the
+// rounding errors of the quotients (2^-22 of at most 2^16 / T) stay below the
+// 0.5 / T that part them from a wrong whole number.
+__device__ __forceinline__ int tiled(int v, int T, float invT) {
+  const int b = v >> 6;
+  const int r = (int)(((float)b + 0.5f) * invT);   // b / T, below kTileCells / 64
+  const int m = b - r * T + r;
+  const int t = m - (int)(((float)m + 0.5f) * invT) * T;
+  return (t << kTileBits) | (r << 6) | (v & 63);
+}
+
 // 1. bin: one chunk of kChunk points per workgroup, read once.  Every lane
 //    keeps its 32 points' cells and z keys in registers while the chunk's
 //    tile histogram builds up in LDS; the exclusive scan of the histogram
@@ -175,7 +192,8 @@ __global__ __launch_bounds__(256) void voxel_bin(const float4* __restrict__ pts,
   __syncthreads();
   const int64_t beg = (int64_t)c * kChunk;
   const int64_t end = beg + kChunk < N ? beg + kChunk : N;
-  int cell[kPerLane];
+  const float invT = 1.0f / (float)T;
+  int cell[kPerLane];   // as kept (tiled)
   unsigned zk[kPerLane];
   // eight points a lane in flight
 #pragma unroll
@@ -193,7 +211,10 @@ __global__ __launch_bounds__(256) void voxel_bin(const float4* __restrict__ pts,
       if (j < end) {
         v = cell_of(p[u], nx, ny, xmin, ymin, scale);
         vidx[j] = v;
-        if (v >= 0) atomicAdd(&cur[v >> kTileBits], 1);
+        if (v >= 0) {
+          v = tiled(v, T, invT);
+          atomicAdd(&cur[v >> kTileBits], 1);
+        }
       }
       cell[u0 + u] = v;
       zk[u0 + u] = zkey(p[u].z);
@@ -313,13 +334,16 @@ __global__ __launch_bounds__(256) void voxel_merge(const int* __restrict__ pc,
                                                    const unsigned* __restrict__ pz,
                                                    const int* __restrict__ pf,
                                                    int* __restrict__ count, float* __restrict__ zmax,
-                                                   int* __restrict__ first, int64_t G, int groups) {
+                                                   int* __restrict__ first, int64_t G, int T,
+                                                   int groups) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= G) return;
-  const int t = (int)(v >> kTileBits);
-  const int l = (int)(v & (kTileCells - 1));
+  const int at = tiled((int)v, T, 1.0f / (float)T);
+  const int t = at >> kTileBits;
+  const int l = at & (kTileCells - 1);
   int c = 0, f = INT_MAX;
   unsigned z = kKeyNegInf;
+#pragma unroll 4
   for (int s = t * groups; s < (t + 1) * groups; ++s) {
     const int64_t o = (int64_t)s * kTileCells + l;
     c += pc[o];
@@ -359,8 +383,8 @@ Binned binned_layout(int64_t N, int64_t G) {
       1, std::min<int64_t>(b.nb / kMinChunksPerGroup, (2048 + b.T - 1) / b.T));
   // A workgroup's time grows with its chunks, the partial tiles written and
   // read back with the groups: the best number grows as the root of the
-  // chunks (4 M points 46 us at 7 groups, 52 at 3 and at 15; 8 M 77 at 7, 84 at
-  // 15, 93 at 3; 20 M 187 at 12, 210 at 32).
+  // chunks (4 M points 43 us at 4 to 10 groups, 46 at 3; 8 M 71 at 7 and 8, 80
+  // at 3, 10 and 12).
   b.groups = std::max(1, std::min(most, (int)std::lround(std::sqrt((double)b.nb) / 4)));
   b.cpg = (b.nb + b.groups - 1) / b.groups;
   size_t off = 0;
@@ -422,7 +446,7 @@ hipError_t voxel_f32_launch(const float* pts, int* vidx, int* count, float* zmax
     hipLaunchKernelGGL(voxel_tile_reduce, dim3(b.T * b.groups), blk, 0, s, H, R, pc, pz, pf, b.T,
                        b.nb, b.groups, b.cpg);
     hipLaunchKernelGGL(voxel_merge, dim3(grid_for(G, INT_MAX)), blk, 0, s, pc, pz, pf, count,
-                       zmax, first, G, b.groups);
+                       zmax, first, G, b.T, b.groups);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(voxel_init, dim3(grid_for(G, 256 * 8)), blk, 0, s, count, zmax, first, G);
