@@ -1,19 +1,29 @@
 // Bird's-eye-view pillar binning of a point cloud (FP32 points -> int cells).
 //
 // Per cell: count, maximum z and smallest point index; per point: its cell.
-// All three reductions are order independent, so both paths below give
+// All three reductions are order independent, so all paths below give
 // bit-identical outputs.
 //
-// Two paths, chosen by size:
+// Three paths, chosen by size:
 //
-// * direct (small clouds, and grids of more than kMaxTiles tiles): init, then
-//   one lane per point with three atomics on its cell in global memory, on
-//   values that need no decoding afterwards (zmax as the float itself, see
-//   put_zmax; first as unsigned, -1 last): two launches, three before
-//   (100 000 points 17.4 -> 15.2 us, 20 000 8.6 -> 6.3).  Bound by the
-//   atomics, about 27 G/s whatever their scope, 11 us of it at 100 000 points.
-//   One workgroup per 2048 cells reading every point's cell and reducing in
-//   LDS took 19.7 us (8.8 at 20 000).
+// * direct (clouds below 56 Ki points, and grids that the others do not
+//   take): init, then one lane per point with three atomics on its cell in
+//   global memory, on values that need no decoding afterwards (zmax as the
+//   float itself, see put_zmax; first as unsigned, -1 last): two launches
+//   (20 000 points 6.3 us, three launches 8.6).  Bound by the atomics, about
+//   27 G/s whatever their scope.
+//
+// * listed (56 Ki to 1 Mi points, no workspace): per chunk, the points sorted
+//   by tile of the grid, as 16-bit places kept in the chunk's own part of
+//   vidx; per tile, its points of all chunks reduced in LDS and written out;
+//   last, the points' cells into vidx.  No atomics on global memory and no
+//   partial tiles, at the price of reading the points three times (the second
+//   time a 128-byte line for a few of its eight points, which bounds the
+//   largest).  us, direct -> listed: 70 000 points 12.5 -> 10.7, 100 000
+//   15.4 -> 11.1, 200 000 27.5 -> 12.8, 400 000 49.7 -> 17.7, 1 M 117 -> 31;
+//   all points in one cell, 400 000: 5070 -> 1150.  (A cloud almost all
+//   outside of the grid has no atomics to save: 400 000 points, 2 % inside,
+//   6.9 -> 12.5.)
 //
 // * binned (large clouds): the grid is cut into tiles of kTileCells cells,
 //   small enough that one tile's accumulators live in LDS.  A tile takes its
@@ -153,15 +163,15 @@ __device__ void block_scan_tiles(int n, F val, int* out, int* wsum) {
 // Where a cell is kept: blocks of 64 consecutive cells are dealt to the T
 // tiles in turn, each round of T blocks one tile further, so that the rows and
 // the columns of a dense part of the cloud spread over all tiles.  Returns
-// tile << kTileBits | place in the tile.  b < 2^16 and T <= 2^10: the
+// tile << tb | place in the tile of 2^tb cells.  b < 2^16 and T <= 2^10: the
 // rounding errors of the quotients (2^-22 of at most 2^16 / T) stay below the
 // 0.5 / T that part them from a wrong whole number.
-__device__ __forceinline__ int tiled(int v, int T, float invT) {
+__device__ __forceinline__ int tiled(int v, int T, float invT, int tb) {
   const int b = v >> 6;
-  const int r = (int)(((float)b + 0.5f) * invT);   // b / T, below kTileCells / 64
+  const int r = (int)(((float)b + 0.5f) * invT);   // b / T, below 2^(tb - 6)
   const int m = b - r * T + r;
   const int t = m - (int)(((float)m + 0.5f) * invT) * T;
-  return (t << kTileBits) | (r << 6) | (v & 63);
+  return (t << tb) | (r << 6) | (v & 63);
 }
 
 // 1. bin: one chunk of kChunk points per workgroup, read once.  Every lane
@@ -212,7 +222,7 @@ __global__ __launch_bounds__(256) void voxel_bin(const float4* __restrict__ pts,
         v = cell_of(p[u], nx, ny, xmin, ymin, scale);
         vidx[j] = v;
         if (v >= 0) {
-          v = tiled(v, T, invT);
+          v = tiled(v, T, invT, kTileBits);
           atomicAdd(&cur[v >> kTileBits], 1);
         }
       }
@@ -338,7 +348,7 @@ __global__ __launch_bounds__(256) void voxel_merge(const int* __restrict__ pc,
                                                    int groups) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= G) return;
-  const int at = tiled((int)v, T, 1.0f / (float)T);
+  const int at = tiled((int)v, T, 1.0f / (float)T, kTileBits);
   const int t = at >> kTileBits;
   const int l = at & (kTileCells - 1);
   int c = 0, f = INT_MAX;
@@ -353,6 +363,153 @@ __global__ __launch_bounds__(256) void voxel_merge(const int* __restrict__ pc,
   count[v] = c;
   zmax[v] = zval(z);
   first[v] = c ? f : -1;
+}
+
+// ------------------------------------------------------------------ listed
+// 1. list: per chunk of CHUNK points (the last chunk takes the rest, fewer
+//    than two chunks), the points' places in the chunk sorted by tile, 16
+//    bits each, behind the T + 1 offsets of the tiles' runs, written over the
+//    chunk's own part of vidx (the first 2 (T + 1 + n) of its 4 n bytes).
+constexpr int kListTiles = 256;      // tiles, at most: a workgroup a CU in the reduction
+constexpr int kListThreads = 1024;   // lanes of the reduction: chunks, at most
+
+template <int CHUNK>
+__global__ __launch_bounds__(256) void voxel_list(const float4* __restrict__ pts,
+                                                  uint32_t* __restrict__ lists, int64_t N, int nx,
+                                                  int ny, float xmin, float ymin, float scale,
+                                                  int T, int tb) {
+  static_assert(2 * (kListTiles + 1 + CHUNK) < 4 * CHUNK, "the list fits in the chunk's vidx");
+  constexpr int PER = 2 * CHUNK / 256;
+  __shared__ int cur[kListTiles], off[kListTiles + 1], wsum[4];
+  __shared__ uint32_t words[(kListTiles + 1 + 2 * CHUNK + 1) / 2];
+  uint16_t* out = reinterpret_cast<uint16_t*>(words);
+  const float invT = 1.0f / (float)T;
+  const int64_t beg = (int64_t)blockIdx.x * CHUNK;
+  const int n = (int)(blockIdx.x + 1 == gridDim.x ? N - beg : CHUNK);
+  if ((int)threadIdx.x < T) cur[threadIdx.x] = 0;
+  float4 p[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (u >= PER / 2 && n <= CHUNK) break;
+    p[u] = pts[beg + min((int)threadIdx.x + 256 * u, n - 1)];
+  }
+  __syncthreads();
+  int tile[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (u >= PER / 2 && n <= CHUNK) break;
+    const int v = cell_of(p[u], nx, ny, xmin, ymin, scale);
+    tile[u] = v >= 0 && (int)threadIdx.x + 256 * u < n ? tiled(v, T, invT, tb) >> tb : -1;
+    if (tile[u] >= 0) atomicAdd(&cur[tile[u]], 1);
+  }
+  __syncthreads();
+  block_scan_tiles(T, [&](int i) { return cur[i]; }, off, wsum);
+  for (int t = threadIdx.x; t <= T; t += 256) {
+    out[t] = (uint16_t)off[t];
+    if (t < T) cur[t] = T + 1 + off[t];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    if (u >= PER / 2 && n <= CHUNK) break;
+    if (tile[u] >= 0) out[atomicAdd(&cur[tile[u]], 1)] = (uint16_t)(threadIdx.x + 256 * u);
+  }
+  __syncthreads();
+  const int m = (T + 1 + off[T] + 1) / 2;
+  for (int i = threadIdx.x; i < m; i += 256) lists[beg + i] = words[i];
+}
+
+// 2. reduce: one workgroup per tile.  The tile's runs of all chunks (at most
+//    kListThreads) are laid end to end by a prefix sum of their lengths, so
+//    that every lane has the same share of them whatever their lengths; each
+//    point is read again for its cell in the tile and its z.
+template <int CHUNK>
+__global__ __launch_bounds__(kListThreads) void voxel_list_reduce(
+    const float4* __restrict__ pts, const uint16_t* __restrict__ lists, int* __restrict__ count,
+    float* __restrict__ zmax, int* __restrict__ first, int64_t G, int nx, int ny, float xmin,
+    float ymin, float scale, int T, int tb, int nb) {
+  __shared__ int acc_c[kTileCells], acc_f[kTileCells];
+  __shared__ unsigned acc_z[kTileCells];
+  __shared__ int pre[kListThreads];   // points of the tile in the chunks before
+  __shared__ int at[kListThreads];    // where a chunk's run starts in the lists, less pre
+  __shared__ int wsum[kListThreads / 64];
+  const float invT = 1.0f / (float)T;
+  const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int a = 0, len = 0;
+  if (tid < nb) {
+    const uint16_t* h = lists + (int64_t)tid * (2 * CHUNK) + t;
+    a = h[0];
+    len = h[1] - a;
+  }
+  for (int i = tid; i < 1 << tb; i += kListThreads) {
+    acc_c[i] = 0;
+    acc_z[i] = kKeyNegInf;
+    acc_f[i] = INT_MAX;
+  }
+  int incl = len;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += y;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kListThreads / 64; ++w) {
+    base += w < wave ? wsum[w] : 0;
+    total += wsum[w];
+  }
+  const int excl = base + incl - len;
+  pre[tid] = excl;
+  at[tid] = tid * (2 * CHUNK) + T + 1 + a - excl;
+  __syncthreads();
+  constexpr int U = 4;   // points of a lane in flight
+  for (int i0 = tid; i0 < total; i0 += U * kListThreads) {
+    int64_t j[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u * kListThreads, total - 1);
+      int c = 0;   // the last chunk with pre <= i
+#pragma unroll
+      for (int d = kListThreads / 2; d > 0; d >>= 1)
+        if (pre[c + d] <= i) c += d;
+      j[u] = (int64_t)c * CHUNK + lists[at[c] + i];
+    }
+    float4 p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = pts[j[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * kListThreads >= total) break;
+      const int l =
+          tiled(cell_of(p[u], nx, ny, xmin, ymin, scale), T, invT, tb) & ((1 << tb) - 1);
+      atomicAdd(&acc_c[l], 1);
+      atomicMax(&acc_z[l], zkey(p[u].z));
+      atomicMin(&acc_f[l], (int)j[u]);
+    }
+  }
+  __syncthreads();
+  for (int l = tid; l < 1 << tb; l += kListThreads) {
+    const int r = l >> 6;
+    const int m = t - r;   // mod T: the block's place in its round
+    const int64_t v = ((int64_t)r * T + m + (T - 1 - m) / T * T) * 64 + (l & 63);
+    if (v < G) {
+      const int c = acc_c[l];
+      count[v] = c;
+      zmax[v] = zval(acc_z[l]);
+      first[v] = c ? acc_f[l] : -1;
+    }
+  }
+}
+
+// 3. cells: the points' cells into vidx, now that the lists have been read.
+__global__ __launch_bounds__(256) void voxel_cells(const float4* __restrict__ pts,
+                                                   int* __restrict__ vidx, int64_t N, int nx,
+                                                   int ny, float xmin, float ymin, float scale) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride)
+    vidx[i] = cell_of(pts[i], nx, ny, xmin, ymin, scale);
 }
 
 unsigned grid_for(int64_t work, int64_t cap) {
@@ -403,6 +560,30 @@ Binned binned_layout(int64_t N, int64_t G) {
   return b;
 }
 
+// The listed path's tiles and chunks (tb 0: not taken).  Below 56 Ki points
+// the direct path's two launches are faster (50 000 9.8 against 10.5 us,
+// 70 000 12.5 against 10.7); a grid of fewer than 64 tiles of 64 cells leaves
+// the reduction too few workgroups, one of more than 256 tiles of 4096 has no
+// room for its offsets.  Chunks of 512 points up to 256 Ki (100 000 11.1
+// against 11.9; 400 000 equal).
+constexpr int64_t kListedMinPoints = 56 << 10, kListedSmallChunk = 256 << 10;
+struct Listed {
+  int tb = 0, T = 0, nb = 0;
+  bool small = false;
+};
+Listed listed(int64_t N, int64_t G) {
+  Listed l;
+  if (N < kListedMinPoints || N / 1024 > kListThreads || G <= 63 * 64 ||
+      G > (int64_t)kListTiles * kTileCells)
+    return l;
+  l.tb = 6;
+  while (((G - 1) >> l.tb) >= kListTiles) ++l.tb;
+  l.T = (int)((G - 1) >> l.tb) + 1;
+  l.small = N <= kListedSmallChunk;
+  l.nb = (int)(N / (l.small ? 512 : 1024));
+  return l;
+}
+
 }  // namespace
 
 size_t voxel_f32_workspace(int64_t N, int nx, int ny) {
@@ -447,6 +628,25 @@ hipError_t voxel_f32_launch(const float* pts, int* vidx, int* count, float* zmax
                        b.nb, b.groups, b.cpg);
     hipLaunchKernelGGL(voxel_merge, dim3(grid_for(G, INT_MAX)), blk, 0, s, pc, pz, pf, count,
                        zmax, first, G, b.T, b.groups);
+    return hipGetLastError();
+  }
+  if (const Listed l = listed(N, G); l.tb) {
+    uint32_t* lists = reinterpret_cast<uint32_t*>(vidx);
+    const uint16_t* lists16 = reinterpret_cast<const uint16_t*>(vidx);
+    const dim3 wide(kListThreads);
+    if (l.small) {
+      hipLaunchKernelGGL(voxel_list<512>, dim3(l.nb), blk, 0, s, p4, lists, N, nx, ny, xmin, ymin,
+                         scale, l.T, l.tb);
+      hipLaunchKernelGGL(voxel_list_reduce<512>, dim3(l.T), wide, 0, s, p4, lists16, count, zmax,
+                         first, G, nx, ny, xmin, ymin, scale, l.T, l.tb, l.nb);
+    } else {
+      hipLaunchKernelGGL(voxel_list<1024>, dim3(l.nb), blk, 0, s, p4, lists, N, nx, ny, xmin,
+                         ymin, scale, l.T, l.tb);
+      hipLaunchKernelGGL(voxel_list_reduce<1024>, dim3(l.T), wide, 0, s, p4, lists16, count, zmax,
+                         first, G, nx, ny, xmin, ymin, scale, l.T, l.tb, l.nb);
+    }
+    hipLaunchKernelGGL(voxel_cells, dim3(grid_for(N, 256 * 32)), blk, 0, s, p4, vidx, N, nx, ny,
+                       xmin, ymin, scale);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(voxel_init, dim3(grid_for(G, 256 * 8)), blk, 0, s, count, zmax, first, G);
