@@ -29,7 +29,8 @@
 //   small enough that one tile's accumulators live in LDS.  A tile takes its
 //   cells from all over the grid (tiled): with consecutive cells the tiles of
 //   a cloud's dense rows held twice the mean, and the reduction waited for
-//   them (8 M points 84 -> 71 us, 4 M 46 -> 43, 1.1 M 33.5 -> 31.4).
+//   them (8 M points 84 -> 71 us, 4 M 46 -> 43, 1.1 M 33.5 -> 31.4; tiles of
+//   4096 cells).
 //     1. bin:    per chunk of kChunk points (read once), the cell of every
 //                point (vidx) and an 8-byte record (z key, cell in tile,
 //                index in chunk) per point, counting-sorted by tile in LDS
@@ -53,9 +54,12 @@
 namespace ug {
 namespace {
 
-constexpr int kTileBits = 12;
-constexpr int kTileCells = 1 << kTileBits;        // cells per tile (48 KiB of LDS)
-constexpr int kMaxTiles = 1024;                   // binned grids: <= 4 Mi cells
+// Cells per tile: 24 KiB of LDS, five reduce workgroups a CU.  With 4096, two
+// a CU, the reduction of a small cloud left half of the CUs idle (1.1 M
+// points 31.3 -> 28.7 us, 2 M 33.4 -> 30.1, 4 M 43 -> 39.5, 8 M 70 -> 68).
+constexpr int kTileBits = 11;
+constexpr int kTileCells = 1 << kTileBits;
+constexpr int kMaxTiles = 2048;                   // binned grids: <= 4 Mi cells
 constexpr int64_t kChunk = 8192;                  // points per bin workgroup
 static_assert(kChunk <= 8192, "a record keeps the index in its chunk in 13 bits");
 constexpr int64_t kBinnedMinPoints = int64_t(1) << 20;
@@ -127,16 +131,16 @@ __global__ __launch_bounds__(256) void voxel_scatter(const float4* __restrict__ 
 }
 
 // ------------------------------------------------------------------ binned
-// Exclusive prefix sums of n <= kMaxTiles values (val(i) for i < n) into
-// out[0..n], out[n] = total, by one 256-lane workgroup (four values a lane).
-// `wsum` is 4 ints of LDS.  Ends with a barrier.
-template <typename F>
-__device__ void block_scan_tiles(int n, F val, int* out, int* wsum) {
+// Exclusive prefix sums of n <= 256 PER values (val(i) for i < n) into
+// out[0..n], out[n] = total < 2^16, by one 256-lane workgroup (PER values a
+// lane).  `wsum` is 4 ints of LDS.  Ends with a barrier.
+template <int PER, typename F>
+__device__ void block_scan_tiles(int n, F val, uint16_t* out, int* wsum) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  int a[4], s = 0;
+  int a[PER], s = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = 4 * t + k;
+  for (int k = 0; k < PER; ++k) {
+    const int i = PER * t + k;
     a[k] = i < n ? val(i) : 0;
     s += a[k];
   }
@@ -151,19 +155,19 @@ __device__ void block_scan_tiles(int n, F val, int* out, int* wsum) {
   int off = incl - s;
   for (int w = 0; w < wave; ++w) off += wsum[w];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = 4 * t + k;
-    if (i < n) out[i] = off;
+  for (int k = 0; k < PER; ++k) {
+    const int i = PER * t + k;
+    if (i < n) out[i] = (uint16_t)off;
     off += a[k];
   }
-  if (t == 255) out[n] = off;
+  if (t == 255) out[n] = (uint16_t)off;
   __syncthreads();
 }
 
 // Where a cell is kept: blocks of 64 consecutive cells are dealt to the T
 // tiles in turn, each round of T blocks one tile further, so that the rows and
 // the columns of a dense part of the cloud spread over all tiles.  Returns
-// tile << tb | place in the tile of 2^tb cells.  b < 2^16 and T <= 2^10: the
+// tile << tb | place in the tile of 2^tb cells.  b < 2^16: the
 // rounding errors of the quotients (2^-22 of at most 2^16 / T) stay below the
 // 0.5 / T that part them from a wrong whole number.
 __device__ __forceinline__ int tiled(int v, int T, float invT, int tb) {
@@ -189,12 +193,12 @@ __device__ __forceinline__ uint64_t record(unsigned zk, int cell, int idx) {
 }
 
 __global__ __launch_bounds__(256) void voxel_bin(const float4* __restrict__ pts,
-                                                 int* __restrict__ vidx, int* __restrict__ H,
-                                                 uint64_t* __restrict__ R, int64_t N, int nx,
+                                                 int* __restrict__ vidx,
+                                                 uint16_t* __restrict__ H, uint64_t* __restrict__ R, int64_t N, int nx,
                                                  int ny, float xmin, float ymin, float scale,
                                                  int T) {
   __shared__ int cur[kMaxTiles];       // histogram, then cursors
-  __shared__ int off[kMaxTiles + 1];   // exclusive scan of the histogram
+  __shared__ uint16_t off[kMaxTiles + 1];   // exclusive scan of the histogram
   __shared__ int wsum[4];
   __shared__ uint64_t rec[kChunk];     // the chunk's records, sorted by tile
   const int c = blockIdx.x;
@@ -231,8 +235,8 @@ __global__ __launch_bounds__(256) void voxel_bin(const float4* __restrict__ pts,
     }
   }
   __syncthreads();
-  block_scan_tiles(T, [&](int i) { return cur[i]; }, off, wsum);
-  int* h = H + (int64_t)c * (T + 1);
+  block_scan_tiles<kMaxTiles / 256>(T, [&](int i) { return cur[i]; }, off, wsum);
+  uint16_t* h = H + (int64_t)c * (T + 1);
   for (int t = threadIdx.x; t <= T; t += 256) h[t] = off[t];
   for (int t = threadIdx.x; t < T; t += 256) cur[t] = off[t];
   __syncthreads();
@@ -267,13 +271,12 @@ __device__ __forceinline__ void reduce_record(uint64_t r, int base, int* acc_c, 
   atomicMin(&acc_f[cc], base + (int)(r >> 44));
 }
 
-__global__ __launch_bounds__(256) void voxel_tile_reduce(const int* __restrict__ H,
+__global__ __launch_bounds__(256) void voxel_tile_reduce(const uint16_t* __restrict__ H,
                                                          const uint64_t* __restrict__ R,
                                                          int* __restrict__ pc,
                                                          unsigned* __restrict__ pz,
                                                          int* __restrict__ pf, int T, int nb,
                                                          int groups, int cpg) {
-  // 48 KiB of accumulators and 8 KiB of run bounds: two workgroups a CU
   __shared__ int acc_c[kTileCells];
   __shared__ unsigned acc_z[kTileCells];
   __shared__ int acc_f[kTileCells];
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(256) void voxel_tile_reduce(const int* __restrict__
     const int s1 = s0 + kStage < c1 ? s0 + kStage : c1;
     __syncthreads();   // the previous stage's bounds are no longer read
     for (int c = s0 + threadIdx.x; c < s1; c += 256) {
-      const int* h = H + (int64_t)c * (T + 1) + t;
+      const uint16_t* h = H + (int64_t)c * (T + 1) + t;
       bnd[c - s0] = make_int2(h[0], h[1]);
     }
     __syncthreads();
@@ -372,6 +375,7 @@ __global__ __launch_bounds__(256) void voxel_merge(const int* __restrict__ pc,
 //    chunk's own part of vidx (the first 2 (T + 1 + n) of its 4 n bytes).
 constexpr int kListTiles = 256;      // tiles, at most: a workgroup a CU in the reduction
 constexpr int kListThreads = 1024;   // lanes of the reduction: chunks, at most
+constexpr int kListCells = 4096;     // of a tile, at most
 
 template <int CHUNK>
 __global__ __launch_bounds__(256) void voxel_list(const float4* __restrict__ pts,
@@ -380,7 +384,8 @@ __global__ __launch_bounds__(256) void voxel_list(const float4* __restrict__ pts
                                                   int T, int tb) {
   static_assert(2 * (kListTiles + 1 + CHUNK) < 4 * CHUNK, "the list fits in the chunk's vidx");
   constexpr int PER = 2 * CHUNK / 256;
-  __shared__ int cur[kListTiles], off[kListTiles + 1], wsum[4];
+  __shared__ int cur[kListTiles], wsum[4];
+  __shared__ uint16_t off[kListTiles + 1];
   __shared__ uint32_t words[(kListTiles + 1 + 2 * CHUNK + 1) / 2];
   uint16_t* out = reinterpret_cast<uint16_t*>(words);
   const float invT = 1.0f / (float)T;
@@ -403,9 +408,9 @@ __global__ __launch_bounds__(256) void voxel_list(const float4* __restrict__ pts
     if (tile[u] >= 0) atomicAdd(&cur[tile[u]], 1);
   }
   __syncthreads();
-  block_scan_tiles(T, [&](int i) { return cur[i]; }, off, wsum);
+  block_scan_tiles<kListTiles / 256>(T, [&](int i) { return cur[i]; }, off, wsum);
   for (int t = threadIdx.x; t <= T; t += 256) {
-    out[t] = (uint16_t)off[t];
+    out[t] = off[t];
     if (t < T) cur[t] = T + 1 + off[t];
   }
   __syncthreads();
@@ -428,8 +433,8 @@ __global__ __launch_bounds__(kListThreads) void voxel_list_reduce(
     const float4* __restrict__ pts, const uint16_t* __restrict__ lists, int* __restrict__ count,
     float* __restrict__ zmax, int* __restrict__ first, int64_t G, int nx, int ny, float xmin,
     float ymin, float scale, int T, int tb, int nb) {
-  __shared__ int acc_c[kTileCells], acc_f[kTileCells];
-  __shared__ unsigned acc_z[kTileCells];
+  __shared__ int acc_c[kListCells], acc_f[kListCells];
+  __shared__ unsigned acc_z[kListCells];
   __shared__ int pre[kListThreads];   // points of the tile in the chunks before
   __shared__ int at[kListThreads];    // where a chunk's run starts in the lists, less pre
   __shared__ int wsum[kListThreads / 64];
@@ -534,14 +539,15 @@ Binned binned_layout(int64_t N, int64_t G) {
   Binned b;
   b.T = (int)((G + kTileCells - 1) / kTileCells);
   b.nb = (int)((N + kChunk - 1) / kChunk);
-  // The workspace holds the partial tiles of up to about 2048 reduce
-  // workgroups, of at least kMinChunksPerGroup chunks each.
+  // The workspace holds the partial tiles of up to about 2048 workgroups of
+  // 4096 cells, of at least kMinChunksPerGroup chunks each.
+  const int T2 = (b.T + 1) / 2;
   const int most = (int)std::max<int64_t>(
-      1, std::min<int64_t>(b.nb / kMinChunksPerGroup, (2048 + b.T - 1) / b.T));
+      1, std::min<int64_t>(b.nb / kMinChunksPerGroup, (2048 + T2 - 1) / T2));
   // A workgroup's time grows with its chunks, the partial tiles written and
   // read back with the groups: the best number grows as the root of the
-  // chunks (4 M points 43 us at 4 to 10 groups, 46 at 3; 8 M 71 at 7 and 8, 80
-  // at 3, 10 and 12).
+  // chunks (4 M points 39.2 to 39.5 us at 4 to 6 groups, 40 at 3 and 7; 8 M
+  // 67.3 to 68 at 4 to 8, 70.5 at 3).
   b.groups = std::max(1, std::min(most, (int)std::lround(std::sqrt((double)b.nb) / 4)));
   b.cpg = (b.nb + b.groups - 1) / b.groups;
   size_t off = 0;
@@ -550,7 +556,7 @@ Binned binned_layout(int64_t N, int64_t G) {
     off += (bytes + 255) / 256 * 256;
     return at;
   };
-  b.H = take(sizeof(int) * (size_t)b.nb * (b.T + 1));
+  b.H = take(sizeof(uint16_t) * (size_t)b.nb * (b.T + 1));
   b.R = take(sizeof(uint64_t) * (size_t)b.nb * kChunk);
   const size_t parts = (size_t)b.T * most * kTileCells;
   b.pc = take(sizeof(int) * parts);
@@ -574,7 +580,7 @@ struct Listed {
 Listed listed(int64_t N, int64_t G) {
   Listed l;
   if (N < kListedMinPoints || N / 1024 > kListThreads || G <= 63 * 64 ||
-      G > (int64_t)kListTiles * kTileCells)
+      G > (int64_t)kListTiles * kListCells)
     return l;
   l.tb = 6;
   while (((G - 1) >> l.tb) >= kListTiles) ++l.tb;
@@ -617,7 +623,7 @@ hipError_t voxel_f32_launch(const float* pts, int* vidx, int* count, float* zmax
     if (!ws || ws_bytes < b.total || (reinterpret_cast<uintptr_t>(ws) & 255))
       return hipErrorInvalidValue;
     char* w = static_cast<char*>(ws);
-    int* H = reinterpret_cast<int*>(w + b.H);
+    uint16_t* H = reinterpret_cast<uint16_t*>(w + b.H);
     uint64_t* R = reinterpret_cast<uint64_t*>(w + b.R);
     int* pc = reinterpret_cast<int*>(w + b.pc);
     unsigned* pz = reinterpret_cast<unsigned*>(w + b.pz);
