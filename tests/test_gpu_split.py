@@ -123,3 +123,16 @@ def test_conv_tiny_values(n, c, h, w):
     Y = G.run_conv(X, W)
     ref, scale = OK.conv3x3_f64(X, W), OK.conv3x3_abs_f64(X, W)
     assert np.all(np.abs(Y - ref) <= 9 * c * 2.0 ** -23 * scale)
+
+
+# 128 x 256 tiles, A loaded for two steps of 16 at a time: odd and even numbers
+# of steps, one to five, the first of them whole or not; edges of both sides
+@pytest.mark.parametrize("M,N,K", [(1930, 3900, 1), (1930, 3900, 16), (2048, 4096, 17),
+                                   (1930, 3900, 33), (2047, 4095, 48), (1930, 3900, 64),
+                                   (1930, 3900, 65)])
+def test_gemm_error_wide_tiles(M, N, K):
+    test_gemm_error(M, N, K)
+
+
+def test_gemm_values_without_a_split_wide_tiles():
+    test_gemm_values_without_a_split(1930, 3900, 40)
