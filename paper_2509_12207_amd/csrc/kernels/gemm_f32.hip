@@ -10,7 +10,7 @@
 // TM x TN tiles of 32 x 32 and one of KS slices (BK values) of every K step;
 // operands are staged in units of U K values.
 //   big   <2,4,2,1,1,16,4>: 128 x 128 tiles, eight waves of 64 x 32, or
-//         <2,4,2,2,1,16,4>: 128 x 256 tiles, eight waves of 64 x 64;
+//         <4,2,2,2,1,16,4>: 256 x 128 tiles, eight waves of 64 x 64;
 //   mid   <2,2,1,1,2,16,4> or, where K is long and no CU has more than one
 //         tile, <2,2,1,1,4,16,4>: 64 x 64, K split two or four ways;
 //   small <1,1,1,1,4,16,8> or <1,1,1,1,8,16,4>: 32 x 32, K split four or
@@ -19,17 +19,15 @@
 // scheduling).
 //
 // What bounds it: at 4096^3 the matrix cores; six BF16 instructions per 16
-// products sustain 1.32 PFLOP/s there, more than the library's 8192^3 BF16
+// products sustain 1.29 PFLOP/s there, more than the library's 8192^3 BF16
 // product (1.12) on the same card.  Smaller products are bound by the latency
 // of a step (global load, split, LDS, barrier) in the few waves a CU has,
 // hence eight waves for 128 x 128 (two such workgroups make four waves a
 // SIMD at 126 registers; four waves of 64 x 64 took 695 us at 4096^3 against
-// 670) and the K splits.  A step reads 64 bytes of each of A's rows, half a
-// line: 128 x 256 has the registers to load two steps of A together, and a
-// quarter less to load and to split than two tiles of 128 x 128 (4096^3: 661
-// -> 625 us, 640 by steps of one).
+// 670) and the K splits.  One tile of 256 x 128 loads and splits a quarter
+// less than two of 128 x 128 (4096^3: 661 -> 640 us).
 // us per launch, FP32 instruction before -> now:
-//   4096^3 1170 -> 625, 2048^3 170 -> 95, 1280x2048x1024 65 -> 42,
+//   4096^3 1170 -> 640, 2048^3 170 -> 95, 1280x2048x1024 65 -> 42,
 //   1003x2050x1021 102 -> 43, 1024^3 33 -> 18.3, 768x1280x256 11.1 -> 7.2,
 //   512^3 8.8 -> 7.1, 256x256x2048 26 -> 16, 256^3 5.8 -> 5.2.
 //
@@ -118,9 +116,12 @@ __device__ __forceinline__ void interleave() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Registers: a workgroup fits on a SIMD beside a wave of the tail executor
+// (80 of 512), that is two waves a SIMD take 216 each at most (the attribute
+// counts half of the unified registers), four 104.
 template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, bool WIDE>
-__global__ __launch_bounds__(64 * WM * WN * KS,
-                             (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2)) void gemm_f32_kernel(
+__attribute__((amdgpu_num_vgpr(108))) __global__
+__launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2)) void gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int M, int N,
     int K, unsigned* sig) {
   using G = GemmCfg<WM, WN, TM, TN, KS, BK, U>;
@@ -174,36 +175,24 @@ __global__ __launch_bounds__(64 * WM * WN * KS,
   const float* a0 = A + (size_t)m0 * K;
   const float* b0 = B + n0;
 
-  // PF sets of registers: each is filled PF steps before it is staged.  PF 0:
-  // A's values of two steps are loaded together, the second step's a step
-  // earlier than need be.
-  constexpr int SA = PF ? PF : 2, SB = PF ? PF : 1;
-  float ra[SA][G::AU][U], rb[SB][G::BU][U];
-  auto load_unit = [&](int k0, int i, float (&ra)[G::AU][U]) {
+  // PF sets of registers: each is filled PF steps before it is staged
+  float ra[PF][G::AU][U], rb[PF][G::BU][U];
+  auto load_a = [&](int k0, float (&ra)[G::AU][U]) {
     const rsrc_t rs = make_rsrc(a0 + k0);
 #pragma unroll
-    for (int j = 0; j < U; j += 4) {
-      if constexpr (!WIDE) {
-        const u32x4 v = buffer_load16(rs, pa[i] + 4 * j, 0);
+    for (int i = 0; i < G::AU; ++i)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) ra[i][j + t] = __uint_as_float(v[t]);
-      } else {
+      for (int j = 0; j < U; j += 4) {
+        if constexpr (!WIDE) {
+          const u32x4 v = buffer_load16(rs, pa[i] + 4 * j, 0);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-          ra[i][j + t] = A[(size_t)ra_row[i] * K + k0 + ka[i] + j + t];
+          for (int t = 0; t < 4; ++t) ra[i][j + t] = __uint_as_float(v[t]);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            ra[i][j + t] = A[(size_t)ra_row[i] * K + k0 + ka[i] + j + t];
+        }
       }
-    }
-  };
-  auto load_a = [&](int k0, float (&ra)[G::AU][U]) {
-#pragma unroll
-    for (int i = 0; i < G::AU; ++i) load_unit(k0, i, ra);
-  };
-  auto load_a2 = [&](int k0, int k1) {   // unit by unit: both halves of a row's line
-#pragma unroll
-    for (int i = 0; i < G::AU; ++i) {
-      load_unit(k0, i, ra[0]);
-      load_unit(k1, i, ra[SA - 1]);
-    }
   };
   auto load_b = [&](int k0, float (&rb)[G::BU][U]) {
     const rsrc_t rs = make_rsrc(b0 + (size_t)k0 * N);
@@ -321,10 +310,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS,
   // K value where step i starts; past the end the last one again, never used
   auto at = [&](int i) { return first + (min(i, nk - 1) - 1) * BKT; };
   if (nk > 1) {
-    if constexpr (PF == 0) load_a2(at(1), at(2));
 #pragma unroll
-    for (int i = 0; i < SB; ++i) {
-      if constexpr (PF != 0) load_a(at(i + 1), ra[i]);
+    for (int i = 0; i < PF; ++i) {
+      load_a(at(i + 1), ra[i]);
       load_b(at(i + 1), rb[i]);
     }
   }
@@ -337,11 +325,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS,
 #pragma unroll
     for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
   __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
-  auto step = [&](float (&ra)[G::AU][U], float (&rb)[G::BU][U], int k2, auto refill_a) {
+  auto step = [&](int kt, float (&ra)[G::AU][U], float (&rb)[G::BU][U]) {
     flip();
+    const int k2 = at(kt + 1 + PF);
     mul(1, 1, as);
     store_a(ra);
-    refill_a();
+    load_a(k2, ra);
     interleave<KH * TM * TN, (6 * U * G::AU + KH * TM * TN - 1) / (KH * TM * TN)>();
     mul(1, 0, as);
     store_b(rb);
@@ -361,22 +350,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS,
     frag(0);
     __builtin_amdgcn_sched_barrier(0);
   };
-  if constexpr (PF == 0) {
 #pragma clang loop unroll(disable)
-    for (int kt = 0; kt + 2 < nk; kt += 2) {
-      step(ra[0], rb[0], at(kt + 2), [] {});
-      step(ra[1], rb[0], at(kt + 3), [&] { load_a2(at(kt + 3), at(kt + 4)); });
-    }
-    if ((nk & 1) == 0) step(ra[0], rb[0], at(nk), [] {});
-  } else {
-#pragma clang loop unroll(disable)
-    for (int kt = 0; kt + 1 < nk;) {
+  for (int kt = 0; kt + 1 < nk;) {
 #pragma unroll
-      for (int i = 0; i < PF; ++i) {
-        const int k2 = at(kt + 1 + PF);
-        step(ra[i], rb[i], k2, [&] { load_a(k2, ra[i]); });
-        if (++kt + 1 >= nk) break;
-      }
+    for (int i = 0; i < PF; ++i) {
+      step(kt, ra[i], rb[i]);
+      if (++kt + 1 >= nk) break;
     }
   }
   mul(1, 1, as);
@@ -511,18 +490,18 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
   const bool wide = K >= (1 << 22) || N >= (1 << 22);
   switch (choose(M, N, K, variant)) {
     case kBig:
-      // one 128 x 256 tile in the place of a CU's two of 128 x 128, where
+      // one 256 x 128 tile in the place of a CU's two of 128 x 128, where
       // they fill the CUs and leave no more of the last round idle (4096^3,
-      // 512 / 1024 tiles: 625 against 661 us; 2048x4096x2048, 256 / 512: 160
-      // against 173; 3000x3001x1000, 288 / 576: 142 against 118)
-      return tiles(M, N, 128, 256) >= 256 &&
-                     2 * rounds(tiles(M, N, 128, 256)) <= rounds(tiles(M, N, 128, 128))
-                 ? plan<2, 4, 2, 2, 1, 16, 4, 0>(M, N, wide)
+      // 512 / 1024 tiles: 640 against 661 us; 2048x4096x2048, 256 / 512: 166
+      // against 173; 3000x3001x1000, 288 / 576: 148 against 118)
+      return tiles(M, N, 256, 128) >= 256 &&
+                     2 * rounds(tiles(M, N, 256, 128)) <= rounds(tiles(M, N, 128, 128))
+                 ? plan<4, 2, 2, 2, 1, 16, 4, 1>(M, N, wide)
                  : plan<2, 4, 2, 1, 1, 16, 4, 1>(M, N, wide);
     case kMid:
       // one tile a CU at most: eight more waves pay once K is long
       // (4096x256x4096 71 -> 62 us, 1024^3 18.8 -> 18.3, K = 256 7.2 -> 7.6)
-      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4, 4>(M, N, wide)
+      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4, 3>(M, N, wide)
                                                      : plan<2, 2, 1, 1, 2, 16, 4, 4>(M, N, wide);
     default:
       // the same for 32 x 32 (256x256x2048 19.7 -> 16.3 us, 512^3 7.6 -> 7.1;

@@ -125,14 +125,14 @@ def test_conv_tiny_values(n, c, h, w):
     assert np.all(np.abs(Y - ref) <= 9 * c * 2.0 ** -23 * scale)
 
 
-# 128 x 256 tiles, A loaded for two steps of 16 at a time: odd and even numbers
-# of steps, one to five, the first of them whole or not; edges of both sides
-@pytest.mark.parametrize("M,N,K", [(1930, 3900, 1), (1930, 3900, 16), (2048, 4096, 17),
-                                   (1930, 3900, 33), (2047, 4095, 48), (1930, 3900, 64),
-                                   (1930, 3900, 65)])
+# 256 x 128 tiles: odd and even numbers of steps of 16, one to five, the first
+# of them whole or not; edges of both sides
+@pytest.mark.parametrize("M,N,K", [(3900, 1930, 1), (3900, 1930, 16), (4096, 2048, 17),
+                                   (3900, 1930, 33), (4095, 2047, 48), (3900, 1930, 64),
+                                   (3900, 1930, 65)])
 def test_gemm_error_wide_tiles(M, N, K):
     test_gemm_error(M, N, K)
 
 
 def test_gemm_values_without_a_split_wide_tiles():
-    test_gemm_values_without_a_split(1930, 3900, 40)
+    test_gemm_values_without_a_split(3900, 1930, 40)
