@@ -46,7 +46,7 @@
 // is a chain of steps whose latency (barrier, LDS, loads) K slices divide.
 // us per launch, 256 x 256 only -> now: BF16 4096^3 122 -> 117, 2048^3 47 -> 24,
 // 1280x1792x768 22 -> 9.2, 1024^3 25 -> 6.5, 512^3 16 -> 4.1, 256x256x2048
-// 42 -> 5.9; BF16 convolution C = 256, 256^2 88 -> 84, C = 128, 128^2 45 -> 17,
+// 42 -> 5.9; BF16 convolution C = 256, 256^2 88, C = 128, 128^2 45 -> 17,
 // C = 64, 128^2 26 -> 8.6, C = 256, 32^2 80 -> 8.9; FP8 2048x8192x8192
 // 122 -> 115, 2048^3 27 -> 14, 1024^3 15 -> 4.9.
 #include "mfma.hpp"
@@ -252,9 +252,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
 #pragma unroll
     for (int j = 0; j < TN; ++j) b[j] = frag(base, BM + (wn * TN + j) * 32);
   };
-  auto multiply = [&](const i32x8 (&a)[TM], const i32x8 (&b)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
+  auto multiply_row = [&](int i, const i32x8 (&a)[TM], const i32x8 (&b)[TN]) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         if constexpr (T == kRingFp8) {
@@ -270,6 +268,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
           }
         }
       }
+  };
+  auto multiply = [&](const i32x8 (&a)[TM], const i32x8 (&b)[TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) multiply_row(i, a, b);
   };
   // Step s: wait until stage s+1 is in LDS for every wave (this wave's loads
   // but the NST - 2 latest stages, then the barrier) and this wave's reads of
@@ -294,16 +296,28 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     ring_wait_loads<2 * CPT>();
     asm volatile("s_barrier" ::: "memory");
     read(0, a0, b0);
+    // row by row, so that one set of A's fragments is enough: a row's is read
+    // again for the next step once its products are issued (256 x 256: 214
+    // registers, 240 with two sets; 216 fit beside a wave of the tail executor)
+    auto half = [&](int next, const i32x8 (&b)[TN], i32x8 (&bn)[TN]) {
+      const unsigned char* base = lds + (next % NST) * R::STAGE;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bn[j] = frag(base, BM + (wn * TN + j) * 32);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        multiply_row(i, a0, b);
+        __builtin_amdgcn_sched_barrier(0);
+        a0[i] = frag(base, (wm * TM + i) * 32);
+      }
+    };
     for (int s = 0; s < mine; s += 2) {
-      read(s + 1, a1, b1);
-      multiply(a0, b0);
+      half(s + 1, b0, b1);
       // stages s, s + 1 are in registers in every wave, s + 2 and s + 3 in LDS
       ring_wait_loads<0>();
       __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
       asm volatile("s_barrier" ::: "memory");
       issue2(s + 4);
-      read(s + 2, a0, b0);
-      if (s + 1 < mine) multiply(a1, b1);
+      if (s + 1 < mine) half(s + 2, b1, b0);
     }
   } else {
     for (int s = 0; s < NST; ++s) issue(s);
@@ -399,17 +413,20 @@ int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm)
 // Stages in pairs where workgroups enough hide the shorter lead (us single ->
 // pairs): 256 x 256 from 192 workgroups (4096^3 121.5 -> 117, FP8
 // 2048x8192x8192 122 -> 115; 3072x3072x2048, 144: 47.8 -> 50.1), 128 x 128 from
-// two a CU (2304x3072x768 19.5 -> 18.4, FP8 2048x4096x4096 44 -> 37.5; 2048^3,
-// 256: 23.3 -> 26.6), both always for convolutions (C = 256, 256^2 88 -> 84),
-// 64 x 64 always (1024x2048x1024 9.5 -> 8.7).
+// two a CU (2304x3072x768 19.5 -> 17.9, FP8 2048x4096x4096 44 -> 37.8; 2048^3,
+// 256: 23.3 -> 26.6) and for convolutions (C = 256, 128^2 40.4 -> 38), 64 x 64
+// always (1024x2048x1024 9.5 -> 8.5).  (256 x 256 for a convolution would need
+// 224 registers.)
 template <int T, bool CONV, bool RAGGED>
 Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
   const int64_t steps = (kb + RK - 1) / RK;
   const int64_t t256 = tiles(M, N, 256, 256), t128 = tiles(M, N, 128, 128);
   const int64_t t64 = tiles(M, N, 64, 64), t32 = tiles(M, N, 32, 32);
-  if (t256 >= 144 && 3 * t256 <= t128)
-    return CONV || t256 >= 192 ? ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4, true>()
-                               : ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
+  if (t256 >= 144 && 3 * t256 <= t128) {
+    if constexpr (!CONV)
+      if (t256 >= 192) return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4, true>();
+    return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
+  }
   if (t64 > 512 && 3 * t128 <= t64)
     return CONV || t128 > 256 ? ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4, true>()
                               : ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4>();
