@@ -19,7 +19,7 @@
 //   +7.  A 64-byte K slice (32 values) takes two of them: lane l reads 16-
 //   byte chunk l / 32 for the first and chunk 2 + l / 32 for the second.
 //
-// One kernel, gemm_ring<type, CONV, RAGGED, WM, WN, TM, TN, KS, NST>: a
+// One kernel, gemm_ring<type, RAGGED, WM, WN, TM, TN, KS, NST>: a
 // workgroup of WM x WN x KS waves computes a (WM*TM*32) x (WN*TN*32) tile,
 // each wave TM x TN products of 32 x 32 over every KS-th 64-byte K slice
 // (a step).  Global memory goes straight to LDS (global_load_lds_dwordx4)
@@ -46,9 +46,8 @@
 // is a chain of steps whose latency (barrier, LDS, loads) K slices divide.
 // us per launch, 256 x 256 only -> now: BF16 4096^3 122 -> 117, 2048^3 47 -> 24,
 // 1280x1792x768 22 -> 9.2, 1024^3 25 -> 6.5, 512^3 16 -> 4.1, 256x256x2048
-// 42 -> 5.9; BF16 convolution C = 256, 256^2 88, C = 128, 128^2 45 -> 17,
-// C = 64, 128^2 26 -> 8.6, C = 256, 32^2 80 -> 8.9; FP8 2048x8192x8192
-// 122 -> 115, 2048^3 27 -> 14, 1024^3 15 -> 4.9.
+// 42 -> 5.9; FP8 2048x8192x8192 122 -> 113, 2048^3 27 -> 14, 1024^3 15 -> 4.9.
+#include "lds_load.hpp"
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -60,8 +59,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
-// s_waitcnt lgkmcnt(0) with the vmcnt and expcnt fields at their maxima
-constexpr int kWaitLdsOnly = 15 | (3 << 14) | (7 << 4) | (0 << 8);
 
 __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* tm, int* tn) {
   const int total = tiles_m * tiles_n;
@@ -79,26 +76,7 @@ __device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* t
 constexpr int RK = 64;                       // bytes of K per step
 enum RingType { kRingFp8 = 0, kRingBf16 = 1 };
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ int ring_swz(int row) { return (row >> 2) & 3; }
-
-// s_waitcnt vmcnt(N): all but this wave's N most recent ring loads are in LDS
-template <int N>
-__device__ __forceinline__ void ring_wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
-}
-
-// One 16-byte direct-to-LDS load: lane l writes LDS bytes [lds + 16 l, +16).
-// M0 holds the wave's LDS base; one wait state between writing M0 and the
-// load that reads it.  M0 has no other use in these kernels.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void ring_load16(const unsigned char* g, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
 
 // The two 16-byte chunks of a 64-byte K slice that lane group g (= lane /
 // 32) feeds to the matrix cores.
@@ -106,12 +84,6 @@ template <int T>
 __device__ __forceinline__ int ring_chunk(int g, int h) {
   return T == kRingFp8 ? 2 * g + h : g + 2 * h;
 }
-
-__device__ __forceinline__ bf16x8 as_bf16x8(int4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-// 64 zero bytes: the K slice of a pixel outside the image (3x3 convolution),
-// the chunks past the end of a ragged row
-__device__ __attribute__((aligned(64))) unsigned char kZeroSlice[64];
 
 // Geometry of a ring workgroup: WM x WN x KS waves, each with TM x TN tiles
 // of 32 x 32 and every KS-th K step; each K slice has a ring of NST stages.
@@ -131,16 +103,11 @@ struct Ring {
 
 // Operands: A and Bt as bytes, `kb` bytes per row (a multiple of 64; of 16 if
 // RAGGED).
-// CONV (BF16 only): the 3x3 convolution as an implicit GEMM on NHWC
-// activations `Bt` ([H, W, Cc]) and OHWI weights `A` ([M, 3, 3, Cc], i.e.
-// rows of kb = 18 Cc bytes): M output channels, N = H W pixels, and K slice
-// s = (tap, 32-channel group) of a pixel row read at the pixel shifted by the
-// tap (zero slice outside the image).
-template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
+template <int T, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
           bool PAIR>
 __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     const unsigned char* __restrict__ A, const unsigned char* __restrict__ Bt,
-    float* __restrict__ C, int M, int N, int kb, int H, int W, int Cc, unsigned* sig) {
+    float* __restrict__ C, int M, int N, int kb, unsigned* sig) {
   using R = Ring<WM, WN, TM, TN, KS, NST>;
   constexpr int BM = R::BM, BN = R::BN, CPT = R::CPT;
   __shared__ __attribute__((aligned(1024))) unsigned char ring[R::LDS];
@@ -162,7 +129,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
   // ring_swz(row).  Rows past M or N read the matrix's first row (never
   // stored).
   const unsigned char* src[CPT];
-  int py[CPT], px[CPT];   // convolution: this lane's pixels
   int kcs[CPT];
   unsigned at[CPT];
 #pragma unroll
@@ -175,53 +141,28 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     const bool ok = grow < (isa ? M : N);
     const unsigned char* X = isa ? A : Bt;
     src[i] = (ok ? X + (int64_t)grow * kb : X) + 16 * kc;
-    if constexpr (CONV) {
-      // pixel rows past the image get y = -2: outside for every tap
-      py[i] = ok ? grow / W : -2;
-      px[i] = ok ? grow % W : 0;
-    }
     kcs[i] = kc;
   }
-  const int groups = CONV ? Cc / 32 : 1;   // 32-channel groups per tap
-  const unsigned inv = groups > 1 ? 0xffffffffu / groups + 1 : 0;   // x / groups = umulhi(x, inv)
   // Stages past the end re-load the last K slice into their own slot, which
   // is never read again: every step issues the same number of loads, so the
   // wait counts are constants.
-  auto loader = [&](int step) {
-    const int slot = step % NST;
-    const int sc = min(step * KS + ks, steps - 1);
-    const int k0 = sc * RK;
-    const int tap = CONV ? (groups > 1 ? (int)__umulhi(sc, inv) : sc) : 0;
-    const int grp = sc - tap * groups;
-    const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-    auto one = [=, &src, &at, &py, &px, &kcs](int i) {
-      const unsigned to = (unsigned)(uintptr_t)(lds + slot * R::STAGE) + at[i];
-      const unsigned char* g = src[i] + k0;
-      if (RAGGED && k0 + 16 * kcs[i] >= kb) g = kZeroSlice + 16 * kcs[i];
-      if constexpr (CONV) {
-        if (at[i] >= BM * RK) {   // activation rows (wave-uniform)
-          const int yy = py[i] + dy, xx = px[i] + dx;
-          g = (yy >= 0 && yy < H && xx >= 0 && xx < W)
-                  ? Bt + (((int64_t)yy * W + xx) * Cc + grp * 32) * 2 + 16 * kcs[i]
-                  : kZeroSlice + 16 * kcs[i];
-        }
-      }
-      ring_load16(g, __builtin_amdgcn_readfirstlane(to));
-    };
-    return one;
+  auto load = [&](int step, int i) {
+    const int k0 = min(step * KS + ks, steps - 1) * RK;
+    const unsigned to = (unsigned)(uintptr_t)(lds + step % NST * R::STAGE) + at[i];
+    const unsigned char* g = src[i] + k0;
+    if (RAGGED && k0 + 16 * kcs[i] >= kb) g = kZeroSlice + 16 * kcs[i];
+    load16_lds(g, __builtin_amdgcn_readfirstlane(to));
   };
   auto issue = [&](int step) {
-    auto one = loader(step);
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) one(i);
+    for (int i = 0; i < CPT; ++i) load(step, i);
   };
   // two stages, block by block: the two halves of a row's 128 bytes together
   auto issue2 = [&](int step) {
-    auto one = loader(step), two = loader(step + 1);
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
-      one(i);
-      two(i);
+      load(step, i);
+      load(step + 1, i);
     }
   };
 
@@ -280,7 +221,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
   // never used); multiply stage s.
   auto step = [&](int s, const i32x8 (&ca)[TM], const i32x8 (&cb)[TN], i32x8 (&na)[TM],
                   i32x8 (&nb)[TN]) {
-    ring_wait_loads<(NST - 2) * CPT>();
+    wait_loads<(NST - 2) * CPT>();
     __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
     asm volatile("s_barrier" ::: "memory");
     issue(s + NST);
@@ -293,7 +234,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     static_assert(NST == 4 && KS == 1, "two pairs of stages, one K slice");
     issue2(0);
     issue2(2);
-    ring_wait_loads<2 * CPT>();
+    wait_loads<2 * CPT>();
     asm volatile("s_barrier" ::: "memory");
     read(0, a0, b0);
     // row by row, so that one set of A's fragments is enough: a row's is read
@@ -313,7 +254,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     for (int s = 0; s < mine; s += 2) {
       half(s + 1, b0, b1);
       // stages s, s + 1 are in registers in every wave, s + 2 and s + 3 in LDS
-      ring_wait_loads<0>();
+      wait_loads<0>();
       __builtin_amdgcn_s_waitcnt(kWaitLdsOnly);
       asm volatile("s_barrier" ::: "memory");
       issue2(s + 4);
@@ -321,7 +262,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     }
   } else {
     for (int s = 0; s < NST; ++s) issue(s);
-    ring_wait_loads<(NST - 1) * CPT>();
+    wait_loads<(NST - 1) * CPT>();
     asm volatile("s_barrier" ::: "memory");
     read(0, a0, b0);
     for (int s = 0; s < mine; s += 2) {
@@ -330,7 +271,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
     }
   }
   // no load may still be writing LDS when the workgroup ends
-  ring_wait_loads<0>();
+  wait_loads<0>();
 
   if (KS > 1) {
     // K slices 1..KS-1 hand their sums to slice 0 through LDS, added in order
@@ -381,12 +322,12 @@ struct Launch {
   const void* func;
   int bm, bn, nt;
 };
-template <int T, bool CONV, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
+template <int T, bool RAGGED, int WM, int WN, int TM, int TN, int KS, int NST,
           bool PAIR = false>
 Launch ring() {
   using R = Ring<WM, WN, TM, TN, KS, NST>;
   return {reinterpret_cast<const void*>(
-              &gemm_ring<T, CONV, RAGGED, WM, WN, TM, TN, KS, NST, PAIR>),
+              &gemm_ring<T, RAGGED, WM, WN, TM, TN, KS, NST, PAIR>),
           R::BM, R::BN, R::NT};
 }
 
@@ -395,50 +336,36 @@ int64_t tiles(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm)
 // The tile by the number of workgroups it gives (us at either side of a line):
 // * 256 x 256 from 144 workgroups on (BF16 2560x4096x1024, 160: 30.5 against
 //   32.2 for 128 x 128; 2304x3072x768, 108: 23.9 against 19.7), unless the
-//   edges would be mostly padding (convolution of 128 channels: 48 against 32);
+//   edges would be mostly padding;
 // * 128 x 128 where 64 x 64 would take more than two rounds of 256 CUs
 //   (1280x1792x768, 560 / 140 workgroups: 9.2 against 11.4; 1024x2048x1024,
 //   512 / 128: 10.9 against 10.0), with the same exception;
 // * 32 x 32 with eight K slices for few workgroups and a long K (512x512x2048
-//   6.4 against 7.1 for 32 x 64, 512^3 4.6 against 4.1) and, a step costing
-//   more there (pixel addresses), for every convolution that small (C = 256,
-//   32^2: 8.9 against 16.7; C = 32, 32^2: 5.6 against 6.5);
+//   6.4 against 7.1 for 32 x 64, 512^3 4.6 against 4.1);
 // * 32 x 64 with two K slices up to 128 workgroups of 64 x 64 (512x1024x512
 //   4.2 against 4.7; 768x1024x512, 192: 5.2 against 4.9);
 // * 64 x 64, with two K slices where one round of CUs holds them all and K is
-//   long (1024^3 6.5 against 7.0; K = 512: equal) or, for a convolution, two
-//   rounds do (C = 160, 100^2: 20.3 against 26.0; C = 64, 256^2, 1024
-//   workgroups: 21.1 against 17.4), four for a longer one (C = 256, 64^2: 17.2
-//   against 19.7; C = 64, 128^2, 18 steps: 9.4 against 8.6).
+//   long (1024^3 6.5 against 7.0; K = 512: equal).
 // Stages in pairs where workgroups enough hide the shorter lead (us single ->
-// pairs): 256 x 256 from 192 workgroups (4096^3 121.5 -> 117, FP8
-// 2048x8192x8192 122 -> 115; 3072x3072x2048, 144: 47.8 -> 50.1), 128 x 128 from
+// pairs): 256 x 256 from 192 workgroups (4096^3 121.5 -> 118, FP8
+// 2048x8192x8192 122 -> 113; 3072x3072x2048, 144: 47.8 -> 50.1), 128 x 128 from
 // two a CU (2304x3072x768 19.5 -> 17.9, FP8 2048x4096x4096 44 -> 37.8; 2048^3,
-// 256: 23.3 -> 26.6) and for convolutions (C = 256, 128^2 40.4 -> 38), 64 x 64
-// always (1024x2048x1024 9.5 -> 8.5).  (256 x 256 for a convolution would need
-// 224 registers.)
-template <int T, bool CONV, bool RAGGED>
+// 256: 23.3 -> 26.6), 64 x 64 always (1024x2048x1024 9.5 -> 8.5).
+template <int T, bool RAGGED>
 Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
   const int64_t steps = (kb + RK - 1) / RK;
   const int64_t t256 = tiles(M, N, 256, 256), t128 = tiles(M, N, 128, 128);
   const int64_t t64 = tiles(M, N, 64, 64), t32 = tiles(M, N, 32, 32);
-  if (t256 >= 144 && 3 * t256 <= t128) {
-    if constexpr (!CONV)
-      if (t256 >= 192) return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4, true>();
-    return ring<T, CONV, RAGGED, 2, 4, 4, 2, 1, 4>();
-  }
+  if (t256 >= 144 && 3 * t256 <= t128)
+    return t256 >= 192 ? ring<T, RAGGED, 2, 4, 4, 2, 1, 4, true>()
+                       : ring<T, RAGGED, 2, 4, 4, 2, 1, 4>();
   if (t64 > 512 && 3 * t128 <= t64)
-    return CONV || t128 > 256 ? ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4, true>()
-                              : ring<T, CONV, RAGGED, 2, 4, 2, 1, 1, 4>();
-  if (t32 <= 256 && (CONV || steps >= 64)) return ring<T, CONV, RAGGED, 1, 1, 1, 1, 8, 4>();
-  if constexpr (CONV) {
-    if (t64 <= 256 && steps >= 36) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 4, 4>();
-    if (t64 <= 512) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 2, 4>();
-  } else {
-    if (t64 <= 128) return ring<T, CONV, RAGGED, 1, 2, 1, 1, 2, 4>();
-    if (t64 <= 256 && steps >= 32) return ring<T, CONV, RAGGED, 2, 2, 1, 1, 2, 4>();
-  }
-  return ring<T, CONV, RAGGED, 2, 2, 1, 1, 1, 4, true>();
+    return t128 > 256 ? ring<T, RAGGED, 2, 4, 2, 1, 1, 4, true>()
+                      : ring<T, RAGGED, 2, 4, 2, 1, 1, 4>();
+  if (t32 <= 256 && steps >= 64) return ring<T, RAGGED, 1, 1, 1, 1, 8, 4>();
+  if (t64 <= 128) return ring<T, RAGGED, 1, 2, 1, 1, 2, 4>();
+  if (t64 <= 256 && steps >= 32) return ring<T, RAGGED, 2, 2, 1, 1, 2, 4>();
+  return ring<T, RAGGED, 2, 2, 1, 1, 1, 4, true>();
 }
 
 OpPlan ring_plan(const Launch& l, int64_t M, int64_t N) {
@@ -450,41 +377,31 @@ OpPlan ring_plan(const Launch& l, int64_t M, int64_t N) {
 }
 
 hipError_t ring_launch(const OpPlan& p, const void* A, const void* Bt, float* C, int64_t M,
-                       int64_t N, int64_t kb, int64_t H, int64_t W, int64_t Cc, unsigned* sig,
-                       hipStream_t s) {
-  int m = (int)M, n = (int)N, k = (int)kb, h = (int)H, w = (int)W, c = (int)Cc;
-  void* args[] = {&A, &Bt, &C, &m, &n, &k, &h, &w, &c, &sig};
+                       int64_t N, int64_t kb, unsigned* sig, hipStream_t s) {
+  int m = (int)M, n = (int)N, k = (int)kb;
+  void* args[] = {&A, &Bt, &C, &m, &n, &k, &sig};
   return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
 }
 
 }  // namespace
 
 OpPlan gemm_fp8_plan(int64_t M, int64_t N, int64_t K) {
-  return ring_plan(K % RK == 0 ? pick_ring<kRingFp8, false, false>(M, N, K)
-                               : pick_ring<kRingFp8, false, true>(M, N, K), M, N);
+  return ring_plan(K % RK == 0 ? pick_ring<kRingFp8, false>(M, N, K)
+                               : pick_ring<kRingFp8, true>(M, N, K), M, N);
 }
 
 hipError_t gemm_fp8_launch(const unsigned char* A, const unsigned char* Bt, float* C, int64_t M,
                            int64_t N, int64_t K, hipStream_t s) {
-  return ring_launch(gemm_fp8_plan(M, N, K), A, Bt, C, M, N, K, 0, 0, 0, nullptr, s);
+  return ring_launch(gemm_fp8_plan(M, N, K), A, Bt, C, M, N, K, nullptr, s);
 }
 
 OpPlan gemm_bf16_plan(int64_t M, int64_t N, int64_t K) {
-  return ring_plan(pick_ring<kRingBf16, false, false>(M, N, 2 * K), M, N);
+  return ring_plan(pick_ring<kRingBf16, false>(M, N, 2 * K), M, N);
 }
 
 hipError_t gemm_bf16_launch(const uint16_t* A, const uint16_t* Bt, float* C, int64_t M,
                             int64_t N, int64_t K, hipStream_t s, unsigned* sig) {
-  return ring_launch(gemm_bf16_plan(M, N, K), A, Bt, C, M, N, 2 * K, 0, 0, 0, sig, s);
-}
-
-OpPlan conv3x3_bf16_plan(int64_t C, int64_t H, int64_t W) {
-  return ring_plan(pick_ring<kRingBf16, true, false>(C, H * W, 18 * C), C, H * W);
-}
-
-hipError_t conv3x3_bf16_launch(const uint16_t* X, const uint16_t* Wt, float* Y, int64_t C,
-                               int64_t H, int64_t W, hipStream_t s, unsigned* sig) {
-  return ring_launch(conv3x3_bf16_plan(C, H, W), Wt, X, Y, C, H * W, 18 * C, H, W, C, sig, s);
+  return ring_launch(gemm_bf16_plan(M, N, K), A, Bt, C, M, N, 2 * K, sig, s);
 }
 
 }  // namespace ug

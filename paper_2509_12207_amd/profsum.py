@@ -60,10 +60,11 @@ TRAFFIC_KERNELS = {
     "softmax": (r"softmax_reg<4, 4, ", 1, "paper_2509_12207_amd/csrc/kernels/pointwise.hip"),
     "voxel": (r"voxel_(init|scatter|list|cells|bin|tile_reduce|merge)", 3,
               "paper_2509_12207_amd/csrc/kernels/voxel.hip"),
-    "gemm_fp8": (r"gemm_ring<0, false,", 1,
+    "gemm_fp8": (r"gemm_ring<0,", 1,
                  "paper_2509_12207_amd/csrc/kernels/gemm_lowp.hip"),
-    "gemm_bf16": (r"gemm_ring<1, false,", 1, "paper_2509_12207_amd/csrc/kernels/gemm_lowp.hip"),
-    "conv3x3_bf16": (r"gemm_ring<1, true,", 1, "paper_2509_12207_amd/csrc/kernels/gemm_lowp.hip"),
+    "gemm_bf16": (r"gemm_ring<1,", 1, "paper_2509_12207_amd/csrc/kernels/gemm_lowp.hip"),
+    "conv3x3_bf16": (r"conv3x3_bf16_kernel", 1,
+                     "paper_2509_12207_amd/csrc/kernels/conv3x3_bf16.hip"),
 }
 
 
@@ -118,9 +119,9 @@ def traffic(fetch_dir, write_dir, roof_json, root):
 SQ_KERNELS = [("voxel bin", r"voxel_bin"), ("voxel tile_reduce", r"voxel_tile_reduce"),
               ("FP32 GEMM 4096^3", r"gemm_f32_kernel<2, 2, 2, 2, 1, true>"),
               ("FP32 conv C256 256^2", r"conv3x3_f32_kernel<2, 2, 2, 2, 1, 8, 16>"),
-              ("BF16 GEMM 4096^3", r"gemm_ring<1, false,"),
-              ("BF16 conv C256 256^2", r"gemm_ring<1, true,"),
-              ("FP8 GEMM 8192^3", r"gemm_ring<0, false,"),
+              ("BF16 GEMM 4096^3", r"gemm_ring<1,"),
+              ("BF16 conv C256 256^2", r"conv3x3_bf16_kernel"),
+              ("FP8 GEMM 8192^3", r"gemm_ring<0,"),
               ("bias+ReLU 16384^2", r"bias_relu_vec<0")]
 
 

@@ -64,3 +64,13 @@ def test_gemm_fp8_stage_pairs(M, N, K):
 @pytest.mark.parametrize("C,H,W", [(224, 193, 192)])
 def test_conv3x3_bf16_stage_pairs(C, H, W):
     test_conv3x3_bf16_tiles(C, H, W)
+
+
+# 64 channels of 16x16 pixels, 32 of 8x16, by groups of 64 channels and of 32:
+# channels that the tile does not divide, tiles cut in both directions, one
+# group and several
+@pytest.mark.parametrize("C,H,W", [(64, 310, 321), (128, 225, 230), (160, 180, 200), (64, 9, 33),
+                                   (128, 8, 16), (32, 17, 15), (96, 7, 50), (224, 31, 1),
+                                   (32, 340, 333)])
+def test_conv3x3_bf16_patches(C, H, W):
+    test_conv3x3_bf16_tiles(C, H, W)
