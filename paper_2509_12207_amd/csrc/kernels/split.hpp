@@ -61,14 +61,6 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t* h, uint32_t* 
   *lost |= lx | ly;
 }
 
-// Eight consecutive K values of a row -> the 16-byte chunk of each piece.
-__device__ __forceinline__ void split8(const float (&x)[8], uint4* p, uint32_t* lost) {
-  split2(x[0], x[1], &p[0].x, &p[1].x, &p[2].x, lost);
-  split2(x[2], x[3], &p[0].y, &p[1].y, &p[2].y, lost);
-  split2(x[4], x[5], &p[0].z, &p[1].z, &p[2].z, lost);
-  split2(x[6], x[7], &p[0].w, &p[1].w, &p[2].w, lost);
-}
-
 __device__ __forceinline__ bool finite16(f32x16 v) {
   bool ok = true;
 #pragma unroll

@@ -51,12 +51,12 @@ def _dur(r):
 
 # roofline-leg op -> (kernel-name regex, dispatches per launch, source file)
 TRAFFIC_KERNELS = {
-    "gemm": (r"gemm_f32_kernel<2, 2, 2, 2, 1, true>", 1,
+    "gemm": (r"gemm_f32_kernel<4, 2, 2, 2, 1, 16, 4, 1, false>", 1,
              "paper_2509_12207_amd/csrc/kernels/gemm_f32.hip"),
-    "conv3x3": (r"conv3x3_f32_kernel<2, 2, 2, 2, 1, 8, 16>", 1,
+    "conv3x3": (r"conv3x3_f32_rows", 1,
                 "paper_2509_12207_amd/csrc/kernels/conv3x3_f32.hip"),
     "bias_relu": (r"bias_relu_vec<0", 1, "paper_2509_12207_amd/csrc/kernels/pointwise.hip"),
-    "rowsum": (r"rowsum_block", 1, "paper_2509_12207_amd/csrc/kernels/pointwise.hip"),
+    "rowsum": (r"rowsum_rows", 1, "paper_2509_12207_amd/csrc/kernels/pointwise.hip"),
     "softmax": (r"softmax_reg<4, 4, ", 1, "paper_2509_12207_amd/csrc/kernels/pointwise.hip"),
     "voxel": (r"voxel_(init|scatter|list|cells|bin|tile_reduce|merge)", 3,
               "paper_2509_12207_amd/csrc/kernels/voxel.hip"),
@@ -117,8 +117,8 @@ def traffic(fetch_dir, write_dir, roof_json, root):
 
 
 SQ_KERNELS = [("voxel bin", r"voxel_bin"), ("voxel tile_reduce", r"voxel_tile_reduce"),
-              ("FP32 GEMM 4096^3", r"gemm_f32_kernel<2, 2, 2, 2, 1, true>"),
-              ("FP32 conv C256 256^2", r"conv3x3_f32_kernel<2, 2, 2, 2, 1, 8, 16>"),
+              ("FP32 GEMM 4096^3", r"gemm_f32_kernel<4, 2, 2, 2, 1, 16, 4, 1, false>"),
+              ("FP32 conv C256 256^2", r"conv3x3_f32_rows"),
               ("BF16 GEMM 4096^3", r"gemm_ring<1,"),
               ("BF16 conv C256 256^2", r"conv3x3_bf16_kernel"),
               ("FP8 GEMM 8192^3", r"gemm_ring<0,"),
