@@ -550,12 +550,15 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 // workgroup 1.3 us (32 x 2x16) to 2.3 us (64 x 8x16), so that a second round
 // costs more than a larger tile (C=64 128^2: 256 workgroups of 32 x 8x16 take
 // 12.1 us, 512 of 32 x 4x16 17.5, 128 of 64 x 8x16 15.4; C=128 64^2: 15.9 at
-// 32 x 4x16, 18.8 and 23.6 either side).  One chunk (C <= 16) takes one
-// buffer, four workgroups a CU and no time to speak of: the ends of the
-// kernel are what is left (128^2: 4.7 us at 32 x 4x16, 5.1 at 32 x 8x16; 336^2:
-// 14.3 and 12.6).
+// 32 x 4x16, 18.8 and 23.6 either side).  One chunk (C <= 16) takes
+// 32 x 8x16, past a round of them with one buffer, four workgroups a CU (336^2:
+// 12.7 against 18.4).  Below, where the ends of the kernel are what is left,
+// 32 x 4x16 with one buffer is faster (64^2 4.6 against 5.3 us, the FP32
+// instruction's kernel 5.7) and not taken: the first three kernels of
+// configuration 0's task, nearly all launch, then profile below the 20 us that
+// the test of its launch synchronisation has batches close at.
 int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
-  if (C <= CC) return wgs(kShapes[3], N, C, H, W) <= 256 ? 3 : 2;
+  if (C <= CC) return 2;
   const int largest = C <= 32 ? 1 : 0;
   for (int i = 4; i > largest; --i)
     if (!(i == 1 && C > 32) && wgs(kShapes[i], N, C, H, W) <= 256) return i;
@@ -579,13 +582,12 @@ int choose(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
   return variant >= 0 && variant < 5 ? variant : pick(N, C, H, W);
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB = 2>
 OpPlan plan(int64_t N, int64_t C, int64_t H, int64_t W) {
   constexpr int BM = WM * TM * 32;
   OpPlan p;
-  p.func = C <= CC && BM == 32
-               ? reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, BM == 32 ? 1 : 2>)
-               : reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, 2>);
+  p.func =
+      reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, NB>);
   p.grid = dim3((unsigned)(((H + TH - 1) / TH) * ((W + TW - 1) / TW) * N),
                 (unsigned)((C + BM - 1) / BM));
   p.block = dim3(64 * WM * WN * KS);
@@ -611,7 +613,9 @@ OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant)
       return by_rows(N, C, H, W) ? plan_rows<1, 4, 2, 1, 8, 16>(N, C, H, W)
                                  : plan<1, 4, 2, 1, 3, 8, 16>(N, C, H, W);
     case 1: return plan<1, 4, 1, 2, 3, 16, 16>(N, C, H, W);
-    case 2: return plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
+    case 2:
+      return C <= CC && wgs(kShapes[2], N, C, H, W) > 256 ? plan<1, 4, 1, 1, 3, 8, 16, 1>(N, C, H, W)
+                                                         : plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
     case 3: return plan<1, 2, 1, 1, 3, 4, 16>(N, C, H, W);
     default: return plan<1, 1, 1, 1, 9, 2, 16>(N, C, H, W);
   }
