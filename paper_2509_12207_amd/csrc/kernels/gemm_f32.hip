@@ -486,7 +486,7 @@ OpPlan plan(int64_t M, int64_t N, bool wide) {
 }  // namespace
 
 OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
-  // 32-bit offsets within a step's panels: 128 rows of K values, 128 of N
+  // 32-bit offsets within a step's panels: up to 256 rows of K values, 16 of N
   const bool wide = K >= (1 << 22) || N >= (1 << 22);
   switch (choose(M, N, K, variant)) {
     case kBig:
