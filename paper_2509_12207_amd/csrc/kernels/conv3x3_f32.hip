@@ -26,14 +26,14 @@
 //   other multiplies.
 //
 // What bounds it: at C = 256, 256^2 the matrix cores are busy about 65 % of
-// the time (MFMA alone about 270 us of 401), the rest is splitting that the
+// the time (MFMA alone about 270 us of 370), the rest is splitting that the
 // other workgroup does not cover.  The small tiles are bound by the latency
-// of a chunk (loads, split, LDS, barrier: 1.3 to 1.8 us) and by the launch.
+// of a chunk (loads, split, LDS, barrier: 0.9 to 1.6 us) and by the launch.
 // us per launch, FP32 instruction before -> now:
-//   C=256 256^2 670 -> 401, C=236 145^2 288 -> 142, C=128 128^2 52 -> 29,
-//   C=64 256^2 48 -> 33, C=256 64^2 59 -> 35, C=64 128^2 17.4 -> 12.1,
-//   C=128 64^2 20.5 -> 15.9, C=64 84^2 12.9 -> 9.8, C=32 256^2 16.2 -> 12.9,
-//   C=256 32^2 24 -> 21, C=16 64^2 5.7 -> 4.5, C=16 336^2 15.1 -> 12.6.
+//   C=256 256^2 670 -> 370, C=236 145^2 288 -> 130, C=128 128^2 52 -> 27.5,
+//   C=64 256^2 48 -> 30, C=256 64^2 59 -> 28.6, C=64 128^2 17.4 -> 10.2,
+//   C=128 64^2 20.5 -> 12.8, C=64 84^2 12.9 -> 8.2, C=32 128^2 9.0 -> 6.1,
+//   C=256 32^2 24 -> 17.3, C=16 64^2 5.8 -> 5.6, C=16 336^2 15.1 -> 11.5.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -148,17 +148,22 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   if (tid == 0) redo = 0;
 
   // Staging units.  Weights: three taps of a row (one ky) of four channels of
-  // an output channel, 4 x 12 bytes 36 bytes apart.  Patch: four channels of
-  // a pixel, consecutive threads on consecutive pixels.  Output channels past
-  // C repeat the last one (never stored).  Buffer loads, relative to the
-  // chunk: what lies past the tensor (channels past C) or has offset 2^31
-  // (pixels outside the image) reads as zero.
+  // an output channel, 4 x 12 bytes; a unit's channels are four apart, so that
+  // the twelve lanes of a row read 144 bytes in a piece (channels next to each
+  // other, with lanes 144 bytes apart, touched three times the lines: C = 256,
+  // 32^2 20.4 us against 17.5).  Patch: the same four channels of a pixel,
+  // consecutive threads on consecutive pixels.  In LDS a unit's channels are
+  // neighbours: channel 4 j + q of the chunk is at 4 q + j in both operands.
+  // Output channels past C repeat the last one (never stored).  Buffer loads:
+  // what lies past the tensor, a channel past C or a pixel outside the image
+  // (offset 2^31) reads as zero.  The resources move along by scalar
+  // additions; waves without a unit load nothing.
   uint32_t wo[Cf::WU], xo[Cf::XU];
   int wl[Cf::WU], xl[Cf::XU], xq[Cf::XU];   // LDS places; channel quad of the patch unit
 #pragma unroll
   for (int i = 0; i < Cf::WU; ++i) {
-    const int u = tid + NT * i, q = u % 4, ky = u / 4 % 3, row = u / 12;
-    wo[i] = (((uint32_t)min(row, C - 1 - o0) * C + 4 * q) * 9 + 3 * ky) * 4;
+    const int u = tid + NT * i, ky = u % 3, q = u / 3 % 4, row = u / 12;
+    wo[i] = (((uint32_t)min(row, C - 1 - o0) * C + q) * 9 + 3 * ky) * 4;
     wl[i] = row < BM ? 3 * ky * Cf::WT + (q / 2) * Cf::WH + row * 16 + (q % 2) * 8 : -1;
   }
 #pragma unroll
@@ -172,31 +177,42 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   }
 
   float rw[Cf::WU][4][3], rx[Cf::XU][4];   // the chunk staged next
-  auto load = [&](int c0) {
-    const int64_t left = ((int64_t)C * C - ((int64_t)o0 * C + c0)) * 36;   // bytes to the end
-    const auto ws = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(Wt + ((size_t)o0 * C + c0) * 9), 0,
-        (int)(uint32_t)(left < 0xffffffffll ? left : 0xffffffffll), 0x00027000);
+  // the next chunk: its weights and the bytes from them to the end, its first
+  // channel plane, the channels left
+  const float* wp = Wt + (size_t)o0 * C * 9;
+  int64_t left = ((int64_t)C * C - (int64_t)o0 * C) * 36;
+  const float* xp = Xn;
+  int cl = C;
+  auto load = [&]() {
+    const auto ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wp), 0,
+                                                      left >> 32 ? -1 : (int)left, 0x00027000);
 #pragma unroll
-    for (int i = 0; i < Cf::WU; ++i)
+    for (int i = 0; i < Cf::WU; ++i) {
+      if (BM * 12 % NT != 0 && wid * 64 + NT * i >= BM * 12) continue;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const u32x3 v = __builtin_bit_cast(
-            u32x3, __builtin_amdgcn_raw_buffer_load_b96(ws, wo[i] + 36 * j, 0, 0));
+            u32x3, __builtin_amdgcn_raw_buffer_load_b96(ws, wo[i] + 144 * j, 0, 0));
 #pragma unroll
         for (int t = 0; t < 3; ++t) rw[i][j][t] = __uint_as_float(v[t]);
       }
+    }
 #pragma unroll
     for (int i = 0; i < Cf::XU; ++i) {
-      const int c = c0 + 4 * xq[i];
-      const auto xs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float*>(Xn + (size_t)min(c, C - 1) * plane), 0,
-          (int)((uint32_t)max(0, min(C - c, 4)) * (uint32_t)plane * 4), 0x00027000);
+      if (Cf::PXP * 4 % NT != 0 && wid * 64 + NT * i >= Cf::PXP * 4) continue;
+      const float* xc = xp + (size_t)xq[i] * plane;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        rx[i][j] = __uint_as_float(
-            __builtin_amdgcn_raw_buffer_load_b32(xs, xo[i] + j * (uint32_t)plane * 4, 0, 0));
+      for (int j = 0; j < 4; ++j) {
+        const auto xs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(xc + 4 * j * plane), 0,
+            xq[i] + 4 * j < cl ? (int)((uint32_t)plane * 4) : 0, 0x00027000);
+        rx[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xs, xo[i], 0, 0));
+      }
     }
+    wp += CC * 9;
+    left -= CC * 36;
+    xp += CC * plane;
+    cl -= CC;
   };
   uint32_t lost = 0;
   auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
@@ -251,10 +267,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   };
 
   const int chunks = NB == 1 ? 1 : (C + CC - 1) / CC;
-  load(0);
+  load();
   store_w();
   store_x();
-  if (chunks > 1) load(CC);
+  if (chunks > 1) load();
   lds_barrier();
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -277,7 +293,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
       if (t == 0 && more) store_w();
       if (t == TAPS - 1 && more) {
         store_x();
-        if (ch + 2 < chunks) load((ch + 2) * CC);
+        if (ch + 2 < chunks) load();
       }
       mul(2, 0, as);
       mul(0, 2, as);
@@ -395,11 +411,15 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
     xc[i] = 8 * min(h, 1);
   }
   float rw[36], rx[Cf::XU][4];
-  auto load_w = [&](int c0) {
-    const int64_t left = ((int64_t)C * C - ((int64_t)o0 * C + c0)) * 36;   // bytes to the end
-    const auto ws = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(Wt + ((size_t)o0 * C + c0) * 9), 0,
-        (int)(uint32_t)(left < 0xffffffffll ? left : 0xffffffffll), 0x00027000);
+  // the next chunk: its weights and the bytes from them to the end; its first
+  // channel plane, the channels left
+  const float* wp = Wt + (size_t)o0 * C * 9;
+  int64_t left = ((int64_t)C * C - (int64_t)o0 * C) * 36;
+  const float* xp = Xn;
+  int cl = C;
+  auto load_w = [&]() {
+    const auto ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wp), 0,
+                                                      left >> 32 ? -1 : (int)left, 0x00027000);
 #pragma unroll
     for (int j = 0; j < 9; ++j) {
       const u32x4 v = __builtin_bit_cast(
@@ -407,19 +427,24 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
 #pragma unroll
       for (int t = 0; t < 4; ++t) rw[4 * j + t] = __uint_as_float(v[t]);
     }
+    wp += CC * 9;
+    left -= CC * 36;
   };
-  auto load_x = [&](int c0) {
+  auto load_x = [&]() {
 #pragma unroll
     for (int i = 0; i < Cf::XU; ++i) {
-      const int c = c0 + xc[i];
+      // (a scalar for the compiler: a resource in vector registers is looped over)
+      const int ch = __builtin_amdgcn_readfirstlane(max(0, min(cl - xc[i], 8)));
       const auto xs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float*>(Xn + (size_t)min(c, C - 1) * plane), 0,
-          (int)((uint32_t)max(0, min(C - c, 8)) * (uint32_t)plane * 4), 0x00027000);
+          const_cast<float*>(xp + (size_t)xc[i] * plane), 0,
+          (int)((uint32_t)ch * (uint32_t)plane * 4), 0x00027000);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         rx[i][j] = __uint_as_float(
             __builtin_amdgcn_raw_buffer_load_b32(xs, xo[i] + j * (uint32_t)plane * 4, 0, 0));
     }
+    xp += CC * plane;
+    cl -= CC;
   };
   uint32_t lost = 0;
   auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
@@ -465,12 +490,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
   };
 
   const int chunks = (C + CC - 1) / CC;
-  load_w(0);
-  load_x(0);
+  load_w();
+  load_x();
 #pragma unroll
   for (int t = 0; t < 3; ++t) store_w(t);
   store_x();
-  if (chunks > 1) load_x(CC);
+  if (chunks > 1) load_x();
   lds_barrier();
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -496,9 +521,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
         if (ky < 2 || more) store_w((3 * ky + 3) % 9 + kx);   // the next tap row
         if (ky == 2 && kx == 1 && more) {
           store_x();
-          if (ch + 2 < chunks) load_x((ch + 2) * CC);
+          if (ch + 2 < chunks) load_x();
         }
-        if (ky == 1 && kx == 2 && more) load_w((ch + 1) * CC);
+        if (ky == 1 && kx == 2 && more) load_w();
         mul(2, 0, as);
         mul(0, 2, as);
         if (kx < 2) frag(ky, kx + 1, 2);
@@ -551,12 +576,13 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 // costs more than a larger tile (C=64 128^2: 256 workgroups of 32 x 8x16 take
 // 12.1 us, 512 of 32 x 4x16 17.5, 128 of 64 x 8x16 15.4; C=128 64^2: 15.9 at
 // 32 x 4x16, 18.8 and 23.6 either side).  One chunk (C <= 16) takes
-// 32 x 8x16, past a round of them with one buffer, four workgroups a CU (336^2:
-// 12.7 against 18.4).  Below, where the ends of the kernel are what is left,
-// 32 x 4x16 with one buffer is faster (64^2 4.6 against 5.3 us, the FP32
-// instruction's kernel 5.7) and not taken: the first three kernels of
-// configuration 0's task, nearly all launch, then profile below the 20 us that
-// the test of its launch synchronisation has batches close at.
+// 32 x 8x16 on four waves, past a round of them with one buffer, so that more
+// share a CU (336^2: 11.5 us against 19.2 with two and 12.2 on twelve waves).
+// Below, where the ends of the kernel are what is left, 32 x 4x16 on six waves
+// with one buffer is faster (64^2 4.5 against 5.6, the FP32 instruction's
+// kernel 5.8) and not taken: the first three kernels of configuration 0's
+// task, nearly all launch, then profile below the 20 us that the test of its
+// launch synchronisation has batches close at.
 int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
   if (C <= CC) return 2;
   const int largest = C <= 32 ? 1 : 0;
@@ -614,8 +640,10 @@ OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant)
                                  : plan<1, 4, 2, 1, 3, 8, 16>(N, C, H, W);
     case 1: return plan<1, 4, 1, 2, 3, 16, 16>(N, C, H, W);
     case 2:
-      return C <= CC && wgs(kShapes[2], N, C, H, W) > 256 ? plan<1, 4, 1, 1, 3, 8, 16, 1>(N, C, H, W)
-                                                         : plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
+      if (C <= CC)
+        return wgs(kShapes[2], N, C, H, W) > 256 ? plan<1, 4, 1, 1, 1, 8, 16, 1>(N, C, H, W)
+                                                 : plan<1, 4, 1, 1, 1, 8, 16, 2>(N, C, H, W);
+      return plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
     case 3: return plan<1, 2, 1, 1, 3, 4, 16>(N, C, H, W);
     default: return plan<1, 1, 1, 1, 9, 2, 16>(N, C, H, W);
   }

@@ -79,7 +79,7 @@ def test_gemm_tiny_values(lo):
 
 # ------------------------------------------------------------- convolution
 # 64 x 8x16 by tap rows and at once, 32 x 16x16, 32 x 8x16, 32 x 4x16 and
-# 32 x 2x16 with two buffers; one chunk of channels at 32 x 4x16 and 32 x 8x16
+# 32 x 2x16; one chunk of channels, with two buffers and with one
 CONV = [(1, 64, 250, 250), (1, 130, 70, 90), (1, 30, 250, 260), (1, 40, 100, 140), (1, 40, 60, 80),
         (1, 100, 33, 47), (3, 17, 5, 16), (2, 16, 40, 50), (1, 3, 13, 21), (1, 7, 200, 199)]
 
