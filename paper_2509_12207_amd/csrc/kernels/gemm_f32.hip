@@ -9,7 +9,8 @@
 // (WM*TM*32) x (WN*TN*32); its waves form a WM x WN x KS grid; each wave owns
 // TM x TN tiles of 32 x 32 and one of KS slices (BK values) of every K step;
 // operands are staged in units of U K values.
-//   big   <2,4,2,1,1,16,4>: 128 x 128 tiles, eight waves of 64 x 32, or
+//   big   <2,4,2,1,1,16,4>: 128 x 128 tiles, eight waves of 64 x 32,
+//         <2,2,2,2,2,16,4>: the same in waves of 64 x 64, K split two ways, or
 //         <4,2,2,2,1,16,4>: 256 x 128 tiles, eight waves of 64 x 64;
 //   mid   <2,2,1,1,2,16,4> or, where K is long and no CU has more than one
 //         tile, <2,2,1,1,4,16,4>: 64 x 64, K split two or four ways;
@@ -27,8 +28,8 @@
 // 670) and the K splits.  One tile of 256 x 128 loads and splits a quarter
 // less than two of 128 x 128 (4096^3: 661 -> 640 us).
 // us per launch, FP32 instruction before -> now:
-//   4096^3 1170 -> 640, 2048^3 170 -> 95, 1280x2048x1024 65 -> 42,
-//   1003x2050x1021 102 -> 43, 1024^3 33 -> 18.3, 768x1280x256 11.1 -> 7.2,
+//   4096^3 1170 -> 616, 2048^3 170 -> 87, 1280x2048x1024 65 -> 42,
+//   1003x2050x1021 102 -> 41, 1024^3 33 -> 18.3, 768x1280x256 11.1 -> 7.2,
 //   512^3 8.8 -> 7.1, 256x256x2048 26 -> 16, 256^3 5.8 -> 5.2.
 //
 // The pipeline of a step: while the products of the m pieces run, the next
@@ -494,9 +495,15 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
       // they fill the CUs and leave no more of the last round idle (4096^3,
       // 512 / 1024 tiles: 640 against 661 us; 2048x4096x2048, 256 / 512: 166
       // against 173; 3000x3001x1000, 288 / 576: 148 against 118)
-      return tiles(M, N, 256, 128) >= 256 &&
-                     2 * rounds(tiles(M, N, 256, 128)) <= rounds(tiles(M, N, 128, 128))
-                 ? plan<4, 2, 2, 2, 1, 16, 4, 1>(M, N, wide)
+      if (tiles(M, N, 256, 128) >= 256 &&
+          2 * rounds(tiles(M, N, 256, 128)) <= rounds(tiles(M, N, 128, 128)))
+        return plan<4, 2, 2, 2, 1, 16, 4, 1>(M, N, wide);
+      // one tile a CU at most and K long: waves of 64 x 64, a third fewer LDS
+      // reads a product, and K in two slices so that there are eight of them
+      // (2048^3 90.6 -> 87.0 us, 1500^3 59.9 -> 56.9, 1280x2048x1024 42.9 -> 41.8;
+      // K = 512 24.0 -> 25.0, K = 256 15.0 -> 16.7)
+      return K >= 1000 && tiles(M, N, 128, 128) <= 256
+                 ? plan<2, 2, 2, 2, 2, 16, 4, 1>(M, N, wide)
                  : plan<2, 4, 2, 1, 1, 16, 4, 1>(M, N, wide);
     case kMid:
       // one tile a CU at most: eight more waves pay once K is long

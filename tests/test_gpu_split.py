@@ -136,3 +136,15 @@ def test_gemm_error_wide_tiles(M, N, K):
 
 def test_gemm_values_without_a_split_wide_tiles():
     test_gemm_values_without_a_split(3900, 1930, 40)
+
+
+# 128 x 128 tiles with K in two slices of 16: K a multiple of their step and
+# not, one slice short of its last step, edges of both sides
+@pytest.mark.parametrize("M,N,K", [(1500, 1700, 1000), (1537, 1665, 1024), (1530, 1690, 1037),
+                                   (700, 2800, 1010)])
+def test_gemm_error_two_slices(M, N, K):
+    test_gemm_error(M, N, K)
+
+
+def test_gemm_values_without_a_split_two_slices():
+    test_gemm_values_without_a_split(1500, 1700, 1005)
