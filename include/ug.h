@@ -791,7 +791,7 @@ ug_status ug_launch_cost(const ug_kernel* k, void* const* buffers, uint32_t n_bu
                          uint32_t n, void* hip_stream, int64_t* host_ns, int64_t* gpu_ns);
 
 /* Tile variants (the autotuner of configuration 2).  The FP32 GEMM has 3
- * tile shapes (0: 128x128, 1: 64x64 with a K split of two or four, 2: 32x32
+ * tile shapes (0: 128x128 or 256x128, 1: 64x64 with a K split of two or four, 2: 32x32
  * with a K split of four or eight) and the FP32 3x3 convolution 5 (output
  * channels x pixel patch, 0: 64 x 8x16, 1: 32 x 16x16, 2: 32 x 8x16,
  * 3: 32 x 4x16, 4: 32 x 2x16); each launcher picks one by a fixed rule unless the process-wide
