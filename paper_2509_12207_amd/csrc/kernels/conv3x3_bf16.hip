@@ -10,20 +10,22 @@
 // with the 16 bytes k = 8 (l / 32) .. +7).
 //
 // LDS rows (a pixel, or a weight row of one tap) are CG values; their 16-byte
-// chunks are XOR-permuted by the row so that a read of one chunk by sixteen
-// consecutive rows, which is what a fragment's half is whatever the tap,
-// touches all 64 LDS banks once.  Groups are 64 channels, whole 128-byte
-// lines, unless C is not a multiple of 64.
+// chunks are XOR-permuted, by the row for weights and by the column for
+// pixels, so that a fragment's read of one chunk of 32 weight rows, or of 16
+// pixels of two rows of the tile, whatever the tap, touches every LDS bank
+// equally (permuted by the pixel's place in the patch, whose rows are 18
+// apart, two lanes of sixteen met in a bank: 2 to 6 % slower).  Groups are 64
+// channels, whole 128-byte lines, unless C is not a multiple of 64.
 //
 // What bounds it: read tap by tap, as the product of a matrix that holds
 // every pixel nine times, the convolution was bound by the rate at which
 // stages reach LDS; with patches a large one is bound by the matrix cores
-// (C = 256, 256^2: 1.10 PFLOP/s), a mid one by LDS reads (a wave reads 16 bytes
+// (C = 256, 256^2: 1.15 PFLOP/s), a mid one by LDS reads (a wave reads 16 bytes
 // for every product row and column it has), a small one by the latency of its
 // 27 stages a 64 channels.  us per launch, tap by tap -> now: C = 256, 256^2
-// 88 -> 70, 128^2 38 -> 24, 64^2 17 -> 9.4, 32^2 8.5 -> 8.6; C = 128, 256^2 30 -> 24,
-// 128^2 17.4 -> 8.5, 32^2 6.9 -> 5.8; C = 64, 336^2 25 -> 15.6, 128^2 8.6 -> 4.9;
-// C = 96, 160^2 17.7 -> 9.3; C = 32, 336^2 17 -> 7.2, 64^2 5.6 -> 3.7.
+// 88 -> 67.4, 128^2 38 -> 22.7, 64^2 17 -> 9.0, 32^2 8.5 -> 8.6; C = 128, 256^2
+// 30 -> 21.6, 128^2 17.4 -> 8.1, 64^2 11.4 -> 5.8; C = 64, 336^2 25 -> 14.3, 128^2
+// 8.6 -> 4.7; C = 96, 160^2 17.7 -> 8.9; C = 32, 336^2 17 -> 7.1, 64^2 5.6 -> 3.7.
 // (A second patch buffer, filled during the group before: 1 to 15 % slower,
 // for the workgroups a CU that it takes.)
 #include "lds_load.hpp"
@@ -40,7 +42,8 @@ template <int WM, int WN, int TM, int TN, int TH, int TW, int CG, int TS, int NS
 struct Patch {
   static constexpr int BM = WM * TM * 32, WAVES = WM * WN, NT = 64 * WAVES;
   static constexpr int ROWB = 2 * CG, CH = CG / 8;             // bytes, chunks of an LDS row
-  static constexpr int PW = TW + 2, PP = (TH + 2) * PW;        // the patch's pixels
+  static constexpr int PW = CG == 64 ? TW + 2 : TW + 4;        // the patch's pixels, two unused
+  static constexpr int PP = (TH + 2) * PW;                     //   where a row has to be 4 n
   static constexpr int PB = (PP * ROWB + 1023) / 1024;         // its 1 KiB blocks, a wave's load each
   static constexpr int PPT = (PB + WAVES - 1) / WAVES;         // loads per wave
   static constexpr int STAGE = TS * BM * ROWB, WB = STAGE / 1024, WPT = (WB + WAVES - 1) / WAVES;
@@ -50,7 +53,8 @@ struct Patch {
   static_assert((NST - 1) * WPT < 64, "the wait counts fit vmcnt");
 };
 
-// permutation of the chunks of LDS row `row`
+// permutation of the chunks of weight row `row`, of a pixel in column `row` of
+// the patch
 template <int CG>
 __device__ __forceinline__ int patch_swz(int row) {
   return CG == 64 ? (row >> 1) & 7 : (row >> 2) & 3;
@@ -105,11 +109,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_bf16_kernel(
     for (int i = 0; i < P::PPT; ++i) {
       const int b = min(i * P::WAVES + wave, P::PB - 1);
       const int p = (b * 64 + lane) / P::CH, py = p / P::PW;
-      const int y = y0 + py - 1, x = x0 + p - py * P::PW - 1;
+      const int px = p - py * P::PW, y = y0 + py - 1, x = x0 + px - 1;
       const bool in = p < P::PP && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
       const unsigned char* from =
           in ? X + (((size_t)y * W + x) * C + (size_t)g * CG) * 2 +
-                   16 * (lane % P::CH ^ patch_swz<CG>(p))
+                   16 * (lane % P::CH ^ patch_swz<CG>(px))
              : kZeroSlice;
       load16_lds(from, __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds + b * 1024));
     }
@@ -163,8 +167,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_bf16_kernel(
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const int p = pix[j] + tap / 3 * P::PW + tap % 3;
+          const int px = ((wn * TN + j) * 32 + col) % TW + tap % 3;
           b[j] = *reinterpret_cast<const int4*>(lds + p * P::ROWB +
-                                                16 * ((2 * k + half) ^ patch_swz<CG>(p)));
+                                                16 * ((2 * k + half) ^ patch_swz<CG>(px)));
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
