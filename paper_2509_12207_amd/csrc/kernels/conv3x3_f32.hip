@@ -31,9 +31,9 @@
 // of a chunk (loads, split, LDS, barrier: 0.9 to 1.6 us) and by the launch.
 // us per launch, FP32 instruction before -> now:
 //   C=256 256^2 670 -> 370, C=236 145^2 288 -> 130, C=128 128^2 52 -> 27.5,
-//   C=64 256^2 48 -> 30, C=256 64^2 59 -> 28.6, C=64 128^2 17.4 -> 10.2,
+//   C=64 256^2 48 -> 30, C=256 64^2 59 -> 28.3, C=64 128^2 17.4 -> 9.5,
 //   C=128 64^2 20.5 -> 12.8, C=64 84^2 12.9 -> 8.2, C=32 128^2 9.0 -> 6.1,
-//   C=256 32^2 24 -> 17.3, C=16 64^2 5.8 -> 5.6, C=16 336^2 15.1 -> 11.5.
+//   C=256 32^2 24 -> 16.6, C=16 64^2 5.8 -> 5.6, C=16 336^2 15.1 -> 11.5.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -68,6 +68,12 @@ struct ConvCfg {
   static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
 };
 
+// Column of pixel p of a tile: a row of the tile starts two pixels on, so that
+// the sixteen pixels of a row and those of the next, 18 apart in the patch,
+// lie in LDS banks of their own for the lanes that read them together (C = 256,
+// 32^2 17.3 -> 16.6 us, 64^2 29.4 -> 28.3; the large tiles the same).
+__device__ __forceinline__ int column(int p) { return (p - 2 * (p / 16)) & 15; }
+
 // Inputs without a split: taps t0 .. t1 - 1 of a wave's tile (output channels
 // from o, pixels from p of the patch at y0, x0) with the FP32 instruction,
 // from memory.
@@ -92,7 +98,7 @@ __device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], const float* _
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int p = p0 + j * 32 + col;
-        const int yy = y0 + p / TW + t / 3 - 1, xx = x0 + p % TW + t % 3 - 1;
+        const int yy = y0 + p / TW + t / 3 - 1, xx = x0 + column(p) + t % 3 - 1;
         y[j] = c < C && yy >= 0 && yy < H && xx >= 0 && xx < W
                    ? X[c * plane + (size_t)yy * W + xx] : 0.f;
       }
@@ -111,7 +117,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TM][TN], float* _
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int p = p0 + j * 32 + col;
-    const int yy = y0 + p / TW, xx = x0 + p % TW;
+    const int yy = y0 + p / TW, xx = x0 + column(p);
     if (yy >= H || xx >= W) continue;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -246,7 +252,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int p = (wn * TN + j) * 32 + col;
-    fb[j] = 9 * Cf::WT + half * Cf::XH + ((p / TW + ky0) * PW + p % TW + kx0) * 16;
+    fb[j] = 9 * Cf::WT + half * Cf::XH + ((p / TW + ky0) * PW + column(p) + kx0) * 16;
   }
   uint4 a[3][TM], b[3][TN];
   auto frag = [&](int t, int p) {
@@ -470,7 +476,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int p = (wn * TN + j) * 32 + col;
-    fb[j] = 2 * Cf::WS + half * Cf::XH + ((p / TW) * PW + p % TW) * 16;
+    fb[j] = 2 * Cf::WS + half * Cf::XH + ((p / TW) * PW + column(p)) * 16;
   }
   uint4 a[3][TM], b[3][TN];
   auto frag = [&](int ky, int kx, int p) {
@@ -572,10 +578,10 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 }
 
 // The smallest tile that one round of the 256 CUs holds: a chunk takes a
-// workgroup 1.3 us (32 x 2x16) to 2.3 us (64 x 8x16), so that a second round
+// workgroup 0.9 us (32 x 2x16) to 2.3 us (64 x 8x16), so that a second round
 // costs more than a larger tile (C=64 128^2: 256 workgroups of 32 x 8x16 take
-// 12.1 us, 512 of 32 x 4x16 17.5, 128 of 64 x 8x16 15.4; C=128 64^2: 15.9 at
-// 32 x 4x16, 18.8 and 23.6 either side).  One chunk (C <= 16) takes
+// 10.2 us, 512 of 32 x 4x16 14.9, 128 of 64 x 8x16 14.6; C=128 64^2: 13.0 at
+// 32 x 4x16, 14.9 and 19.3 either side).  One chunk (C <= 16) takes
 // 32 x 8x16 on four waves, past a round of them with one buffer, so that more
 // share a CU (336^2: 11.5 us against 19.2 with two and 12.2 on twelve waves).
 // Below, where the ends of the kernel are what is left, 32 x 4x16 on six waves
@@ -592,8 +598,9 @@ int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
 }
 
 // 64 x 8x16: a round of two tap-row workgroups a CU takes 1.9 times as long as
-// one of a nine-tap workgroup a CU (C=256 256^2, 2048 workgroups: 401 against
-// 419 us; C=236 145^2, 760: 152 against 142).
+// one of a nine-tap workgroup a CU (C=64 200^2, 325 workgroups: 24.5 against
+// 27.8 us; C=128 128^2, 256: 31.1 against 26.4; C=236 145^2, 760: 133 against
+// 127; C=256 256^2, 2048: 372 and 372).
 bool by_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
   const int64_t n = wgs(kShapes[0], N, C, H, W);
   return 19 * ((n + 511) / 512) < 10 * ((n + 255) / 256);
