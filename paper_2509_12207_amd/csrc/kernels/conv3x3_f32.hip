@@ -220,11 +220,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
     xp += CC * plane;
     cl -= CC;
   };
-  uint32_t lost = 0;
   auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
     uint2 p[3];
-    split2(a, b, &p[0].x, &p[1].x, &p[2].x, &lost);
-    split2(c, d, &p[0].y, &p[1].y, &p[2].y, &lost);
+    split2(a, b, &p[0].x, &p[1].x, &p[2].x);
+    split2(c, d, &p[0].y, &p[1].y, &p[2].y);
 #pragma unroll
     for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
   };
@@ -314,13 +313,14 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
     flip = -flip;
   }
 
-  bool bad = (lost & 0xffffu) != 0;
+  bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       ah[i][j] += as[i][j];
       bad = bad || !finite16(ah[i][j]);
+      ah[i][j] *= kSplitUnscale;
     }
   if (bad) redo = 1;
   __syncthreads();   // also: every read of the stages is done
@@ -452,11 +452,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
     xp += CC * plane;
     cl -= CC;
   };
-  uint32_t lost = 0;
   auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
     uint2 p[3];
-    split2(a, b, &p[0].x, &p[1].x, &p[2].x, &lost);
-    split2(c, d, &p[0].y, &p[1].y, &p[2].y, &lost);
+    split2(a, b, &p[0].x, &p[1].x, &p[2].x);
+    split2(c, d, &p[0].y, &p[1].y, &p[2].y);
 #pragma unroll
     for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
   };
@@ -545,13 +544,14 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
     xflip = -xflip;
   }
 
-  bool bad = (lost & 0xffffu) != 0;
+  bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       ah[i][j] += as[i][j];
       bad = bad || !finite16(ah[i][j]);
+      ah[i][j] *= kSplitUnscale;
     }
   if (bad) redo = 1;
   __syncthreads();

@@ -34,10 +34,10 @@
 //
 // The pipeline of a step: while the products of the m pieces run, the next
 // step's values (in registers, loaded a step ahead) are split and written to
-// the other LDS buffer, six vector instructions per value interleaved with
-// the matrix instructions; after the step's only barrier the next fragments
-// are read under the remaining products.  The barrier waits for LDS only
-// (__syncthreads would also drain the global loads).
+// the other LDS buffer, six and a half vector instructions per value
+// interleaved with the matrix instructions; after the step's only barrier the
+// next fragments are read under the remaining products.  The barrier waits for
+// LDS only (__syncthreads would also drain the global loads).
 //
 // Workgroups are dispatched round-robin over the 8 XCDs; the linear id is
 // remapped so each XCD works on a contiguous band of output tiles (sharing A
@@ -223,12 +223,11 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
         rb[i][j] = k < kn ? v : 0.f;
       }
   };
-  uint32_t lost = 0;
   auto put = [&](const float (&x)[U], unsigned char* at) {
     uint32_t p[3][U / 2];
 #pragma unroll
     for (int j = 0; j < U / 2; ++j)
-      split2(x[2 * j], x[2 * j + 1], &p[0][j], &p[1][j], &p[2][j], &lost);
+      split2(x[2 * j], x[2 * j + 1], &p[0][j], &p[1][j], &p[2][j]);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       if constexpr (U == 8)
@@ -332,11 +331,11 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
     mul(1, 1, as);
     store_a(ra);
     load_a(k2, ra);
-    interleave<KH * TM * TN, (6 * U * G::AU + KH * TM * TN - 1) / (KH * TM * TN)>();
+    interleave<KH * TM * TN, (13 * U / 2 * G::AU + KH * TM * TN - 1) / (KH * TM * TN)>();
     mul(1, 0, as);
     store_b(rb);
     load_b(k2, rb);
-    interleave<KH * TM * TN, (6 * U * G::BU + KH * TM * TN - 1) / (KH * TM * TN)>();
+    interleave<KH * TM * TN, (13 * U / 2 * G::BU + KH * TM * TN - 1) / (KH * TM * TN)>();
     mul(0, 1, as);
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
@@ -366,13 +365,14 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   mul(0, 2, as);
   mul(0, 0, ah);
 
-  bool bad = (lost & 0xffffu) != 0;
+  bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       ah[i][j] += as[i][j];
       bad = bad || !finite16(ah[i][j]);
+      ah[i][j] *= kSplitUnscale;
     }
   if (bad) redo = 1;
   __syncthreads();   // also: every read of the stages is done

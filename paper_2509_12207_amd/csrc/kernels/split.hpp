@@ -15,13 +15,19 @@
 //
 // Rate: six v_mfma_f32_32x32x16_bf16 (32 cycles each) take the place of eight
 // v_mfma_f32_32x32x2_f32 (64 cycles each): 2.67 times fewer matrix cycles.
-// The split costs six vector instructions per staged element, paid once per
-// element and workgroup tile.
+// The split costs six and a half vector instructions per staged element, paid
+// once per element and workgroup tile.
 //
-// Two kinds of input have no such split: values that are not finite (or
-// round to infinity in bfloat16), which turn every output they touch into
-// a NaN, and values below about 2^-109, whose l is not a bfloat16 value.
-// Both are noticed (the outputs; the lower halves of the l's) and the
+// Values are multiplied by 2^16 as they are split and the sums by 2^-32 at the
+// end: a multiple of 2^-149 becomes one of 2^-133, the last bit of a subnormal
+// bfloat16, so that the three pieces hold every FP32 value, subnormal ones
+// too (the matrix instruction takes subnormal operands as they are).  Without
+// the factor values below 2^-109 had none, and a tile that held one, as every
+// tile of a softmax output with a spread of 75 in its logits does, was
+// computed twice.
+//
+// What has no split is noticed by a result that is not finite: operands that
+// are infinite, NaN or 2^112 and more, and sums of 2^96 and more.  The
 // workgroup then computes its tile again with the FP32 instruction.
 #pragma once
 
@@ -47,10 +53,13 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {   // nearest e
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// Splits a pair; `lost` collects the bits of l that bfloat16 cannot hold
-// (its lower half).
-__device__ __forceinline__ void split2(float x, float y, uint32_t* h, uint32_t* m, uint32_t* l,
-                                       uint32_t* lost) {
+constexpr float kSplitScale = 0x1p16f;      // of the values split
+constexpr float kSplitUnscale = 0x1p-32f;   // of their products
+
+// Splits a pair.
+__device__ __forceinline__ void split2(float x, float y, uint32_t* h, uint32_t* m, uint32_t* l) {
+  x *= kSplitScale;
+  y *= kSplitScale;
   *h = pack_bf16(x, y);
   const float rx = x - __uint_as_float(*h << 16);
   const float ry = y - __uint_as_float(*h & 0xffff0000u);
@@ -58,7 +67,6 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t* h, uint32_t* 
   const uint32_t lx = __float_as_uint(rx - __uint_as_float(*m << 16));
   const uint32_t ly = __float_as_uint(ry - __uint_as_float(*m & 0xffff0000u));
   *l = __builtin_amdgcn_perm(ly, lx, 0x07060302u);
-  *lost |= lx | ly;
 }
 
 __device__ __forceinline__ bool finite16(f32x16 v) {
