@@ -48,6 +48,17 @@ constexpr int kXcds = 8;
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Geometry of exact_tile.
+constexpr int EC = 4;   // input channels per step
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
+struct ExactCfg {
+  static constexpr int NT = 64 * WM * WN * KS, BM = WM * TM * 32;
+  static constexpr int PW = TW + 2, PX = (TH + 2) * PW;
+  static constexpr int WR = BM + 1;                   // floats per channel and tap
+  static constexpr int WU = (BM * 9 * EC + NT - 1) / NT, XU = (PX * EC + NT - 1) / NT;
+  static constexpr int BYTES = 4 * EC * (9 * WR + PX);
+};
+
 template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB>
 struct ConvCfg {
   static constexpr int WAVES = WM * WN, NT = 64 * WAVES * KS;
@@ -66,6 +77,7 @@ struct ConvCfg {
   static constexpr int WU = (BM * 12 + NT - 1) / NT;             // weight units per thread
   static constexpr int XU = (PXP * 4 + NT - 1) / NT;             // patch units per thread
   static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
+  static_assert(LDS >= ExactCfg<WM, WN, TM, TN, KS, TH, TW>::BYTES, "unsplit values fit in LDS");
 };
 
 // Column of pixel p of a tile: a row of the tile starts two pixels on, so that
@@ -74,39 +86,80 @@ struct ConvCfg {
 // 32^2 17.3 -> 16.6 us, 64^2 29.4 -> 28.3; the large tiles the same).
 __device__ __forceinline__ int column(int p) { return (p - 2 * (p / 16)) & 15; }
 
-// Inputs without a split: taps t0 .. t1 - 1 of a wave's tile (output channels
-// from o, pixels from p of the patch at y0, x0) with the FP32 instruction,
-// from memory.
-template <int TM, int TN, int TW>
-__device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], const float* __restrict__ X,
-                                        const float* __restrict__ Wt, int C, int H, int W, int o0,
-                                        int p0, int y0, int x0, int t0, int t1) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+// A workgroup's tile with the FP32 instruction, on the values as they are
+// (inputs without a split): four input channels
+// a step, in one buffer of FP32 values (weights [channel][tap][row], patch
+// [channel][pixel]), the next step's in registers; a wave's taps are those of
+// its K slice.  The thread's index is hidden from the compiler, which would
+// otherwise keep what it has in common with the kernel's in registers
+// throughout.
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW>
+__device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], float* raw,
+                                           const float* __restrict__ X,
+                                           const float* __restrict__ Wt, int C, int H, int W, int o0,
+                                           int y0, int x0) {
+  using E = ExactCfg<WM, WN, TM, TN, KS, TH, TW>;
+  constexpr int NT = E::NT, BM = E::BM, PW = E::PW, TAPS = 9 / KS;
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));
+  const int half = tid >> 5 & 1, col = tid & 31, wave = tid >> 6;
+  const int t0 = wave / (WM * WN) * TAPS, wm = wave % (WM * WN) / WN, wn = wave % WN;
   const size_t plane = (size_t)H * W;
+  float rw[E::WU], rx[E::XU];
+  auto load = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < E::WU; ++i) {
+      const int u = tid + NT * i, o = o0 + u / (9 * EC), k = u % (9 * EC);
+      rw[i] = u < BM * 9 * EC && o < C && c0 + k / 9 < C ? Wt[((size_t)o * C + c0) * 9 + k] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < E::XU; ++i) {
+      const int u = tid + NT * i, c = u / E::PX, r = u % E::PX;
+      const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
+      rx[i] = c < EC && c0 + c < C && yy >= 0 && yy < H && xx >= 0 && xx < W
+                  ? X[(c0 + c) * plane + (size_t)yy * W + xx] : 0.f;
+    }
+  };
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
-  for (int t = t0; t < t1; ++t)
-    for (int c = half; c < C + half; c += 2) {
-      float x[TM], y[TN];
+  // the lower half of a wave takes the even channels of a step, the upper the odd ones
+  const float* w = raw + (half * 9 + t0) * E::WR + wm * TM * 32 + col;
+  const float* x[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int o = min(o0 + i * 32 + col, C - 1);
-        x[i] = c < C ? Wt[((size_t)o * C + c) * 9 + t] : 0.f;
-      }
+  for (int j = 0; j < TN; ++j) {
+    const int p = (wn * TN + j) * 32 + col;
+    x[j] = raw + EC * 9 * E::WR + half * E::PX + p / TW * PW + column(p);
+  }
+  load(0);
+#pragma clang loop unroll(disable)
+  for (int c0 = 0; c0 < C; c0 += EC) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int p = p0 + j * 32 + col;
-        const int yy = y0 + p / TW + t / 3 - 1, xx = x0 + column(p) + t % 3 - 1;
-        y[j] = c < C && yy >= 0 && yy < H && xx >= 0 && xx < W
-                   ? X[c * plane + (size_t)yy * W + xx] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_32x32x2(x[i], y[j], acc[i][j]);
+    for (int i = 0; i < E::WU; ++i) {
+      const int u = tid + NT * i;
+      if (u < BM * 9 * EC) raw[u % (9 * EC) * E::WR + u / (9 * EC)] = rw[i];
     }
+#pragma unroll
+    for (int i = 0; i < E::XU; ++i) {
+      const int u = tid + NT * i;
+      if (u < E::PX * EC) raw[EC * 9 * E::WR + u] = rx[i];
+    }
+    __syncthreads();
+    if (c0 + EC < C) load(c0 + EC);
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) {
+      const int at = (t0 + t) / 3 * PW + (t0 + t) % 3;
+#pragma unroll
+      for (int c = 0; c < EC; c += 2)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = mfma_32x32x2(w[(9 * c + t) * E::WR + i * 32], x[j][c * E::PX + at], acc[i][j]);
+    }
+    __syncthreads();   // read, and at the end free for the sums of the K slices
+  }
 }
 
 template <int TM, int TN, int TW>
@@ -325,8 +378,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   if (bad) redo = 1;
   __syncthreads();   // also: every read of the stages is done
   if (redo)
-    exact_tile<TM, TN, TW>(ah, Xn, Wt, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0, x0, ks * TAPS,
-                           (ks + 1) * TAPS);
+    exact_tile<WM, WN, TM, TN, KS, TH, TW>(ah, reinterpret_cast<float*>(lds), Xn, Wt, C, H, W, o0, y0,
+                                           x0);
 
   if (KS > 1) {
     constexpr int PER = TM * TN * 16 * 64;   // floats per wave
@@ -375,6 +428,7 @@ struct RowsCfg {
   static constexpr int XU = (PXP * 4 + NT - 1) / NT;
   static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
   static_assert(BM * 4 <= NT, "at most one weight unit a thread");
+  static_assert(LDS >= ExactCfg<WM, WN, TM, TN, 1, TH, TW>::BYTES, "unsplit values fit in LDS");
 };
 
 template <int WM, int WN, int TM, int TN, int TH, int TW>
@@ -555,7 +609,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
     }
   if (bad) redo = 1;
   __syncthreads();
-  if (redo) exact_tile<TM, TN, TW>(ah, Xn, Wt, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0, x0, 0, 9);
+  if (redo)
+    exact_tile<WM, WN, TM, TN, 1, TH, TW>(ah, reinterpret_cast<float*>(lds), Xn, Wt, C, H, W, o0, y0, x0);
   store_tile<TM, TN, TW>(ah, Y + (size_t)n * C * plane, C, H, W, o0 + wm * TM * 32, wn * TN * 32, y0,
                          x0);
   group_done(sig);

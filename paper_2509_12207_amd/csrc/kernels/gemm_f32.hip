@@ -81,8 +81,10 @@ struct GemmCfg {
   static constexpr int UPR = BKT / U;                  // units per row and step
   static constexpr int AU = BM * UPR / NT, BU = BN * UPR / NT;   // units per thread
   static constexpr int LDS = 2 * STAGE;                // bytes
+  static constexpr int RAW = BKT + 1;                  // floats per row of unsplit values
   static_assert(BK == 16 || BK == 32, "one or two matrix instructions per row");
   static_assert(BM * UPR % NT == 0 && BN * UPR % NT == 0, "even split of the units");
+  static_assert(LDS >= 4 * ROWS * RAW, "unsplit values fit in LDS");
   static_assert(KS == 1 || LDS >= (KS - 1) * 4096 * TM * TN * WM * WN, "reduction fits in LDS");
 };
 
@@ -115,6 +117,79 @@ __device__ __forceinline__ void interleave() {
     __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// A workgroup's tile with the FP32 instruction, on the values as they are
+// (inputs without a split): the same K slices, one
+// buffer of FP32 rows a step, the next step's values in registers.  The
+// thread's index is hidden from the compiler, which would otherwise keep what
+// it has in common with the kernel's in registers throughout.
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U>
+__device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], float* raw,
+                                           const float* __restrict__ A,
+                                           const float* __restrict__ B, int M, int N, int K, int m0,
+                                           int n0) {
+  using G = GemmCfg<WM, WN, TM, TN, KS, BK, U>;
+  constexpr int BM = G::BM, BN = G::BN, BKT = G::BKT, NT = G::NT, UPR = G::UPR;
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));
+  const int half = tid >> 5 & 1, col = tid & 31, wave = tid >> 6;
+  const int ks = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  float ra[G::AU][U], rb[G::BU][U];
+  auto load = [&](int64_t k0) {
+#pragma unroll
+    for (int i = 0; i < G::AU; ++i) {
+      const int u = tid + NT * i, m = min(m0 + u / UPR, M - 1);
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int64_t k = k0 + U * (u % UPR) + j;
+        ra[i][j] = k < K ? A[(size_t)m * K + k] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < G::BU; ++i) {
+      const int u = tid + NT * i, n = min(n0 + u % BN, N - 1);
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int64_t k = k0 + U * (u / BN) + j;
+        rb[i][j] = k < K ? B[(size_t)k * N + n] : 0.f;
+      }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
+  const float* x = raw + (wm * TM * 32 + col) * G::RAW + ks * BK + half;
+  const float* y = raw + (BM + wn * TN * 32 + col) * G::RAW + ks * BK + half;
+  load(0);
+#pragma clang loop unroll(disable)
+  for (int64_t k0 = 0; k0 < K; k0 += BKT) {
+#pragma unroll
+    for (int i = 0; i < G::AU; ++i)
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int u = tid + NT * i;
+        raw[u / UPR * G::RAW + U * (u % UPR) + j] = ra[i][j];
+      }
+#pragma unroll
+    for (int i = 0; i < G::BU; ++i)
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int u = tid + NT * i;
+        raw[(BM + u % BN) * G::RAW + U * (u / BN) + j] = rb[i][j];
+      }
+    __syncthreads();
+    if (k0 + BKT < K) load(k0 + BKT);
+#pragma unroll
+    for (int k = 0; k < BK; k += 2)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = mfma_32x32x2(x[i * 32 * G::RAW + k], y[j * 32 * G::RAW + k], acc[i][j]);
+    __syncthreads();   // read, and at the end free for the sums of the K slices
+  }
 }
 
 // Registers: a workgroup fits on a SIMD beside a wave of the tail executor
@@ -376,30 +451,8 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
     }
   if (bad) redo = 1;
   __syncthreads();   // also: every read of the stages is done
-  if (redo) {   // inputs without a split: the FP32 instruction, from memory
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) ah[i][j] = zero16();
-    for (int64_t k0 = ks * BK; k0 < K; k0 += BKT)
-      for (int64_t k = k0 + half; k < k0 + BK; k += 2) {
-        float x[TM], y[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int m = min(m0 + (wm * TM + i) * 32 + col, M - 1);
-          x[i] = k < K ? A[(size_t)m * K + k] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int n = min(n0 + (wn * TN + j) * 32 + col, N - 1);
-          y[j] = k < K ? B[(size_t)k * N + n] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) ah[i][j] = mfma_32x32x2(x[i], y[j], ah[i][j]);
-      }
-  }
+  if (redo)
+    exact_tile<WM, WN, TM, TN, KS, BK, U>(ah, reinterpret_cast<float*>(lds), A, B, M, N, K, m0, n0);
 
   if (KS > 1) {
     // K slices 1..KS-1 hand their partial sums to slice 0 through LDS; slice
