@@ -120,7 +120,7 @@ __device__ __forceinline__ void interleave() {
 }
 
 // A workgroup's tile with the FP32 instruction, on the values as they are
-// (inputs without a split): the same K slices, one
+// (inputs without a split, and sums too short for one): the same K slices, one
 // buffer of FP32 rows a step, the next step's values in registers.  The
 // thread's index is hidden from the compiler, which would otherwise keep what
 // it has in common with the kernel's in registers throughout.
@@ -440,7 +440,7 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   mul(0, 2, as);
   mul(0, 0, ah);
 
-  bool bad = false;
+  bool bad = K < kSplitMinTerms;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
