@@ -16,7 +16,7 @@
 // buffers: the next chunk is split, from registers loaded a chunk ahead,
 // while this one multiplies.
 //
-// Two kernels:
+// Kernels:
 // * conv3x3_f32_kernel <WM, WN, TM, TN, KS, TH, TW>: all nine taps of a chunk
 //   in LDS, the taps divided over KS groups of wavefronts (three: one tap row
 //   each; nine: one tap) and summed through LDS in a fixed order.  One
@@ -24,6 +24,7 @@
 // * conv3x3_f32_rows <WM, WN, TM, TN, TH, TW>: the weights of one tap row at
 //   a time in LDS, so that two workgroups share a CU and one splits while the
 //   other multiplies.
+// * conv3x3_f32_few: few channels, with the FP32 instruction.
 //
 // What bounds it: at C = 256, 256^2 the matrix cores are busy about 65 % of
 // the time (MFMA alone about 270 us of 370), the rest is splitting that the
@@ -86,9 +87,22 @@ struct ConvCfg {
 // 32^2 17.3 -> 16.6 us, 64^2 29.4 -> 28.3; the large tiles the same).
 __device__ __forceinline__ int column(int p) { return (p - 2 * (p / 16)) & 15; }
 
+// Image and first pixel of a workgroup's tile: each XCD takes a contiguous
+// band of them.
+template <int TH, int TW>
+__device__ __forceinline__ void pixels_of(int H, int W, int* n, int* y0, int* x0) {
+  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
+  const int xcd = blockIdx.x % kXcds;
+  const int id = xcd * (gridDim.x / kXcds) + min(xcd, (int)(gridDim.x % kXcds)) + blockIdx.x / kXcds;
+  const int pt = id % (tiles_x * tiles_y);
+  *n = id / (tiles_x * tiles_y);
+  *y0 = (pt / tiles_x) * TH;
+  *x0 = (pt % tiles_x) * TW;
+}
+
 // A workgroup's tile with the FP32 instruction, on the values as they are
-// (inputs without a split): four input channels
-// a step, in one buffer of FP32 values (weights [channel][tap][row], patch
+// (inputs without a split, and few channels): four input channels a step, in
+// one buffer of FP32 values (weights [channel][tap][row], patch
 // [channel][pixel]), the next step's in registers; a wave's taps are those of
 // its K slice.  The thread's index is hidden from the compiler, which would
 // otherwise keep what it has in common with the kernel's in registers
@@ -104,21 +118,32 @@ __device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], float* raw,
   asm("" : "+v"(tid));
   const int half = tid >> 5 & 1, col = tid & 31, wave = tid >> 6;
   const int t0 = wave / (WM * WN) * TAPS, wm = wave % (WM * WN) / WN, wn = wave % WN;
-  const size_t plane = (size_t)H * W;
+  const uint32_t plane = (uint32_t)H * W;
+  // offsets from a step's first row of weights and first channel plane (four
+  // planes of fewer than 2^26 floats); channels before which a unit is read
+  uint32_t wo[E::WU], xo[E::XU];
+  int wc[E::WU], xc[E::XU];
+#pragma unroll
+  for (int i = 0; i < E::WU; ++i) {
+    const int u = tid + NT * i, o = u / (9 * EC), k = u % (9 * EC);
+    wo[i] = (uint32_t)o * (uint32_t)(9 * C) + k;
+    wc[i] = u < BM * 9 * EC && o0 + o < C ? C - k / 9 : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < E::XU; ++i) {
+    const int u = tid + NT * i, c = u / E::PX, r = u % E::PX;
+    const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
+    xo[i] = c * plane + (uint32_t)yy * W + xx;
+    xc[i] = c < EC && yy >= 0 && yy < H && xx >= 0 && xx < W ? C - c : 0;
+  }
   float rw[E::WU], rx[E::XU];
   auto load = [&](int c0) {
+    const float* w = Wt + ((size_t)o0 * C + c0) * 9;
+    const float* x = X + (size_t)c0 * plane;
 #pragma unroll
-    for (int i = 0; i < E::WU; ++i) {
-      const int u = tid + NT * i, o = o0 + u / (9 * EC), k = u % (9 * EC);
-      rw[i] = u < BM * 9 * EC && o < C && c0 + k / 9 < C ? Wt[((size_t)o * C + c0) * 9 + k] : 0.f;
-    }
+    for (int i = 0; i < E::WU; ++i) rw[i] = c0 < wc[i] ? w[wo[i]] : 0.f;
 #pragma unroll
-    for (int i = 0; i < E::XU; ++i) {
-      const int u = tid + NT * i, c = u / E::PX, r = u % E::PX;
-      const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
-      rx[i] = c < EC && c0 + c < C && yy >= 0 && yy < H && xx >= 0 && xx < W
-                  ? X[(c0 + c) * plane + (size_t)yy * W + xx] : 0.f;
-    }
+    for (int i = 0; i < E::XU; ++i) rx[i] = c0 < xc[i] ? x[xo[i]] : 0.f;
   };
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -196,11 +221,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wid / Cf::WAVES, wave = wid % Cf::WAVES;
   const int wm = wave / WN, wn = wave % WN;
-  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
-  const int xcd = blockIdx.x % kXcds;
-  const int id = xcd * (gridDim.x / kXcds) + min(xcd, (int)(gridDim.x % kXcds)) + blockIdx.x / kXcds;
-  const int pt = id % (tiles_x * tiles_y), n = id / (tiles_x * tiles_y);
-  const int y0 = (pt / tiles_x) * TH, x0 = (pt % tiles_x) * TW;
+  int n, y0, x0;
+  pixels_of<TH, TW>(H, W, &n, &y0, &x0);
   const int o0 = blockIdx.y * BM;
   const size_t plane = (size_t)H * W;
   const float* Xn = X + (size_t)n * C * plane;
@@ -443,11 +465,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
-  const int xcd = blockIdx.x % kXcds;
-  const int id = xcd * (gridDim.x / kXcds) + min(xcd, (int)(gridDim.x % kXcds)) + blockIdx.x / kXcds;
-  const int pt = id % (tiles_x * tiles_y), n = id / (tiles_x * tiles_y);
-  const int y0 = (pt / tiles_x) * TH, x0 = (pt % tiles_x) * TW;
+  int n, y0, x0;
+  pixels_of<TH, TW>(H, W, &n, &y0, &x0);
   const int o0 = blockIdx.y * BM;
   const size_t plane = (size_t)H * W;
   const float* Xn = X + (size_t)n * C * plane;
@@ -616,6 +635,28 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
   group_done(sig);
 }
 
+// Few channels: exact_tile alone.  A chunk of the split is 16 channels, staged
+// and multiplied whole however few there are (336^2, C = 4: 10.1 us split, 7.2 so;
+// 8: 10.3 and 9.8; 12: 10.6 and, the FP32 instruction's kernel before, 12.1.  64^2,
+// C = 3 and 8: 5.3 split, 3.7 and 4.6).
+constexpr int kFew = 8;
+template <int WM, int WN, int TM, int TN, int TH, int TW>
+__global__ __launch_bounds__(64 * WM * WN) void conv3x3_f32_few(
+    const float* __restrict__ X, const float* __restrict__ Wt, float* __restrict__ Y, int C, int H,
+    int W, unsigned* sig) {
+  using E = ExactCfg<WM, WN, TM, TN, 1, TH, TW>;
+  static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
+  __shared__ float lds[E::BYTES / 4];
+  int n, y0, x0;
+  pixels_of<TH, TW>(H, W, &n, &y0, &x0);
+  const int o0 = blockIdx.y * E::BM, wave = threadIdx.x >> 6;
+  const size_t image = (size_t)n * C * H * W;
+  f32x16 acc[TM][TN];
+  exact_tile<WM, WN, TM, TN, 1, TH, TW>(acc, lds, X + image, Wt, C, H, W, o0, y0, x0);
+  store_tile<TM, TN, TW>(acc, Y + image, C, H, W, o0 + wave / WN * TM * 32, wave % WN * TN * 32, y0, x0);
+  group_done(sig);
+}
+
 // Tile shapes, largest first: {BM, TH, TW}.
 struct Shape {
   int bm, th, tw;
@@ -682,6 +723,14 @@ OpPlan plan(int64_t N, int64_t C, int64_t H, int64_t W) {
   return p;
 }
 
+OpPlan plan_few(int64_t N, int64_t C, int64_t H, int64_t W) {
+  OpPlan p;
+  p.func = reinterpret_cast<const void*>(&conv3x3_f32_few<1, 4, 1, 1, 8, 16>);
+  p.grid = dim3((unsigned)wgs(kShapes[2], N, C, H, W));   // (32 output channels: all)
+  p.block = dim3(256);
+  return p;
+}
+
 template <int WM, int WN, int TM, int TN, int TH, int TW>
 OpPlan plan_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
   constexpr int BM = WM * TM * 32;
@@ -702,6 +751,7 @@ OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant)
                                  : plan<1, 4, 2, 1, 3, 8, 16>(N, C, H, W);
     case 1: return plan<1, 4, 1, 2, 3, 16, 16>(N, C, H, W);
     case 2:
+      if (C <= kFew) return plan_few(N, C, H, W);
       if (C <= CC)
         return wgs(kShapes[2], N, C, H, W) > 256 ? plan<1, 4, 1, 1, 1, 8, 16, 1>(N, C, H, W)
                                                  : plan<1, 4, 1, 1, 1, 8, 16, 2>(N, C, H, W);
