@@ -60,7 +60,7 @@ struct ExactCfg {
   static constexpr int BYTES = 4 * EC * (9 * WR + PX);
 };
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB>
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB, int XB>
 struct ConvCfg {
   static constexpr int WAVES = WM * WN, NT = 64 * WAVES * KS;
   static constexpr int BM = WM * TM * 32;
@@ -72,9 +72,9 @@ struct ConvCfg {
   // weights keep the staging writes of a row, its channels and its tap rows
   // in different banks
   static constexpr int WH = BM * 16 + 32, WT = 6 * WH, XH = PX * 16;
-  static constexpr int STAGE = 9 * WT + 6 * XH;
+  static constexpr int WS = 9 * WT, XS = 6 * XH, X0 = NB * WS, ALL = X0 + XB * XS;
   static constexpr int RED = (KS - 1) * WAVES * TM * TN * 4096;   // sums handed over at the end
-  static constexpr int LDS = NB * STAGE > RED ? NB * STAGE : RED;
+  static constexpr int LDS = ALL > RED ? ALL : RED;
   static constexpr int WU = (BM * 12 + NT - 1) / NT;             // weight units per thread
   static constexpr int XU = (PXP * 4 + NT - 1) / NT;             // patch units per thread
   static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
@@ -207,12 +207,18 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TM][TN], float* _
   }
 }
 
-// NB: two buffers, or one where all channels are one chunk (C <= 16).
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB>
+// NB: two buffers of weights, or one where all channels are one chunk
+// (C <= 16).  XB: as many of the patch, or one, which takes a barrier more a
+// chunk (before the last tap, once every wave has read the patch for it) and
+// 17 KiB less: 64 x 8x16 then fits beside a tail-executor worker (128 KiB of LDS
+// instead of 145 of the 136 left).  The weights staged by then are complete,
+// and the next chunk's first ones are read before it starts, under the last
+// tap's products (C = 128, 128^2 26.4 us with two, 27.9 with one, 27.1 so).
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB, int XB>
 __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
     const float* __restrict__ X, const float* __restrict__ Wt, float* __restrict__ Y, int C, int H,
     int W, unsigned* sig) {
-  using Cf = ConvCfg<WM, WN, TM, TN, KS, TH, TW, NB>;
+  using Cf = ConvCfg<WM, WN, TM, TN, KS, TH, TW, NB, XB>;
   constexpr int BM = Cf::BM, PW = Cf::PW, NT = Cf::NT, TAPS = Cf::TAPS;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[Cf::LDS];
   __shared__ int redo;
@@ -253,7 +259,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
     const int q = __builtin_amdgcn_readfirstlane(u / Cf::PXP);
     const int yy = y0 - 1 + r / PW, xx = x0 - 1 + r % PW;
     xo[i] = yy >= 0 && yy < H && xx >= 0 && xx < W ? (uint32_t)((size_t)yy * W + xx) * 4 : 1u << 31;
-    xl[i] = r < Cf::PX && q < 4 ? 9 * Cf::WT + (q / 2) * Cf::XH + r * 16 + (q % 2) * 8 : -1;
+    xl[i] = r < Cf::PX && q < 4 ? Cf::X0 + (q / 2) * Cf::XH + r * 16 + (q % 2) * 8 : -1;
     xq[i] = min(q, 3);
   }
 
@@ -302,20 +308,20 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
 #pragma unroll
     for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
   };
-  int stage = 0;   // byte offset of the buffer staged into
+  int wst = 0, xst = 0;   // offsets of the buffers staged into
   auto store_w = [&]() {
 #pragma unroll
     for (int i = 0; i < Cf::WU; ++i)
       if (BM * 12 % NT == 0 || wl[i] >= 0)
 #pragma unroll
         for (int t = 0; t < 3; ++t)
-          put(rw[i][0][t], rw[i][1][t], rw[i][2][t], rw[i][3][t], lds + stage + wl[i] + t * Cf::WT,
+          put(rw[i][0][t], rw[i][1][t], rw[i][2][t], rw[i][3][t], lds + wst + wl[i] + t * Cf::WT,
               2 * Cf::WH);
   };
   auto store_x = [&]() {
 #pragma unroll
     for (int i = 0; i < Cf::XU; ++i)
-      if (xl[i] >= 0) put(rx[i][0], rx[i][1], rx[i][2], rx[i][3], lds + stage + xl[i], 2 * Cf::XH);
+      if (xl[i] >= 0) put(rx[i][0], rx[i][1], rx[i][2], rx[i][3], lds + xst + xl[i], 2 * Cf::XH);
   };
 
   // fragments of tap t of this wave: rows of output channels and of pixels
@@ -326,13 +332,16 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int p = (wn * TN + j) * 32 + col;
-    fb[j] = 9 * Cf::WT + half * Cf::XH + ((p / TW + ky0) * PW + column(p) + kx0) * 16;
+    fb[j] = Cf::X0 + half * Cf::XH + ((p / TW + ky0) * PW + column(p) + kx0) * 16;
   }
   uint4 a[3][TM], b[3][TN];
-  auto frag = [&](int t, int p) {
+  auto frag_w = [&](int t, int p, int buf) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
-      a[p][i] = *reinterpret_cast<const uint4*>(lds + fa + t * Cf::WT + p * 2 * Cf::WH + i * 512);
+      a[p][i] = *reinterpret_cast<const uint4*>(lds + fa + buf + t * Cf::WT + p * 2 * Cf::WH +
+                                                i * 512);
+  };
+  auto frag_x = [&](int t, int p) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       b[p][j] = *reinterpret_cast<const uint4*>(lds + fb[j] + ((t / 3) * PW + t % 3) * 16 +
@@ -356,36 +365,62 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) ah[i][j] = as[i][j] = zero16();
-  int flip = Cf::STAGE;
+  constexpr bool kLate = NB == 2 && XB == 1;   // the patch staged behind a barrier
+  int wflip = Cf::WS, xflip = Cf::XS;
+  // fragments of piece p for the tap after t, the next chunk's first included
+  auto next = [&](int t, int p) {
+    if (t + 1 < TAPS) {
+      frag_w(t + 1, p, 0);
+      frag_x(t + 1, p);
+    } else if (kLate) {
+      frag_w(0, p, wflip);
+    }
+  };
+  if (kLate) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) frag_w(0, p, 0);
+  }
 #pragma clang loop unroll(disable)
   for (int ch = 0; ch < chunks; ++ch) {
-    stage += flip;
+    wst += wflip;
+    if (XB == 2) xst += xflip;
     const bool more = ch + 1 < chunks;
-    frag(0, 1);
-    frag(0, 0);
-    frag(0, 2);
+    auto stage_x = [&]() {
+      store_x();
+      if (ch + 2 < chunks) load();
+    };
+    constexpr int kOrder[3] = {1, 0, 2};
+#pragma unroll
+    for (int p : kOrder) {
+      if (!kLate) frag_w(0, p, 0);
+      frag_x(0, p);
+    }
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) {
       mul(1, 1, as);
+      if (kLate && t == TAPS - 1 && more) {
+        lds_barrier();
+        stage_x();
+      }
       mul(1, 0, as);
       mul(0, 1, as);
-      if (t + 1 < TAPS) frag(t + 1, 1);
+      next(t, 1);
       if (t == 0 && more) store_w();
-      if (t == TAPS - 1 && more) {
-        store_x();
-        if (ch + 2 < chunks) load();
-      }
+      if (!kLate && t == TAPS - 1 && more) stage_x();
       mul(2, 0, as);
       mul(0, 2, as);
-      if (t + 1 < TAPS) frag(t + 1, 2);
+      next(t, 2);
       mul(0, 0, ah);
-      if (t + 1 < TAPS) frag(t + 1, 0);
+      next(t, 0);
     }
     lds_barrier();
-    fa += flip;
+    fa += wflip;
+    wflip = -wflip;
+    if (XB == 2) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[j] += flip;
-    flip = -flip;
+      for (int j = 0; j < TN; ++j) fb[j] += xflip;
+      xflip = -xflip;
+    }
   }
 
   bool bad = false;
@@ -663,7 +698,7 @@ struct Shape {
 };
 constexpr Shape kShapes[] = {
     {64, 8, 16},    // rows <1,4,2,1> or <1,4,2,1,3>
-    {32, 16, 16},   // <1,4,1,2,3>
+    {32, 16, 16},   // rows <1,8,1,1>
     {32, 8, 16},    // <1,4,1,1,3>
     {32, 4, 16},    // <1,2,1,1,3>
     {32, 2, 16},    // <1,1,1,1,9>
@@ -693,13 +728,12 @@ int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
   return largest;
 }
 
-// 64 x 8x16: a round of two tap-row workgroups a CU takes 1.9 times as long as
-// one of a nine-tap workgroup a CU (C=64 200^2, 325 workgroups: 24.5 against
-// 27.8 us; C=128 128^2, 256: 31.1 against 26.4; C=236 145^2, 760: 133 against
-// 127; C=256 256^2, 2048: 372 and 372).
+// 64 x 8x16 of nine taps where one round of the CUs holds the workgroups, by tap
+// rows past that, two to a CU (C=128 128^2, 256 workgroups: 27.1 against 30.7 us;
+// C=256 80^2, 200: 43.9 and 59.2; C=64 200^2, 325: 29.3 and 24.4; C=128 192^2, 576:
+// 75.2 and 73.7; C=236 145^2, 760: 134 and 132; C=256 256^2, 2048: 391 and 372).
 bool by_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
-  const int64_t n = wgs(kShapes[0], N, C, H, W);
-  return 19 * ((n + 511) / 512) < 10 * ((n + 255) / 256);
+  return wgs(kShapes[0], N, C, H, W) > 256;
 }
 
 // The variant asked for, else the tuning table's, else the rule above.
@@ -711,12 +745,12 @@ int choose(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
   return variant >= 0 && variant < 5 ? variant : pick(N, C, H, W);
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB = 2>
+template <int WM, int WN, int TM, int TN, int KS, int TH, int TW, int NB = 2, int XB = NB>
 OpPlan plan(int64_t N, int64_t C, int64_t H, int64_t W) {
   constexpr int BM = WM * TM * 32;
   OpPlan p;
   p.func =
-      reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, NB>);
+      reinterpret_cast<const void*>(&conv3x3_f32_kernel<WM, WN, TM, TN, KS, TH, TW, NB, XB>);
   p.grid = dim3((unsigned)(((H + TH - 1) / TH) * ((W + TW - 1) / TW) * N),
                 (unsigned)((C + BM - 1) / BM));
   p.block = dim3(64 * WM * WN * KS);
@@ -748,8 +782,8 @@ OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant)
   switch (choose(N, C, H, W, variant)) {
     case 0:
       return by_rows(N, C, H, W) ? plan_rows<1, 4, 2, 1, 8, 16>(N, C, H, W)
-                                 : plan<1, 4, 2, 1, 3, 8, 16>(N, C, H, W);
-    case 1: return plan<1, 4, 1, 2, 3, 16, 16>(N, C, H, W);
+                                 : plan<1, 4, 2, 1, 3, 8, 16, 2, 1>(N, C, H, W);
+    case 1: return plan_rows<1, 8, 1, 1, 16, 16>(N, C, H, W);
     case 2:
       if (C <= kFew) return plan_few(N, C, H, W);
       if (C <= CC)

@@ -527,14 +527,19 @@ Shape choose(int64_t M, int64_t N, int64_t K, int variant) {
   return variant >= 0 && variant < 3 ? static_cast<Shape>(variant) : pick(M, N);
 }
 
-template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF>
-OpPlan plan(int64_t M, int64_t N, bool wide) {
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, bool WIDE>
+OpPlan plan_at(int64_t M, int64_t N) {
   OpPlan p;
-  p.func = wide ? reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, true>)
-                : reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, false>);
+  p.func = reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, WIDE>);
   p.grid = dim3((unsigned)tiles(M, N, WM * TM * 32, WN * TN * 32));
   p.block = dim3(64 * WM * WN * KS);
   return p;
+}
+// PFW: sets of registers of the WIDE instance
+template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, int PFW = PF>
+OpPlan plan(int64_t M, int64_t N, bool wide) {
+  return wide ? plan_at<WM, WN, TM, TN, KS, BK, U, PFW, true>(M, N)
+              : plan_at<WM, WN, TM, TN, KS, BK, U, PF, false>(M, N);
 }
 
 }  // namespace
@@ -560,8 +565,10 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
                  : plan<2, 4, 2, 1, 1, 16, 4, 1>(M, N, wide);
     case kMid:
       // one tile a CU at most: eight more waves pay once K is long
-      // (4096x256x4096 71 -> 62 us, 1024^3 18.8 -> 18.3, K = 256 7.2 -> 7.6)
-      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4, 3>(M, N, wide)
+      // (4096x256x4096 71 -> 62 us, 1024^3 18.8 -> 18.3, K = 256 7.2 -> 7.6); with
+      // plain loads' addresses a third set of registers would not fit beside a
+      // tail-executor worker
+      return K >= 1024 && tiles(M, N, 64, 64) <= 256 ? plan<2, 2, 1, 1, 4, 16, 4, 3, 2>(M, N, wide)
                                                      : plan<2, 2, 1, 1, 2, 16, 4, 4>(M, N, wide);
     default:
       // the same for 32 x 32 (256x256x2048 19.7 -> 16.3 us, 512^3 7.6 -> 7.1;
