@@ -319,7 +319,8 @@ typedef struct {
                               one segment per core); 0 = every segment runs
                               at once (no CPU contention).  0..1024 */
   uint32_t fuse_workers;   /* with UG_F_FUSE: worker workgroups of the tail
-                              executor (1..1024, 64)                        */
+                              executor (1..1024, 64; at most one less than
+                              the device has CUs run, see ug_tails_open)    */
   int32_t pad1;
   int64_t fuse_idle_ns;    /* with UG_F_FUSE: the executor leaves after this
                               long without progress, and is launched again
@@ -722,8 +723,11 @@ typedef struct {
  * host memory and device memory (allocated here, freed by ug_tails_close).
  * idle_ns: the executor leaves after this long without progress (it is
  * launched again by ug_tails_kick).  log_cap (<= 8192): record the first
- * log_cap tiles served as (publication << 24) | tile.  Errors: UG_EINVAL,
- * UG_EDEVICE. */
+ * log_cap tiles served as (publication << 24) | tile.  workers (1..1024):
+ * with the dispatcher at most one workgroup runs a CU, 255 workers on 256
+ * CUs, so that a contraction always finds a CU with room for it (one beside
+ * which it does not fit would start only once the executor leaves).  Errors:
+ * UG_EINVAL, UG_EDEVICE. */
 ug_status ug_tails_open(int32_t device, uint32_t workers, int64_t idle_ns, uint32_t log_cap,
                         void** queue);
 /* Publishes an item with its key (smaller first; ties by slot); returns its

@@ -1,6 +1,7 @@
 // Host side of the tail executor: slots, publication, keys, relaunches.
 #include "tails.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <cstring>
 #include <set>
@@ -56,7 +57,13 @@ hipError_t TailQueue::open(int device, uint32_t workers, int64_t idle_ns, int64_
     own_stream_ = true;
   }
   if ((e = hipEventCreateWithFlags(&ev_, hipEventDisableTiming)) != hipSuccess) return e;
-  workers_ = workers;
+  // At most one workgroup of the executor a CU (with the dispatcher): every
+  // contraction fits beside one, not beside two or more, and waits for the
+  // executor to leave where no CU has room for it.
+  int cus = 0;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+  if (e != hipSuccess) return e;
+  workers_ = std::min(workers, static_cast<uint32_t>(std::max(cus - 1, 1)));
   idle_ns_ = idle_ns;
   lease_ns_ = lease_ns;
   log_cap_ = log_cap;
