@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
   int tm, tn;
   tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int steps = RAGGED ? (kb + RK - 1) / RK : kb / RK;
+  const int steps = kb / RK + (RAGGED && kb % RK != 0);
   const int mine = (steps + KS - 1) / KS;   // steps of a K slice (the last may be missing)
 
   // A stage is BM + BN rows (of A, then of Bt) of 64 bytes; load i of wave w
