@@ -722,7 +722,9 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 // launch synchronisation has batches close at.
 int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
   if (C <= CC) return 2;
-  const int largest = C <= 32 ? 1 : 0;
+  // (tap rows of 64 x 8x16 have the fewest threads, where a grid of 32 x 16x16
+  // would have more than it can: small images in millions)
+  const int largest = C <= 32 && 512 * wgs(kShapes[1], N, C, H, W) <= kMaxGridThreads ? 1 : 0;
   for (int i = 4; i > largest; --i)
     if (!(i == 1 && C > 32) && wgs(kShapes[i], N, C, H, W) <= 256) return i;
   return largest;

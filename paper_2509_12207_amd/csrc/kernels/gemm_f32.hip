@@ -210,9 +210,17 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wave / (WM * WN);
   const int wm = (wave % (WM * WN)) / WN, wn = wave % WN;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = (M - 1) / BM + 1, tiles_n = (N - 1) / BN + 1;
+  int wg = blockIdx.x;
+  if constexpr (WIDE) {   // (a grid of two sides where one would be too long)
+    wg += blockIdx.y * gridDim.x;
+    if (wg >= tiles_m * tiles_n) {
+      group_done(sig);
+      return;
+    }
+  }
   int tm, tn;
-  tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
+  tile_of(wg, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
   if (tid == 0) redo = 0;
 
@@ -531,8 +539,10 @@ template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, bool WI
 OpPlan plan_at(int64_t M, int64_t N) {
   OpPlan p;
   p.func = reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, WIDE>);
-  p.grid = dim3((unsigned)tiles(M, N, WM * TM * 32, WN * TN * 32));
   p.block = dim3(64 * WM * WN * KS);
+  const int64_t n = tiles(M, N, WM * TM * 32, WN * TN * 32);
+  const int64_t sides = n * p.block.x / kMaxGridThreads + 1;
+  p.grid = dim3((unsigned)((n + sides - 1) / sides), (unsigned)sides);
   return p;
 }
 // PFW: sets of registers of the WIDE instance
@@ -545,8 +555,9 @@ OpPlan plan(int64_t M, int64_t N, bool wide) {
 }  // namespace
 
 OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
-  // 32-bit offsets within a step's panels: up to 256 rows of K values, 16 of N
-  const bool wide = K >= (1 << 22) || N >= (1 << 22);
+  // 32-bit offsets within a step's panels: up to 256 rows of K values, 16 of N.
+  // Long columns: the grid may have a second side.
+  const bool wide = K >= (1 << 22) || N >= (1 << 22) || M >= (1 << 28);
   switch (choose(M, N, K, variant)) {
     case kBig:
       // one 256 x 128 tile in the place of a CU's two of 128 x 128, where

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 1) void gemm_ring(
   const int ks = wid / R::WAVES, wave = wid % R::WAVES;
   const int wm = wave / WN, wn = wave % WN;
   unsigned char* lds = ring + ks * NST * R::STAGE;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = (M - 1) / BM + 1, tiles_n = (N - 1) / BN + 1;
   int tm, tn;
   tile_of(blockIdx.x, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
@@ -356,7 +356,9 @@ Launch pick_ring(int64_t M, int64_t N, int64_t kb) {
   const int64_t steps = (kb + RK - 1) / RK;
   const int64_t t256 = tiles(M, N, 256, 256), t128 = tiles(M, N, 128, 128);
   const int64_t t64 = tiles(M, N, 64, 64), t32 = tiles(M, N, 32, 32);
-  if (t256 >= 144 && 3 * t256 <= t128)
+  // (past the most threads a grid holds, the tile with the fewest for its size:
+  // a narrow product of 2^30 rows or more)
+  if ((t256 >= 144 && 3 * t256 <= t128) || 256 * t64 > kMaxGridThreads)
     return t256 >= 192 ? ring<T, RAGGED, 2, 4, 4, 2, 1, 4, true>()
                        : ring<T, RAGGED, 2, 4, 4, 2, 1, 4>();
   if (t64 > 512 && 3 * t128 <= t64)

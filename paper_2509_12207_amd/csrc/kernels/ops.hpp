@@ -19,6 +19,9 @@ struct OpPlan {
   size_t lds = 0;
 };
 
+// Threads of a grid's x and y sides: what the device's dispatch packet holds.
+constexpr int64_t kMaxGridThreads = 0xffffffff;
+
 // `vec` (operands readable 16 bytes at a time) does not change the plan.
 OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool vec, int variant = -1);
 hipError_t gemm_f32_launch(const float* A, const float* B, float* C, int64_t M, int64_t N,

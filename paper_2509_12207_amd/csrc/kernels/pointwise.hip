@@ -390,7 +390,9 @@ OpPlan softmax_plan(int64_t R, bool nt) {
 
 OpPlan softmax_plan_for(int64_t R, int64_t L, bool vec) {
   const bool nt = R * L * 4 >= kStreamBytes;
-  if (!vec || L > 16384) {
+  // (four waves a row at most where eight or sixteen would be more threads than
+  // a grid holds)
+  if (!vec || L > 16384 || (L > 4096 && R * (L <= 8192 ? 512 : 1024) > kMaxGridThreads)) {
     OpPlan p;
     p.func = reinterpret_cast<const void*>(&softmax_any);
     p.grid = dim3((unsigned)R);
