@@ -32,6 +32,7 @@
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
+#include "submit.hpp"
 
 namespace ug {
 namespace {
@@ -240,7 +241,7 @@ hipError_t conv3x3_bf16_launch(const uint16_t* X, const uint16_t* Wt, float* Y, 
   const OpPlan p = conv3x3_bf16_plan(C, H, W);
   int c = (int)C, h = (int)H, w = (int)W;
   void* args[] = {&Wt, &X, &Y, &c, &h, &w, &sig};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
+  return submit(p, args, s);
 }
 
 }  // namespace ug

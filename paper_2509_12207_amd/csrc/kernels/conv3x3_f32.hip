@@ -39,6 +39,7 @@
 #include "ops.hpp"
 #include "signal.hpp"
 #include "split.hpp"
+#include "submit.hpp"
 
 namespace ug {
 namespace {
@@ -802,7 +803,7 @@ hipError_t conv3x3_f32_launch(const float* X, const float* Wt, float* Y, int64_t
   const OpPlan p = conv3x3_f32_plan(N, C, H, W, variant);
   int c = (int)C, h = (int)H, w = (int)W;
   void* args[] = {&X, &Wt, &Y, &c, &h, &w, &sig};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, p.lds, s);
+  return submit(p, args, s);
 }
 
 }  // namespace ug

@@ -48,6 +48,7 @@
 #include "ops.hpp"
 #include "signal.hpp"
 #include "split.hpp"
+#include "submit.hpp"
 
 namespace ug {
 namespace {
@@ -594,7 +595,7 @@ hipError_t gemm_f32_launch(const float* A, const float* B, float* C, int64_t M, 
   const OpPlan p = gemm_f32_plan(M, N, K, true, variant);
   int m = (int)M, n = (int)N, k = (int)K;
   void* args[] = {&A, &B, &C, &m, &n, &k, &sig};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, p.lds, s);
+  return submit(p, args, s);
 }
 
 }  // namespace ug

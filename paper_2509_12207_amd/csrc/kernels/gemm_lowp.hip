@@ -51,6 +51,7 @@
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
+#include "submit.hpp"
 
 namespace ug {
 namespace {
@@ -382,7 +383,7 @@ hipError_t ring_launch(const OpPlan& p, const void* A, const void* Bt, float* C,
                        int64_t N, int64_t kb, unsigned* sig, hipStream_t s) {
   int m = (int)M, n = (int)N, k = (int)kb;
   void* args[] = {&A, &Bt, &C, &m, &n, &k, &sig};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
+  return submit(p, args, s);
 }
 
 }  // namespace

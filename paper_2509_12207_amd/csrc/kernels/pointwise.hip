@@ -6,6 +6,7 @@
 // exchange across the waves of a workgroup), in a fixed order, so results are
 // reproducible run to run.
 #include "ops.hpp"
+#include "submit.hpp"
 
 namespace ug {
 namespace {
@@ -369,7 +370,7 @@ OpPlan rowsum_f32_plan(int64_t R, int64_t C) {
 hipError_t rowsum_f32_launch(const float* Z, float* r, int64_t R, int64_t C, hipStream_t s) {
   OpPlan p = rowsum_f32_plan(R, C);
   void* args[] = {&Z, &r, &R, &C};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
+  return submit(p, args, s);
 }
 
 namespace {
@@ -415,7 +416,7 @@ hipError_t softmax_f32_launch(const float* X, float* Y, int64_t R, int64_t L, hi
   const uintptr_t x = reinterpret_cast<uintptr_t>(X), y = reinterpret_cast<uintptr_t>(Y);
   OpPlan p = softmax_plan_for(R, L, (x & 3) == 0 && ((x ^ y) & 15) == 0);
   void* args[] = {&X, &Y, &R, &L};
-  return hipLaunchKernel(p.func, p.grid, p.block, args, 0, s);
+  return submit(p, args, s);
 }
 
 // ------------------------------------------------------------ vector add
