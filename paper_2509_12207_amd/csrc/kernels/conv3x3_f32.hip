@@ -700,7 +700,7 @@ struct Shape {
 constexpr Shape kShapes[] = {
     {64, 8, 16},    // rows <1,4,2,1> or <1,4,2,1,3>
     {32, 16, 16},   // rows <1,8,1,1>
-    {32, 8, 16},    // <1,4,1,1,3>
+    {32, 8, 16},    // <1,4,1,1,3> or rows <1,4,1,1>
     {32, 4, 16},    // <1,2,1,1,3>
     {32, 2, 16},    // <1,1,1,1,9>
 };
@@ -723,20 +723,19 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 // launch synchronisation has batches close at.
 int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
   if (C <= CC) return 2;
-  // (tap rows of 64 x 8x16 have the fewest threads, where a grid of 32 x 16x16
-  // would have more than it can: small images in millions)
-  const int largest = C <= 32 && 512 * wgs(kShapes[1], N, C, H, W) <= kMaxGridThreads ? 1 : 0;
-  for (int i = 4; i > largest; --i)
+  for (int i = 4; i > 0; --i)
     if (!(i == 1 && C > 32) && wgs(kShapes[i], N, C, H, W) <= 256) return i;
-  return largest;
+  return C <= 32 ? 2 : 0;
 }
 
-// 64 x 8x16 of nine taps where one round of the CUs holds the workgroups, by tap
-// rows past that, two to a CU (C=128 128^2, 256 workgroups: 27.1 against 30.7 us;
-// C=256 80^2, 200: 43.9 and 59.2; C=64 200^2, 325: 29.3 and 24.4; C=128 192^2, 576:
-// 75.2 and 73.7; C=236 145^2, 760: 134 and 132; C=256 256^2, 2048: 391 and 372).
-bool by_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
-  return wgs(kShapes[0], N, C, H, W) > 256;
+// Nine taps at once where one round of the CUs holds the workgroups, by tap rows
+// past that, two to a CU.  64 x 8x16: C=128 128^2, 256 workgroups: 27.1 against
+// 30.7 us; C=256 80^2, 200: 43.9 and 59.2; C=64 200^2, 325: 29.3 and 24.4; C=128
+// 192^2, 576: 75.2 and 73.7; C=236 145^2, 760: 134 and 132; C=256 256^2, 2048: 391
+// and 372.  32 x 8x16 by tap rows, against a second round of 32 x 16x16: C=20
+// 264^2, 561 workgroups: 16.6 and 18.9 us; C=32 336^2, 882: 21.1 and 21.7.
+bool by_rows(const Shape& t, int64_t N, int64_t C, int64_t H, int64_t W) {
+  return wgs(t, N, C, H, W) > 256;
 }
 
 // The variant asked for, else the tuning table's, else the rule above.
@@ -784,7 +783,7 @@ OpPlan plan_rows(int64_t N, int64_t C, int64_t H, int64_t W) {
 OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant) {
   switch (choose(N, C, H, W, variant)) {
     case 0:
-      return by_rows(N, C, H, W) ? plan_rows<1, 4, 2, 1, 8, 16>(N, C, H, W)
+      return by_rows(kShapes[0], N, C, H, W) ? plan_rows<1, 4, 2, 1, 8, 16>(N, C, H, W)
                                  : plan<1, 4, 2, 1, 3, 8, 16, 2, 1>(N, C, H, W);
     case 1: return plan_rows<1, 8, 1, 1, 16, 16>(N, C, H, W);
     case 2:
@@ -792,7 +791,8 @@ OpPlan conv3x3_f32_plan(int64_t N, int64_t C, int64_t H, int64_t W, int variant)
       if (C <= CC)
         return wgs(kShapes[2], N, C, H, W) > 256 ? plan<1, 4, 1, 1, 1, 8, 16, 1>(N, C, H, W)
                                                  : plan<1, 4, 1, 1, 1, 8, 16, 2>(N, C, H, W);
-      return plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
+      return by_rows(kShapes[2], N, C, H, W) ? plan_rows<1, 4, 1, 1, 8, 16>(N, C, H, W)
+                                             : plan<1, 4, 1, 1, 3, 8, 16>(N, C, H, W);
     case 3: return plan<1, 2, 1, 1, 3, 4, 16>(N, C, H, W);
     default: return plan<1, 1, 1, 1, 9, 2, 16>(N, C, H, W);
   }

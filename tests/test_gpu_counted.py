@@ -18,10 +18,10 @@ CASES = {
     "gemm": [(4096, 2048, 64), (1500, 1700, 1005), (1500, 1700, 65), (1024, 1024, 1024),
              (1024, 1024, 300), (96, 160, 2048), (96, 160, 264), (3, (1 << 22) + 1, 5),
              (2, 3, (1 << 22) + 5)],
-    # few channels; one chunk, one buffer and two; 32 x 2x16, 4x16, 8x16 and (tap
-    # rows) 16x16; 64 x 8x16 of nine taps and by tap rows
+    # few channels; one chunk, one buffer and two; 32 x 2x16, 4x16, 8x16 and, by tap
+    # rows, 8x16 and 16x16; 64 x 8x16 of nine taps and by tap rows
     "conv3x3": [(1, 8, 20, 20), (1, 16, 336, 336), (1, 16, 64, 64), (1, 32, 20, 16), (1, 64, 84, 84),
-                (1, 64, 128, 128), (1, 32, 256, 256), (1, 128, 128, 128), (1, 64, 200, 200)],
+                (1, 64, 128, 128), (1, 20, 264, 264), (1, 32, 256, 256), (1, 128, 128, 128), (1, 64, 200, 200)],
     # 256x256 with stages in pairs and single, 128x128 likewise, 32x32 with eight
     # K slices, 32x64 with two, 64x64 with two and in pairs
     "gemm_bf16": [(3600, 3500, 32), (3073, 3080, 64), (2300, 2310, 96), (1500, 1665, 96),
