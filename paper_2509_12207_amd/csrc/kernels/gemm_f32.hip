@@ -120,6 +120,25 @@ __device__ __forceinline__ void interleave() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Stores a wave's tile, its first row m0 and column n0.
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[TM][TN], float* __restrict__ C, int M,
+                                           int N, int m0, int n0) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + 32 * j + (lane & 31);
+      if (n >= N) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + 32 * i + mfma32_row(r, lane);
+        if (m < M) C[(size_t)m * N + n] = acc[i][j][r];
+      }
+    }
+}
+
 // A workgroup's tile with the FP32 instruction, on the values as they are
 // (inputs without a split, and sums too short for one): the same K slices, one
 // buffer of FP32 rows a step, the next step's values in registers.  The
@@ -191,6 +210,27 @@ __device__ __forceinline__ void exact_tile(f32x16 (&acc)[TM][TN], float* raw,
           acc[i][j] = mfma_32x32x2(x[i * 32 * G::RAW + k], y[j * 32 * G::RAW + k], acc[i][j]);
     __syncthreads();   // read, and at the end free for the sums of the K slices
   }
+}
+
+// Sums of too few products for the split: exact_tile alone.
+template <int WM, int WN, int TM, int TN, int BK, int U>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_f32_short(const float* __restrict__ A,
+                                                               const float* __restrict__ B,
+                                                               float* __restrict__ C, int M, int N,
+                                                               int K, unsigned* sig) {
+  using G = GemmCfg<WM, WN, TM, TN, 1, BK, U>;
+  __shared__ float raw[G::ROWS * G::RAW];
+  const int tiles_m = (M - 1) / G::BM + 1, tiles_n = (N - 1) / G::BN + 1;
+  const int wg = blockIdx.y * gridDim.x + blockIdx.x;   // (two sides where one is too long)
+  if (wg < tiles_m * tiles_n) {
+    int tm, tn;
+    tile_of(wg, tiles_m, tiles_n, &tm, &tn);
+    f32x16 acc[TM][TN];
+    exact_tile<WM, WN, TM, TN, 1, BK, U>(acc, raw, A, B, M, N, K, tm * G::BM, tn * G::BN);
+    const int wave = threadIdx.x >> 6;
+    store_tile<TM, TN>(acc, C, M, N, tm * G::BM + wave / WN * TM * 32, tn * G::BN + wave % WN * TN * 32);
+  }
+  group_done(sig);
 }
 
 // Registers: a workgroup fits on a SIMD beside a wave of the tail executor
@@ -449,7 +489,7 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   mul(0, 2, as);
   mul(0, 0, ah);
 
-  bool bad = K < kSplitMinTerms;
+  bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -494,18 +534,7 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
     }
   }
 
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn * TN * 32 + 32 * j + col;
-      if (n >= N) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * TM * 32 + 32 * i + mfma32_row(r, lane);
-        if (m < M) C[(size_t)m * N + n] = ah[i][j][r];
-      }
-    }
+  store_tile<TM, TN>(ah, C, M, N, m0 + wm * TM * 32, n0 + wn * TN * 32);
   group_done(sig);
 }
 
@@ -536,15 +565,18 @@ Shape choose(int64_t M, int64_t N, int64_t K, int variant) {
   return variant >= 0 && variant < 3 ? static_cast<Shape>(variant) : pick(M, N);
 }
 
+OpPlan plan_of(const void* func, int threads, int64_t tiles) {
+  OpPlan p;
+  p.func = func;
+  p.block = dim3(threads);
+  const int64_t sides = tiles * threads / kMaxGridThreads + 1;
+  p.grid = dim3((unsigned)((tiles + sides - 1) / sides), (unsigned)sides);
+  return p;
+}
 template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, bool WIDE>
 OpPlan plan_at(int64_t M, int64_t N) {
-  OpPlan p;
-  p.func = reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, WIDE>);
-  p.block = dim3(64 * WM * WN * KS);
-  const int64_t n = tiles(M, N, WM * TM * 32, WN * TN * 32);
-  const int64_t sides = n * p.block.x / kMaxGridThreads + 1;
-  p.grid = dim3((unsigned)((n + sides - 1) / sides), (unsigned)sides);
-  return p;
+  return plan_of(reinterpret_cast<const void*>(&gemm_f32_kernel<WM, WN, TM, TN, KS, BK, U, PF, WIDE>),
+                 64 * WM * WN * KS, tiles(M, N, WM * TM * 32, WN * TN * 32));
 }
 // PFW: sets of registers of the WIDE instance
 template <int WM, int WN, int TM, int TN, int KS, int BK, int U, int PF, int PFW = PF>
@@ -559,6 +591,9 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
   // 32-bit offsets within a step's panels: up to 256 rows of K values, 16 of N.
   // Long columns: the grid may have a second side.
   const bool wide = K >= (1 << 22) || N >= (1 << 22) || M >= (1 << 28);
+  if (K < kSplitMinTerms)
+    return plan_of(reinterpret_cast<const void*>(&gemm_f32_short<2, 2, 1, 1, 16, 4>), 256,
+                   tiles(M, N, 64, 64));
   switch (choose(M, N, K, variant)) {
     case kBig:
       // one 256 x 128 tile in the place of a CU's two of 128 x 128, where

@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 CASES = {
     # 256x128; 128x128 with two K slices and with one; 64x64 with four and two;
-    # 32x32 with eight and four; rows longer than 2^22
+    # 32x32 with eight and four; rows longer than 2^22; sums of two products
     "gemm": [(4096, 2048, 64), (1500, 1700, 1005), (1500, 1700, 65), (1024, 1024, 1024),
              (1024, 1024, 300), (96, 160, 2048), (96, 160, 264), (3, (1 << 22) + 1, 5),
-             (2, 3, (1 << 22) + 5)],
+             (2, 3, (1 << 22) + 5), (100, 130, 2)],
     # few channels; one chunk, one buffer and two; 32 x 2x16, 4x16, 8x16 and, by tap
     # rows, 8x16 and 16x16; 64 x 8x16 of nine taps and by tap rows
     "conv3x3": [(1, 8, 20, 20), (1, 16, 336, 336), (1, 16, 64, 64), (1, 32, 20, 16), (1, 64, 84, 84),

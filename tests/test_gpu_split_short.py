@@ -12,7 +12,7 @@ from oracle import kernels as OK
 pytestmark = pytest.mark.gpu
 
 
-# 32x32, 64x64, 128x128 and 256x128 tiles
+# one tile of 64x64 cut in both directions, several, many
 @pytest.mark.parametrize("M,N", [(100, 70), (700, 1100), (1537, 1665), (3900, 1930)])
 def test_short_sums(M, N):
     r = np.random.default_rng(M)
