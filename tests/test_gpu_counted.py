@@ -41,13 +41,14 @@ def test_counts_every_wavefront(op, shape):
     F.test_launch_signal_counts_every_wavefront(op, shape, -1)
 
 
-def test_counts_the_idle_workgroups_of_a_two_sided_grid():
-    M = (1 << 29) + 77
-    a, b = torch.ones(M, device=G.DEV), torch.full((1,), 2.0, device=G.DEV)
+# by the short sums' kernel and the split's
+@pytest.mark.parametrize("M,K", [((1 << 30) + 77, 1), ((1 << 29) + 77, 3)])
+def test_counts_the_idle_workgroups_of_a_two_sided_grid(M, K):
+    a, b = torch.ones(M, K, device=G.DEV), torch.full((K,), 2.0, device=G.DEV)
     c, cnt = torch.zeros(M, device=G.DEV), torch.zeros(1, dtype=torch.int32, device=G.DEV)
     torch.cuda.synchronize()
-    waves = capi.kernel_launch_signal({"op": "gemm", "shape": (M, 1, 1), "in": (0, 1), "out": (2,)},
+    waves = capi.kernel_launch_signal({"op": "gemm", "shape": (M, 1, K), "in": (0, 1), "out": (2,)},
                                       [t.data_ptr() for t in (a, b, c)], cnt.data_ptr(), 0)
     torch.cuda.synchronize()
-    assert plan("gemm", (M, 1, 1)).grid.y > 1 and cnt.item() == waves
-    assert (c == 2).all()
+    assert plan("gemm", (M, 1, K)).grid.y > 1 and cnt.item() == waves
+    assert (c == 2 * K).all()

@@ -15,14 +15,19 @@ def _ints(n, seed):
     return torch.randint(-8, 9, (n,), generator=g, device=G.DEV, dtype=torch.int8).float()
 
 
-@pytest.mark.parametrize("M,N", [((1 << 29) + 77, 1), (1, (1 << 30) + 77)])
-def test_gemm_of_one_column_or_row(M, N):
-    long = _ints(max(M, N), 1)
-    one = torch.full((1,), 3.0, device=G.DEV)
-    c = torch.full((max(M, N),), float("nan"), device=G.DEV)
-    a, b = (long, one) if N == 1 else (one, long)
-    G.launch({"op": "gemm", "shape": (M, N, 1), "in": (0, 1), "out": (2,)}, [a, b, c])
-    assert torch.equal(c, long * 3.0)
+# one product a value, and three (the split's tiles have more threads)
+@pytest.mark.parametrize("M,N,K", [((1 << 30) + 77, 1, 1), (1, (1 << 30) + 77, 1),
+                                   ((1 << 29) + 77, 1, 3), (1, (1 << 29) + 77, 3)])
+def test_gemm_of_one_column_or_row(M, N, K):
+    n = max(M, N)
+    long = _ints(n * K, 1)
+    few = torch.tensor([3.0, -2.0, 5.0], device=G.DEV)[:K].contiguous()
+    c = torch.full((n,), float("nan"), device=G.DEV)
+    a, b = (long, few) if N == 1 else (few, long)
+    G.launch({"op": "gemm", "shape": (M, N, K), "in": (0, 1), "out": (2,)}, [a, b, c])
+    terms = long.view(n, K).unbind(1) if N == 1 else long.view(K, n).unbind(0)
+    want = sum(t * f.item() for t, f in zip(terms, few))
+    assert torch.equal(c, want)
 
 
 def test_fp8_of_one_column():

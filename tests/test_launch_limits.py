@@ -28,7 +28,8 @@ def plan(op, shape):
 
 @pytest.mark.parametrize("op,shape", [
     ("gemm", (680431841, 8, 10)), ("gemm", (3, 1284745033, 2)), ("gemm", ((1 << 31) - 1, 1, 1)),
-    ("gemm", (1, (1 << 31) - 1, 1)), ("gemm", (1 << 28, 60, 32)),
+    ("gemm", (1, (1 << 31) - 1, 1)), ("gemm", ((1 << 31) - 1, 1, 4)),
+    ("gemm", (1, (1 << 31) - 1, 4)), ("gemm", (1 << 28, 60, 32)),
     ("gemm_fp8", (2, 1703227788, 32)), ("gemm_fp8", (1611767944, 4, 32)),
     ("gemm_fp8", (1565754663, 1, 16)), ("gemm_bf16", ((1 << 30) - 1, 4, 32)),
     ("conv3x3", (15871663, 30, 2, 2)), ("conv3x3", (5376279, 22, 1, 25)),
