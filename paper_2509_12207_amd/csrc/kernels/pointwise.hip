@@ -91,9 +91,11 @@ __global__ __launch_bounds__(256) void bias_relu_scalar(const float* __restrict_
 }
 
 // ---------------------------------------------------------------- reductions
+// over the LANES lanes that a lane's index / LANES has in common
+template <int LANES = 64>
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  for (int off = LANES / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
@@ -115,18 +117,18 @@ __device__ __forceinline__ RowParts row_parts(const float* z, int64_t L) {
   return {(int)h, (int)(L - h - 4 * n4), n4};
 }
 
-// WAVES waves per row, U float4 per lane in flight (a chain of dependent
-// rounds of loads is what a row costs: 1280 rows of 2048 took 5.6 us with one
+// T lanes per row (a part of a wave, or whole waves), U float4 per lane in
+// flight (a chain of dependent rounds of loads is what a row costs: 1280 rows of 2048 took 5.6 us with one
 // load in flight a lane, 3.4 with eight; 32 rows of 65536 9.9 us with one
 // workgroup of four waves, 5.0 with sixteen waves).  Rows of any alignment are
 // read 16 bytes at a time (235 rows of 21025: 10.3 us element by element, 4.6
 // so).  Partial sums are combined in a fixed order.
-template <int WAVES, int U>
-__global__ __launch_bounds__(WAVES <= 4 ? 256 : 64 * WAVES) void rowsum_rows(
+template <int T, int U>
+__global__ __launch_bounds__(T <= 256 ? 256 : T) void rowsum_rows(
     const float* __restrict__ Z, float* __restrict__ r, int64_t R, int64_t C) {
-  constexpr int T = WAVES * 64;                    // lanes per row
-  constexpr int ROWS = WAVES <= 4 ? 256 / T : 1;   // rows per workgroup
-  __shared__ float part[ROWS * WAVES];
+  constexpr int WAVES = T / 64;                // of a row
+  constexpr int ROWS = T <= 256 ? 256 / T : 1;   // rows per workgroup
+  __shared__ float part[WAVES > 1 ? ROWS * WAVES : 1];
   const int t = threadIdx.x % T, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * ROWS + threadIdx.x / T;
   float s = 0.f;
@@ -161,16 +163,16 @@ __global__ __launch_bounds__(WAVES <= 4 ? 256 : 64 * WAVES) void rowsum_rows(
       for (int w = 0; w + u < U; w += 2 * u) a[w] += a[w + u];
     s = a[0] + e;
   }
-  s = wave_sum(s);
-  if (WAVES == 1) {
-    if (lane == 0 && row < R) r[row] = s;
+  s = wave_sum<(T < 64 ? T : 64)>(s);
+  if constexpr (WAVES <= 1) {
+    if (t == 0 && row < R) r[row] = s;
     return;
   }
   if (lane == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
   if (t == 0 && row < R) {
     const float* q = part + threadIdx.x / T * WAVES;
-    float v[WAVES];
+    float v[WAVES > 1 ? WAVES : 1];
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) v[w] = q[w];
 #pragma unroll
@@ -342,29 +344,30 @@ hipError_t bias_relu_f32_launch(const float* X, const float* b, float* Y, int64_
   return hipGetLastError();
 }
 
-// One wave a row up to 512 floats (two float4 a lane), four waves a row from
-// there, sixteen where the rows are long and four waves of each would leave
-// CUs with little in flight.
-OpPlan rowsum_f32_plan(int64_t R, int64_t C) {
+namespace {
+template <int T, int U>
+OpPlan rowsum_plan(int64_t R) {
+  constexpr int rows = T <= 256 ? 256 / T : 1;
   OpPlan p;
-  if (C <= 512) {
-    p.func = reinterpret_cast<const void*>(&rowsum_rows<1, 2>);
-    p.grid = dim3((unsigned)((R + 3) / 4));
-    p.block = dim3(256);
-  } else if (C <= 2048) {
-    p.func = reinterpret_cast<const void*>(&rowsum_rows<1, 8>);
-    p.grid = dim3((unsigned)((R + 3) / 4));
-    p.block = dim3(256);
-  } else if (C <= 8192 || R >= 1024) {
-    p.func = reinterpret_cast<const void*>(&rowsum_rows<4, 4>);
-    p.grid = dim3((unsigned)R);
-    p.block = dim3(256);
-  } else {
-    p.func = reinterpret_cast<const void*>(&rowsum_rows<16, 4>);
-    p.grid = dim3((unsigned)R);
-    p.block = dim3(1024);
-  }
+  p.func = reinterpret_cast<const void*>(&rowsum_rows<T, U>);
+  p.grid = dim3((unsigned)((R + rows - 1) / rows));
+  p.block = dim3(rows * T);
   return p;
+}
+}  // namespace
+
+// One wave a row up to 2048 floats, four from there, sixteen where the rows are
+// long and four waves of each would leave CUs with little in flight.  Many short
+// rows cost workgroups: sixteen lanes a row up to 128 floats (two float4 a lane;
+// 47144 rows of 57, one wave a row 7.5 us, so 3.1), 32 up to 512 (four; 40000 of
+// 200, 8.1 and 6.3).  Up to 8192 rows one wave is as fast (3.1 us, the launch).
+OpPlan rowsum_f32_plan(int64_t R, int64_t C) {
+  if (R > 8192 && C <= 128) return rowsum_plan<16, 2>(R);
+  if (R > 8192 && C <= 512) return rowsum_plan<32, 4>(R);
+  if (C <= 512) return rowsum_plan<64, 2>(R);
+  if (C <= 2048) return rowsum_plan<64, 8>(R);
+  if (C <= 8192 || R >= 1024) return rowsum_plan<256, 4>(R);
+  return rowsum_plan<1024, 4>(R);
 }
 
 hipError_t rowsum_f32_launch(const float* Z, float* r, int64_t R, int64_t C, hipStream_t s) {
