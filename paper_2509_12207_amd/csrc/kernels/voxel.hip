@@ -11,7 +11,11 @@
 //   global memory, on values that need no decoding afterwards (zmax as the
 //   float itself, see put_zmax; first as unsigned, -1 last): two launches
 //   (20 000 points 6.3 us, three launches 8.6).  Bound by the atomics, about
-//   27 G/s whatever their scope.
+//   27 G/s whatever their scope.  Many points a cell wait for each other there, and
+//   the two atomics that the float's sign chooses from cost more than a third
+//   launch: such clouds keep zmax as an ordered key, one atomic, and decode it
+//   at the end (dense; 27 000 points in 836 cells 18.5 us against 20.3, 487 000
+//   in 1316 234 against 299).
 //
 // * listed (56 Ki to 1 Mi points, no workspace): per chunk, the points sorted
 //   by tile of the grid, as 16-bit places kept in the chunk's own part of
@@ -23,7 +27,7 @@
 //   15.4 -> 11.1, 200 000 27.5 -> 12.8, 400 000 49.7 -> 17.7, 1 M 117 -> 31;
 //   all points in one cell, 400 000: 5070 -> 1150.  (A cloud almost all
 //   outside of the grid has no atomics to save: 400 000 points, 2 % inside,
-//   6.9 -> 12.5.)
+//   6.9 -> 12.5; 15 % inside, 140 000 points 9.0 -> 11.1.)
 //
 // * binned (large clouds): the grid is cut into tiles of kTileCells cells,
 //   small enough that one tile's accumulators live in LDS.  A tile takes its
@@ -88,15 +92,23 @@ __device__ __forceinline__ int cell_of(float4 p, int nx, int ny, float xmin, flo
 }
 
 // ------------------------------------------------------------------ direct
+// KEYED: zmax holds keys until voxel_decode.
+template <bool KEYED>
 __global__ __launch_bounds__(256) void voxel_init(int* __restrict__ count,
                                                   float* __restrict__ zmax,
                                                   int* __restrict__ first, int64_t G) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < G; i += stride) {
     count[i] = 0;
-    zmax[i] = -INFINITY;
+    zmax[i] = KEYED ? __uint_as_float(kKeyNegInf) : -INFINITY;
     first[i] = -1;
   }
+}
+
+__global__ __launch_bounds__(256) void voxel_decode(float* __restrict__ zmax, int64_t G) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < G; i += stride)
+    zmax[i] = zval(__float_as_uint(zmax[i]));
 }
 
 // Float maximum (-0 < +0) with integer atomics: of values without the sign
@@ -111,6 +123,7 @@ __device__ __forceinline__ void put_zmax(float* at, float z) {
     atomicMax(reinterpret_cast<int*>(at), (int)u);
 }
 
+template <bool KEYED>
 __global__ __launch_bounds__(256) void voxel_scatter(const float4* __restrict__ pts,
                                                      int* __restrict__ vidx,
                                                      int* __restrict__ count,
@@ -123,7 +136,10 @@ __global__ __launch_bounds__(256) void voxel_scatter(const float4* __restrict__ 
     const int v = cell_of(p, nx, ny, xmin, ymin, scale);
     if (v >= 0) {
       atomicAdd(&count[v], 1);
-      put_zmax(&zmax[v], p.z);
+      if (KEYED)
+        atomicMax(reinterpret_cast<unsigned*>(&zmax[v]), zkey(p.z));
+      else
+        put_zmax(&zmax[v], p.z);
       atomicMin(reinterpret_cast<unsigned*>(&first[v]), (unsigned)i);   // -1 is the largest
     }
     vidx[i] = v;
@@ -592,6 +608,11 @@ Listed listed(int64_t N, int64_t G) {
 
 }  // namespace
 
+// Direct clouds whose cells are contended (us, float / keys: 52 600 points, 14.5 a
+// cell 25.4 / 21.9; 55 000, 17 a cell 15.8 / 15.9; 49 000, 7 a cell 17.3 / 16.7; 30 000, 7 a
+// cell 7.7 / 9.3).
+static bool dense(int64_t N, int64_t G) { return N >= (24 << 10) && N >= 12 * G; }
+
 size_t voxel_f32_workspace(int64_t N, int nx, int ny) {
   const int64_t G = (int64_t)nx * ny;
   return use_binned(N, G) ? binned_layout(N, G).total : 0;
@@ -602,11 +623,14 @@ OpPlan voxel_f32_plan(int64_t N, int nx, int ny) {
   p.block = dim3(256);
   const int64_t G = (int64_t)nx * ny;
   if (use_binned(N, G)) {
-    // the widest of the five launches: one lane per cell in the merge
+    // the widest of the three launches: one lane per cell in the merge
     p.func = reinterpret_cast<const void*>(&voxel_merge);
     p.grid = dim3(grid_for(G, INT_MAX));
   } else {
-    p.func = reinterpret_cast<const void*>(&voxel_scatter);
+    // one lane per point
+    p.func = listed(N, G).tb ? reinterpret_cast<const void*>(&voxel_cells)
+             : dense(N, G) ? reinterpret_cast<const void*>(&voxel_scatter<true>)
+                           : reinterpret_cast<const void*>(&voxel_scatter<false>);
     p.grid = dim3(grid_for(N, 256 * 32));
   }
   return p;
@@ -655,10 +679,18 @@ hipError_t voxel_f32_launch(const float* pts, int* vidx, int* count, float* zmax
                        xmin, ymin, scale);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(voxel_init, dim3(grid_for(G, 256 * 8)), blk, 0, s, count, zmax, first, G);
+  const dim3 cells(grid_for(G, 256 * 8)), points(grid_for(N, 256 * 32));
+  if (dense(N, G)) {
+    hipLaunchKernelGGL(voxel_init<true>, cells, blk, 0, s, count, zmax, first, G);
+    hipLaunchKernelGGL(voxel_scatter<true>, points, blk, 0, s, p4, vidx, count, zmax, first, N, nx,
+                       ny, xmin, ymin, scale);
+    hipLaunchKernelGGL(voxel_decode, cells, blk, 0, s, zmax, G);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(voxel_init<false>, cells, blk, 0, s, count, zmax, first, G);
   if (N > 0) {
-    hipLaunchKernelGGL(voxel_scatter, dim3(grid_for(N, 256 * 32)), blk, 0, s, p4, vidx, count,
-                       zmax, first, N, nx, ny, xmin, ymin, scale);
+    hipLaunchKernelGGL(voxel_scatter<false>, points, blk, 0, s, p4, vidx, count, zmax, first, N, nx,
+                       ny, xmin, ymin, scale);
   }
   return hipGetLastError();
 }
