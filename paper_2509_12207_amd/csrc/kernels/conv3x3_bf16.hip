@@ -37,8 +37,6 @@
 namespace ug {
 namespace {
 
-constexpr int kXcds = 8;
-
 template <int WM, int WN, int TM, int TN, int TH, int TW, int CG, int TS, int NST>
 struct Patch {
   static constexpr int BM = WM * TM * 32, WAVES = WM * WN, NT = 64 * WAVES;

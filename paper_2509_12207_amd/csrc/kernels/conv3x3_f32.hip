@@ -40,12 +40,12 @@
 #include "signal.hpp"
 #include "split.hpp"
 #include "submit.hpp"
+#include "tile_map.hpp"
 
 namespace ug {
 namespace {
 
 constexpr int CC = 16;         // input channels per chunk: one matrix instruction a tap
-constexpr int kXcds = 8;
 
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -81,6 +81,15 @@ struct ConvCfg {
   static_assert(WN * TN * 32 == TH * TW && TW == 16, "pixel tile");
   static_assert(LDS >= ExactCfg<WM, WN, TM, TN, KS, TH, TW>::BYTES, "unsplit values fit in LDS");
 };
+
+// Splits four channels into the three pieces at `at`, `piece` bytes apart.
+__device__ __forceinline__ void put(float a, float b, float c, float d, unsigned char* at, int piece) {
+  uint2 p[3];
+  split2(a, b, &p[0].x, &p[1].x, &p[2].x);
+  split2(c, d, &p[0].y, &p[1].y, &p[2].y);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
+}
 
 // Column of pixel p of a tile: a row of the tile starts two pixels on, so that
 // the sixteen pixels of a row and those of the next, 18 apart in the patch,
@@ -301,13 +310,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void conv3x3_f32_kernel(
     left -= CC * 36;
     xp += CC * plane;
     cl -= CC;
-  };
-  auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
-    uint2 p[3];
-    split2(a, b, &p[0].x, &p[1].x, &p[2].x);
-    split2(c, d, &p[0].y, &p[1].y, &p[2].y);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
   };
   int wst = 0, xst = 0;   // offsets of the buffers staged into
   auto store_w = [&]() {
@@ -560,13 +562,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void conv3x3_f32_rows(
     }
     xp += CC * plane;
     cl -= CC;
-  };
-  auto put = [&](float a, float b, float c, float d, unsigned char* at, int piece) {
-    uint2 p[3];
-    split2(a, b, &p[0].x, &p[1].x, &p[2].x);
-    split2(c, d, &p[0].y, &p[1].y, &p[2].y);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(at + j * piece) = p[j];
   };
   int wst = 0, xst = 0;   // offsets of the buffers staged into
   auto store_w = [&](int t) {

@@ -42,33 +42,15 @@
 // Workgroups are dispatched round-robin over the 8 XCDs; the linear id is
 // remapped so each XCD works on a contiguous band of output tiles (sharing A
 // and B panels in its own L2), walked in groups of 8 tile-rows.
-#include <type_traits>
-
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
 #include "split.hpp"
 #include "submit.hpp"
+#include "tile_map.hpp"
 
 namespace ug {
 namespace {
-
-constexpr int kXcds = 8;
-constexpr int kGroupM = 8;
-// s_waitcnt lgkmcnt(0) with the vmcnt and expcnt fields at their maxima
-constexpr int kWaitLdsOnly = 15 | (3 << 14) | (7 << 4) | (0 << 8);
-
-__device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* tm, int* tn) {
-  const int total = tiles_m * tiles_n;
-  const int x = wg % kXcds;   // XCDs below total % kXcds have one tile more
-  const int id = x * (total / kXcds) + min(x, total % kXcds) + wg / kXcds;
-  const int group = kGroupM * tiles_n;
-  const int first_m = (id / group) * kGroupM;
-  const int gm = min(tiles_m - first_m, kGroupM);
-  const int r = id % group;
-  *tm = first_m + r % gm;
-  *tn = r / gm;
-}
 
 template <int WM, int WN, int TM, int TN, int KS, int BK, int U>
 struct GemmCfg {
@@ -83,18 +65,15 @@ struct GemmCfg {
   static constexpr int AU = BM * UPR / NT, BU = BN * UPR / NT;   // units per thread
   static constexpr int LDS = 2 * STAGE;                // bytes
   static constexpr int RAW = BKT + 1;                  // floats per row of unsplit values
-  static_assert(BK == 16 || BK == 32, "one or two matrix instructions per row");
+  static_assert(BK == 16, "one matrix instruction per row");
   static_assert(BM * UPR % NT == 0 && BN * UPR % NT == 0, "even split of the units");
   static_assert(LDS >= 4 * ROWS * RAW, "unsplit values fit in LDS");
   static_assert(KS == 1 || LDS >= (KS - 1) * 4096 * TM * TN * WM * WN, "reduction fits in LDS");
 };
 
-// The 16-byte chunks of a row are permuted so that a read of one chunk by
+// The two 16-byte chunks of a row are permuted so that a read of one chunk by
 // sixteen consecutive rows touches all 64 LDS banks once.
-template <int BK>
-__device__ __forceinline__ int swz(int row) {
-  return BK == 32 ? (row >> 2) & 3 : (row >> 3) & 1;
-}
+__device__ __forceinline__ int swz(int row) { return (row >> 3) & 1; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -279,7 +258,7 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   int oa[G::AU], ob[G::BU];       // its LDS place (piece 0)
   const auto place = [](int r, int q) {
     const int k = q * U % BK;   // in the row
-    return q * U / BK * 3 * G::PIECE + r * G::ROWB + 16 * ((k / 8) ^ swz<BK>(r)) + 2 * (k % 8);
+    return q * U / BK * 3 * G::PIECE + r * G::ROWB + 16 * ((k / 8) ^ swz(r)) + 2 * (k % 8);
   };
 #pragma unroll
   for (int i = 0; i < G::AU; ++i) {
@@ -376,7 +355,7 @@ __launch_bounds__(64 * WM * WN * KS, (TM * TN < 4 && WM * WN * KS >= 8 ? 4 : 2))
   int fa[KH], fb[KH];
 #pragma unroll
   for (int h = 0; h < KH; ++h) {
-    const int c = ks * 3 * G::PIECE + 16 * ((2 * h + half) ^ swz<BK>(col));
+    const int c = ks * 3 * G::PIECE + 16 * ((2 * h + half) ^ swz(col));
     fa[h] = c + (wm * TM * 32 + col) * G::ROWB;
     fb[h] = c + (BM + wn * TN * 32 + col) * G::ROWB;
   }

@@ -52,26 +52,12 @@
 #include "ops.hpp"
 #include "signal.hpp"
 #include "submit.hpp"
+#include "tile_map.hpp"
 
 namespace ug {
 namespace {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-constexpr int kXcds = 8;
-constexpr int kGroupM = 8;
-
-__device__ __forceinline__ void tile_of(int wg, int tiles_m, int tiles_n, int* tm, int* tn) {
-  const int total = tiles_m * tiles_n;
-  const int x = wg % kXcds;   // XCDs below total % kXcds have one tile more
-  const int id = x * (total / kXcds) + min(x, total % kXcds) + wg / kXcds;
-  const int group = kGroupM * tiles_n;
-  const int first_m = (id / group) * kGroupM;
-  const int gm = min(tiles_m - first_m, kGroupM);
-  const int r = id % group;
-  *tm = first_m + r % gm;
-  *tn = r / gm;
-}
 
 // ------------------------------------------------------------ ring kernel
 constexpr int RK = 64;                       // bytes of K per step

@@ -9,14 +9,13 @@
 
 #include <hip/hip_runtime.h>
 
+#include "tile_map.hpp"
+
 namespace ug {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ bf16x8 as_bf16x8(int4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-// s_waitcnt lgkmcnt(0) with the vmcnt and expcnt fields at their maxima
-constexpr int kWaitLdsOnly = 15 | (3 << 14) | (7 << 4) | (0 << 8);
 
 // s_waitcnt vmcnt(N): all but this wave's N most recent loads have arrived
 template <int N>
