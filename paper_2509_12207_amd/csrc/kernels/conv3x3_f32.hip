@@ -482,7 +482,10 @@ struct RowsCfg {
   static constexpr int NT = 64 * WM * WN, BM = WM * TM * 32;
   static constexpr int PH = TH + 2, PW = TW + 2, PX = PH * PW;
   static constexpr int PXP = (PX + 31) / 32 * 32;
-  static constexpr int WH = BM * 16 + 128, WT = 6 * WH, XH = PX * 16;
+  // bytes between the halves of the weights: staging writes in different banks,
+  // or, for 32 x 8x16, three workgroups a CU (C = 20, 264^2 16.6 -> 13.2 us)
+  static constexpr int WP = BM == 32 && TH == 8 ? 16 : 128;
+  static constexpr int WH = BM * 16 + WP, WT = 6 * WH, XH = PX * 16;
   static constexpr int WS = 3 * WT, XS = 6 * XH;          // bytes per buffer
   static constexpr int LDS = 2 * (WS + XS);
   static constexpr int XU = (PXP * 4 + NT - 1) / NT;
@@ -724,11 +727,12 @@ int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
 }
 
 // Nine taps at once where one round of the CUs holds the workgroups, by tap rows
-// past that, two to a CU.  64 x 8x16: C=128 128^2, 256 workgroups: 27.1 against
+// past that, two and three to a CU.  64 x 8x16: C=128 128^2, 256 workgroups: 27.1 against
 // 30.7 us; C=256 80^2, 200: 43.9 and 59.2; C=64 200^2, 325: 29.3 and 24.4; C=128
 // 192^2, 576: 75.2 and 73.7; C=236 145^2, 760: 134 and 132; C=256 256^2, 2048: 391
-// and 372.  32 x 8x16 by tap rows, against a second round of 32 x 16x16: C=20
-// 264^2, 561 workgroups: 16.6 and 18.9 us; C=32 336^2, 882: 21.1 and 21.7.
+// and 372.  32 x 8x16 by tap rows, three to a CU, against a second round of
+// 32 x 16x16: C=20 264^2, 561 workgroups: 13.2 and 18.9 us; C=32 336^2, 882: 19.7 and
+// 21.1.
 bool by_rows(const Shape& t, int64_t N, int64_t C, int64_t H, int64_t W) {
   return wgs(t, N, C, H, W) > 256;
 }

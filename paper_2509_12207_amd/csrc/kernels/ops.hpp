@@ -113,8 +113,8 @@ OpPlan plan_kernel(const ug_kernel& k, int variant = -1);
 int chosen_variant(const ug_kernel& k);
 
 // Tile variants of an operation's launcher (0: one tile shape only): FP32
-// GEMM 3 (128x128, 64x64, 32x32 with a four-way K split), FP32 convolution
-// 5 (see conv3x3_f32.hip).  The launchers and plans of those operations take
+// GEMM 3 (see gemm_f32.hip, pick), FP32 convolution 5 (see conv3x3_f32.hip,
+// kShapes).  The launchers and plans of those operations take
 // a variant; -1 means: the tuning table's entry for the shape, else the
 // launcher's fixed rule.
 int tile_variants(int32_t op);

@@ -1,4 +1,5 @@
-// FP32 products on the BF16 matrix cores of gfx950, with FP32 accuracy.
+// FP32 products on the BF16 matrix cores of gfx950, with FP32 accuracy (the
+// three-way bfloat16 split of Henry, Tang and Heinecke, 2019).
 //
 // An FP32 value is exactly the sum of three bfloat16 values: h is x rounded
 // to nearest, m is x - h rounded to nearest, l is the rest (24 = 3 x 8
@@ -11,7 +12,11 @@
 // per 16 products, where the FP32 instruction rounds once per product, so the
 // sum is closer to the exact one: against fp64 the error (rms) of a K-long
 // product is 0.28-0.40 of the FP32 instruction's for uniform and normal values
-// and K = 32 to 4096, and 0.36-0.48 where all products are positive.
+// and K = 32 to 4096, and 0.36-0.48 where all products are positive; from
+// three terms on it is smaller (kSplitMinTerms).  A sum with one term that is
+// not zero errs by up to 1.63 x 2^-24 of it, where the FP32 instruction rounds
+// it correctly (the split too, if a factor has at most eight significant bits:
+// a permutation's one).
 //
 // Rate: six v_mfma_f32_32x32x16_bf16 (32 cycles each) take the place of eight
 // v_mfma_f32_32x32x2_f32 (64 cycles each): 2.67 times fewer matrix cycles.
