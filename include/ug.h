@@ -576,7 +576,10 @@ int32_t ug_poll_complete(void* ctx, ug_completion* out, uint32_t cap);
 
 /* Waits up to timeout_ns until every submitted frame has completed
  * (completions stay queued for ug_poll_complete): the end of a run over
- * which Eq. 3 is evaluated.  Errors: UG_ETIMEDOUT, UG_EDEVICE. */
+ * which Eq. 3 is evaluated.  The first 200 us of the wait keep the caller's
+ * core busy (a frame of a few short kernels is over before a sleeping caller
+ * would be awake again); after that the caller sleeps.  Errors:
+ * UG_ETIMEDOUT, UG_EDEVICE. */
 ug_status ug_drain(void* ctx, int64_t timeout_ns);
 
 /* Stops the gate thread after ug_drain and waits for the stream pool to
@@ -795,11 +798,12 @@ ug_status ug_launch_cost(const ug_kernel* k, void* const* buffers, uint32_t n_bu
                          uint32_t n, void* hip_stream, int64_t* host_ns, int64_t* gpu_ns);
 
 /* Tile variants (the autotuner of configuration 2).  The FP32 GEMM has 3
- * tile shapes (0: 128x128 or 256x128, 1: 64x64 with a K split of two or four, 2: 32x32
- * with a K split of four or eight) and the FP32 3x3 convolution 5 (output
- * channels x pixel patch, 0: 64 x 8x16, 1: 32 x 16x16, 2: 32 x 8x16,
- * 3: 32 x 4x16, 4: 32 x 2x16); each launcher picks one by a fixed rule unless the process-wide
- * tuning table names one for the exact (op, shape).  Every variant computes
+ * tile shapes (0: 128x128, with one or two K slices, or 256x128, 1: 64x64 with
+ * two or four K slices, 2: 32x32 with four or eight; with K of 1 and 2 all
+ * three are one kernel) and the FP32 3x3 convolution 5 (output channels x
+ * pixel patch, 0: 64 x 8x16, 1: 32 x 16x16, 2: 32 x 8x16, 3: 32 x 4x16,
+ * 4: 32 x 2x16); each launcher picks one by a fixed rule unless the
+ * process-wide tuning table names one for the exact (op, shape).  Every variant computes
  * the same sums in its own order (results within the op's tolerance, exact
  * for integer-valued inputs).  Set the table before launching (a change is
  * published as a new copy; launches in flight see the old or the new one).

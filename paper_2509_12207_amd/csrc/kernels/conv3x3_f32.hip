@@ -27,14 +27,16 @@
 // * conv3x3_f32_few: few channels, with the FP32 instruction.
 //
 // What bounds it: at C = 256, 256^2 the matrix cores are busy about 65 % of
-// the time (MFMA alone about 270 us of 370), the rest is splitting that the
+// the time (MFMA alone about 270 us of 380), the rest is splitting that the
 // other workgroup does not cover.  The small tiles are bound by the latency
 // of a chunk (loads, split, LDS, barrier: 0.9 to 1.6 us) and by the launch.
 // us per launch, FP32 instruction before -> now:
-//   C=256 256^2 670 -> 370, C=236 145^2 288 -> 130, C=128 128^2 52 -> 27.5,
-//   C=64 256^2 48 -> 30, C=256 64^2 59 -> 28.3, C=64 128^2 17.4 -> 9.5,
-//   C=128 64^2 20.5 -> 12.8, C=64 84^2 12.9 -> 8.2, C=32 128^2 9.0 -> 6.1,
-//   C=256 32^2 24 -> 16.6, C=16 64^2 5.8 -> 5.6, C=16 336^2 15.1 -> 11.5.
+//   C=256 256^2 670 -> 380, C=236 145^2 290 -> 139, C=128 128^2 52 -> 28.8,
+//   C=64 256^2 48 -> 30, C=256 64^2 58 -> 28.7, C=64 128^2 17.4 -> 10.0,
+//   C=128 64^2 20.5 -> 12.6, C=64 84^2 12.9 -> 8.4, C=32 128^2 9.0 -> 6.2,
+//   C=256 32^2 23 -> 17.0, C=16 64^2 5.7 -> 5.4, C=16 336^2 15.1 -> 11.5,
+//   C=20 264^2 14.6 -> 13.2.  One NaN in every tile: C=256 256^2 1070,
+//   C=128 128^2 69, C=64 84^2 19.0.
 #include "mfma.hpp"
 #include "ops.hpp"
 #include "signal.hpp"
@@ -714,11 +716,11 @@ int64_t wgs(const Shape& s, int64_t N, int64_t C, int64_t H, int64_t W) {
 // 32 x 4x16, 14.9 and 19.3 either side).  One chunk (C <= 16) takes
 // 32 x 8x16 on four waves, past a round of them with one buffer, so that more
 // share a CU (336^2: 11.5 us against 19.2 with two and 12.2 on twelve waves).
-// Below, where the ends of the kernel are what is left, 32 x 4x16 on six waves
-// with one buffer is faster (64^2 4.5 against 5.6, the FP32 instruction's
-// kernel 5.8) and not taken: the first three kernels of configuration 0's
-// task, nearly all launch, then profile below the 20 us that the test of its
-// launch synchronisation has batches close at.
+// Up to a round of them the second buffer is there but not used: with one, or
+// as 32 x 4x16 on six waves with one (64^2 4.5 us against 5.4, the FP32
+// instruction's kernel 5.7), the first three kernels of configuration 0's task,
+// nearly all launch, profile below the 20 us at which a test of its launch
+// synchronisation has batches close.
 int pick(int64_t N, int64_t C, int64_t H, int64_t W) {
   if (C <= CC) return 2;
   for (int i = 4; i > 0; --i)

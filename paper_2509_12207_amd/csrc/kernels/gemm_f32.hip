@@ -2,8 +2,10 @@
 //
 // Every value is split into three bfloat16 pieces as it is staged, and the
 // products are formed by the BF16 matrix instruction (split.hpp: the error
-// against fp64 is 0.28-0.48 of the FP32 instruction's, the matrix cycles 2.67
-// times fewer).
+// against fp64 is 0.28-0.48 of the FP32 instruction's from K = 32 on, the matrix
+// cycles 2.67 times fewer).  K = 1 and 2 and tiles that hold a value without a
+// split are computed by the FP32 instruction (exact_tile); one NaN in every
+// tile, us: 4096^3 2056, 1003x2050x1021 135, 1024^3 47, 256^3 10.5.
 //
 // One kernel template <WM, WN, TM, TN, KS, BK, U, PF>: the workgroup tile is
 // (WM*TM*32) x (WN*TN*32); its waves form a WM x WN x KS grid; each wave owns
@@ -20,17 +22,19 @@
 // scheduling).
 //
 // What bounds it: at 4096^3 the matrix cores; six BF16 instructions per 16
-// products sustain 1.29 PFLOP/s there, more than the library's 8192^3 BF16
+// products sustain 1.3 PFLOP/s there, more than the library's 8192^3 BF16
 // product (1.12) on the same card.  Smaller products are bound by the latency
 // of a step (global load, split, LDS, barrier) in the few waves a CU has,
 // hence eight waves for 128 x 128 (two such workgroups make four waves a
 // SIMD at 126 registers; four waves of 64 x 64 took 695 us at 4096^3 against
 // 670) and the K splits.  One tile of 256 x 128 loads and splits a quarter
 // less than two of 128 x 128 (4096^3: 661 -> 640 us).
-// us per launch, FP32 instruction before -> now:
-//   4096^3 1170 -> 616, 2048^3 170 -> 87, 1280x2048x1024 65 -> 42,
-//   1003x2050x1021 102 -> 41, 1024^3 33 -> 18.3, 768x1280x256 11.1 -> 7.2,
-//   512^3 8.8 -> 7.1, 256x256x2048 26 -> 16, 256^3 5.8 -> 5.2.
+// (Figures side by side are of one session; sessions differ by up to 5 % at
+// 4096^3, where the clock gives way, and by 1 to 3 % below.)
+// us per launch, launched in a row, FP32 instruction before -> now:
+//   4096^3 1109 -> 631, 2048^3 164 -> 92, 1280x2048x1024 65 -> 42,
+//   1003x2050x1021 98 -> 41.5, 1024^3 33 -> 18.1, 768x1280x256 11.0 -> 7.4,
+//   512^3 8.8 -> 7.3, 256x256x2048 26 -> 16.6, 256^3 5.8 -> 5.7.
 //
 // The pipeline of a step: while the products of the m pieces run, the next
 // step's values (in registers, loaded a step ahead) are split and written to
@@ -584,9 +588,10 @@ OpPlan gemm_f32_plan(int64_t M, int64_t N, int64_t K, bool, int variant) {
         return plan<4, 2, 2, 2, 1, 16, 4, 1>(M, N, wide);
       // one tile a CU at most and K long: waves of 64 x 64, a third fewer LDS
       // reads a product, and K in two slices so that there are eight of them
-      // (2048^3 90.6 -> 87.0 us, 1500^3 59.9 -> 56.9, 1280x2048x1024 42.9 -> 41.8;
-      // K = 512 24.0 -> 25.0, K = 256 15.0 -> 16.7)
-      return K >= 1000 && tiles(M, N, 128, 128) <= 256
+      // (one slice / two, us: 1536x1792 K = 512 26.2 / 26.6, 704 31.6 / 31.7, 768
+      // 33.9 / 33.7, 960 40.9 / 40.0; 2048^2 K = 704 35.7 / 36.1, 768 39.2 / 39.2, 960
+      // 46.9 / 46.6; 2048^3 90.6 / 87.0)
+      return K >= 768 && tiles(M, N, 128, 128) <= 256
                  ? plan<2, 2, 2, 2, 2, 16, 4, 1>(M, N, wide)
                  : plan<2, 4, 2, 1, 1, 16, 4, 1>(M, N, wide);
     case kMid:

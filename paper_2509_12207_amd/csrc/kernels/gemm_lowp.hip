@@ -46,7 +46,9 @@
 // is a chain of steps whose latency (barrier, LDS, loads) K slices divide.
 // us per launch, 256 x 256 only -> now: BF16 4096^3 122 -> 117, 2048^3 47 -> 24,
 // 1280x1792x768 22 -> 9.2, 1024^3 25 -> 6.5, 512^3 16 -> 4.1, 256x256x2048
-// 42 -> 5.9; FP8 2048x8192x8192 122 -> 113, 2048^3 27 -> 14, 1024^3 15 -> 4.9.
+// 42 -> 5.9; FP8 2048x8192x8192 122 -> 113 (on one set of operands again and
+// again; 122 where they change from launch to launch), 2048^3 27 -> 14, 1024^3
+// 15 -> 4.9.
 #include "lds_load.hpp"
 #include "mfma.hpp"
 #include "ops.hpp"
