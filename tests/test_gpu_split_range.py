@@ -57,6 +57,29 @@ def test_conv_small_magnitudes(n, c, h, w, bits, e):
     assert np.all(np.abs(Y - ref) <= bound(K) * scale), np.max(np.abs(Y - ref) / scale)
 
 
+# sums past 2^96, values past 2^112 and sums that overflow only when scaled or on
+# the way: by the FP32 instruction, at most one rounding a product and a sum (the
+# sums of |products| stay below 2^128, so none overflows)
+@pytest.mark.parametrize("ea,eb", [(40, 50), (56, 60), (115, -100), (126, -60)])
+@pytest.mark.parametrize("M,N,K", GEMM[:2])
+def test_gemm_large_magnitudes(M, N, K, ea, eb):
+    r = np.random.default_rng(M + ea)
+    A, B = values(r, (M, K), ea, 23), values(r, (K, N), eb, 23)
+    C = G.run_gemm(A, B)
+    ref, scale = OK.gemm_f64(A, B), OK.gemm_abs_f64(A, B)
+    assert np.all(np.abs(C - ref) <= K * 2.0 ** -23 * scale), np.max(np.abs(C - ref) / scale)
+
+
+@pytest.mark.parametrize("ea,eb", [(56, 60), (115, -100)])
+@pytest.mark.parametrize("n,c,h,w", CONV)
+def test_conv_large_magnitudes(n, c, h, w, ea, eb):
+    r = np.random.default_rng(c + ea)
+    X, W = values(r, (n, c, h, w), ea, 23), values(r, (c, c, 3, 3), eb, 23)
+    Y = G.run_conv(X, W)
+    ref, scale = OK.conv3x3_f64(X, W), OK.conv3x3_abs_f64(X, W)
+    assert np.all(np.abs(Y - ref) <= 9 * c * 2.0 ** -23 * scale), np.max(np.abs(Y - ref) / scale)
+
+
 def _us(op, shape, a, b, out):
     desc = capi.kernel_struct({"op": op, "shape": shape, "in": (0, 1), "out": (2,)})
     ptrs = capi.pointer_array([t.data_ptr() for t in (a, b, out)])
